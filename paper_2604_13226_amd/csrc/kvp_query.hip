@@ -73,7 +73,7 @@ int launch_append(int dtype, const AppendArgs &a, void *stream)
 // ---------------------------------------------------------------------------------
 // Generic attention: one wavefront per packed row, lanes own head_dim/64 columns
 // (head_dim <= 256), online softmax over the item's kv range in fp32.  Slow but
-// shape-agnostic: the fp32 path and any shape the MFMA kernel does not take.
+// shape-agnostic: whatever the matrix-core kernels do not take.
 // ---------------------------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v)
 {
@@ -446,11 +446,13 @@ int launch_combine(int dtype, const AttnArgs &a, void *stream)
 }
 
 int launch_attention_mfma(const AttnArgs &a, void *stream);  // kvp_attention_mfma.hip
+int launch_attention_f32(const AttnArgs &a, void *stream);   // kvp_attention_f32.hip
 
 int launch_attention(int dtype, const AttnArgs &a, int kernel_kind, void *stream)
 {
     if (a.n_items == 0) return 0;
     if (kernel_kind == ATTN_MFMA) return launch_attention_mfma(a, stream);
+    if (kernel_kind == ATTN_F32) return dtype == 0 ? launch_attention_f32(a, stream) : (int)hipErrorInvalidValue;
     if (dtype == 1) hipLaunchKernelGGL((attention_generic_kernel<bf16_t>), dim3(a.n_items), dim3(256), 0, (hipStream_t)stream, a);
     else hipLaunchKernelGGL((attention_generic_kernel<float>), dim3(a.n_items), dim3(256), 0, (hipStream_t)stream, a);
     return (int)hipGetLastError();

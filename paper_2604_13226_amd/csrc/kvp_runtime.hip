@@ -1186,31 +1186,39 @@ int target_items(const kvp_store *s, int64_t tiles = 0, int bm = 0)
 // Groups of packed rows and their split-KV items.  Every group of a request gets the same
 // split length (a multiple of bn rows), chosen so the launch has about target_items work
 // items; a group's kv range stops at the last row any of its query rows may see.
-bool use_mfma(const kvp_store *s, const kvp_cache_t *c)
+int attn_kind(const kvp_store *s, const kvp_cache_t *c)
 {
     const kvp_config_t &g = s->cfg;
-    if (g.dtype != KVP_BF16 || g.head_dim != 128 || s->force_generic) return false;
-    return !(c && c->layout == KVP_PAGED && c->block_size < MFMA_MIN_BLOCK_SIZE);
+    if (s->force_generic || (c && c->layout == KVP_PAGED && c->block_size < MFMA_MIN_BLOCK_SIZE)) return ATTN_GENERIC;
+    if (g.dtype == KVP_BF16) return g.head_dim == 128 ? ATTN_MFMA : ATTN_GENERIC;
+    return g.head_dim == 64 || g.head_dim == 128 || g.head_dim == 256 ? ATTN_F32 : ATTN_GENERIC;
 }
+
+// Packed rows per row block (the MFMA kernel's smaller one).
+int base_bm(int kind) { return kind == ATTN_MFMA ? MFMA_BM : kind == ATTN_F32 ? ATTN_F32_BM : GENERIC_BM; }
 
 void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
                   PrefillPlan &p)
 {
     const kvp_config_t &g = s->cfg;
     const int gq = g.n_q_heads / g.n_kv_heads;
-    const bool mfma = use_mfma(s, cache);
-    // paged + MFMA: an item's blocks must fit the kernel's LDS id table
-    const int max_split = (mfma && cache->layout == KVP_PAGED)
+    const int kind = attn_kind(s, cache);
+    const bool mfma = kind == ATTN_MFMA;
+    // paged + matrix-core kernel: an item's blocks must fit the kernel's LDS id table
+    const int max_split = (kind != ATTN_GENERIC && cache->layout == KVP_PAGED)
                               ? (MFMA_MAX_ITEM_BLOCKS - 1) * cache->block_size / 64 * 64
                               : INT32_MAX;
-    p.kind = mfma ? ATTN_MFMA : ATTN_GENERIC;
-    p.bm = mfma ? MFMA_BM : GENERIC_BM;
+    p.kind = kind;
+    p.bm = base_bm(kind);
     if (mfma) {  // row blocks of 256 when some request has that many packed rows
         for (int r = 0; r < n_req; ++r)
             if ((int64_t)(q_off[r + 1] - q_off[r]) * gq >= 2 * MFMA_BM) p.bm = 2 * MFMA_BM;
         if (s->force_bm == 128 || s->force_bm == 256) p.bm = s->force_bm;
     }
-    const int min_split = mfma ? 256 : 64;
+    // The fp32 kernel deals a range's 32-row tiles to four waves: ranges of whole rounds of four, and
+    // no shorter than a tile takes longer than a combine launch (a tile: 2 us and more).
+    const int min_split = kind == ATTN_GENERIC ? 64 : kind == ATTN_F32 && s->target_items > 0 ? 64 : 256;
+    if (kind == ATTN_F32 && s->target_items == 0) p.bn = 128;
     p.reqs.resize(n_req);
     int64_t n_groups = 0;
     for (int r = 0; r < n_req; ++r) {
@@ -1223,7 +1231,9 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int n_req, const
     int64_t tiles = 0;  // 64-row tiles all the items together will read
     for (int r = 0; r < n_req; ++r)
         tiles += (int64_t)g.n_kv_heads * (((int64_t)p.reqs[r].n_q * gq + p.bm - 1) / p.bm) * ((p.reqs[r].ctx_len + p.reqs[r].n_q + 63) / 64);
-    int want = (int)std::min<int64_t>(MAX_SPLITS, (target_items(s, tiles, mfma ? p.bm : 0) + n_groups - 1) / n_groups);
+    // (the fp32 kernel is bound by the matrix pipe from the first tile on: an item for every CU)
+    const int target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s, tiles, mfma ? p.bm : 0);
+    int want = (int)std::min<int64_t>(MAX_SPLITS, (target + n_groups - 1) / n_groups);
     if (want < 1) want = 1;
     p.split_in_wg = mfma && streams_many_tiles(s, tiles, p.bm);
     for (int r = 0; r < n_req; ++r) {
@@ -1336,8 +1346,9 @@ uint64_t kvp_prefill_workspace_bytes(const kvp_store_t *s, int32_t n_req, int32_
     if (!s || n_req < 0 || max_tot_q < 0 || max_ctx < 0) return 0;
     const kvp_config_t &g = s->cfg;
     const int gq = g.n_q_heads / g.n_kv_heads;
-    const bool mfma = use_mfma(s, nullptr);
-    const int bm = mfma ? MFMA_BM : GENERIC_BM;  // smaller or larger row blocks need no more
+    const int kind = attn_kind(s, nullptr);
+    const bool mfma = kind == ATTN_MFMA;
+    const int bm = base_bm(kind);  // smaller or larger row blocks need no more
     // groups <= Hkv * (rows / bm + one ragged block per request); every group has at most
     // ceil(target / groups) <= target / groups + 1 splits (and never more than MAX_SPLITS)
     const uint64_t groups = (uint64_t)g.n_kv_heads * ((uint64_t)max_tot_q * gq / bm + (uint64_t)n_req);
@@ -1421,7 +1432,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         found = find_plan(s, s->pf_set, sig, hip_stream, sig_hash, hit);
     }
     kvp_store::PrefillCached &pf = *found;
-    const uint64_t qrb = use_mfma(s, cache) ? 0 : q_rot_bytes(s, tot_q);  // (the MFMA kernel rotates the query in registers)
+    const uint64_t qrb = attn_kind(s, cache) != ATTN_GENERIC ? 0 : q_rot_bytes(s, tot_q);  // (the matrix-core kernels rotate the query in registers)
     if (in_capture && !hit)
         return fail(s, KVP_E_INVAL, "kvp_query_prefill under stream capture needs the plan of an earlier call with the same "
                                     "geometry on the same stream (call it once before capturing)");
@@ -1479,7 +1490,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         }
         {
             kvp_store::DebugPlan &dp = s->dbg_plan;
-            const int64_t head[6] = {p.kind, p.bm, (int64_t)p.groups.size(), (int64_t)p.items.size(), p.n_slots, (int64_t)need};
+            const int64_t head[6] = {p.kind == ATTN_MFMA ? 1 : 0, p.bm, (int64_t)p.groups.size(), (int64_t)p.items.size(), p.n_slots, (int64_t)need};
             memcpy(dp.head, head, sizeof head);
             dp.groups.swap(p.groups);  // (already copied into the plan buffer above)
             dp.items.swap(p.items);
@@ -1521,7 +1532,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     hipStream_t st = (hipStream_t)hip_stream;
     CacheView view = make_view(s, cache, cc.shift, pf.bt_dev, pf.bt_stride);
 
-    if (pf.kind != ATTN_MFMA) {  // the MFMA kernel does the query side itself
+    if (pf.kind == ATTN_GENERIC) {  // the matrix-core kernels do the query side themselves
         AppendArgs ap;
         ap.q = q;
         ap.k_new = k_new;
