@@ -18,7 +18,8 @@
 //
 // LDS tiles are unpadded (a direct load writes 64 lanes x 16 B contiguously); bank
 // conflicts are avoided by choosing WHICH 16-byte chunk of a row each lane fetches:
-// K row r keeps logical chunk c at physical chunk c ^ (r & 15), V row r at c ^ 4 (r & 3).
+// K row r keeps logical chunk c at physical chunk c ^ (r & 15), V row r at c ^ 4 (r & 3) (64
+// columns, two rows to a pass over the banks: c ^ (r / 2 & 7) and c ^ 4 (r / 2 & 1)).
 //
 // The kernel also does the query side of the layer (Sec. 4.2.1 step 4): every workgroup
 // rotates its own 128 query rows to positions ctx_len + t in registers (the RoPE partner of
@@ -41,10 +42,7 @@ typedef __attribute__((address_space(3))) void *lds_void_p;
 typedef __attribute__((address_space(1))) const void *glb_void_p;
 
 constexpr int BN = 64;   // kv rows per tile
-constexpr int D = 128;   // head_dim
-constexpr int ROW_BYTES = D * 2;
-constexpr int TILE_BYTES = BN * ROW_BYTES;   // 16 KiB for K, same for V
-constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // K tile then V tile
+constexpr int stage_bytes(int d) { return 2 * BN * d * 2; }  // K tile then V tile
 constexpr int MAX_BLOCK_IDS = MFMA_MAX_ITEM_BLOCKS;  // paged: block ids of one item kept in LDS
 
 __device__ __forceinline__ uint32_t pack_bf16_hw(float a, float b)
@@ -227,12 +225,19 @@ __device__ unsigned long long *kvp_timing_phases;  // [item][8 waves][8]
 //   NW 8, KS 2, 4 stages: 128 rows, the two groups take alternate tiles of the item's range
 //                         (an in-workgroup split-KV that halves the serial chain of a
 //                         latency-bound item) and merge their (m, l, O) through LDS.
-template <int STAGES, int SRC, int NW, int KS, bool NTL>
+template <int D, int STAGES, int SRC, int NW, int KS, bool NTL>
 __device__ __forceinline__ void attention_body(const AttnArgs &a)
 {
+    constexpr int ROW_BYTES = D * 2;
+    constexpr int TILE_BYTES = BN * ROW_BYTES;  // of K, same for V
+    constexpr int STAGE_BYTES = 2 * TILE_BYTES;
+    constexpr int CH = D / 8;      // 16-byte chunks per row
+    constexpr int RPI = 64 / CH;   // rows one load instruction of a wave fills
+    constexpr int NKS = D / 16;    // k-steps of S^T = K Q^T
+    constexpr int EB = D / 32;     // 32-column blocks of O
     constexpr int RW = NW / KS;    // waves per group (a group owns 32 RW rows)
     constexpr int NT = 64 * NW;    // threads
-    constexpr int NI = 16 / NW;    // K (and V) load instructions per wave per tile
+    constexpr int NI = BN / RPI / NW;  // K (and V) load instructions per wave per tile
     constexpr int PR = STAGES / KS - 1;  // rounds (of KS tiles) loaded ahead
     static_assert(STAGES % KS == 0 && PR >= 1, "stages");
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -266,18 +271,21 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     const int64_t tail_off = ((int64_t)it.q_off * a.n_kv + it.kv_head) * D;
 
     // direct HBM -> LDS load of tile tj: wave w, instruction i fills tile rows
-    // 4 (NW i + w) .. +3 (1 KiB contiguous in LDS); lane l owns slot (row + l / 16, chunk l % 16)
+    // RPI (NW i + w) .. + RPI - 1 (1 KiB contiguous in LDS); lane l owns slot (row + l / CH, chunk l % CH)
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-    const int slot_row = lane >> 4, slot_chunk = lane & 15;
-    const int k_chunk = slot_chunk ^ ((4 * wave + slot_row) & 15);  // logical chunk fetched
-    const int v_chunk = slot_chunk ^ (4 * slot_row);
+    const int slot_row = lane / CH, slot_chunk = lane % CH;
+    // tile row r keeps logical chunk c of K at chunk c ^ k_swz(r), of V at c ^ 4 v_swz(r)
+    auto k_swz = [](int r) -> int { return D == 64 ? (r >> 1) & 7 : r & 15; };
+    auto v_swz = [](int r) -> int { return D == 64 ? (r >> 1) & 1 : r & 3; };
+    // logical chunks this lane fetches; the same for every instruction of a wave while NW RPI is a multiple of 16
+    const int k_chunk0 = slot_chunk ^ k_swz(RPI * wave + slot_row), v_chunk = slot_chunk ^ (4 * v_swz(RPI * wave + slot_row));
     const int last_tile_rows = it.kv_end - it.kv_begin - (n_tiles - 1) * BN;  // 1..64 (cache modes)
-    // paged layout: the LDS word with the block id of load instruction i of tile tj.  The 4 rows
-    // of one instruction lie in one block (blocks hold a multiple of 4 rows, items start at a
+    // paged layout: the LDS word with the block id of load instruction i of tile tj.  The RPI rows
+    // of one instruction lie in one block (blocks hold a multiple of 8 rows, items start at a
     // multiple of 64), clamped rows included, so the word is the same for the whole wave.
     auto blk_word = [&](int tj, int i) -> int {
         const int max_r = tj == n_tiles - 1 ? last_tile_rows - 1 : BN - 1;
-        const int rb = 4 * (NW * i + wave) < max_r ? 4 * (NW * i + wave) : max_r;
+        const int rb = RPI * (NW * i + wave) < max_r ? RPI * (NW * i + wave) : max_r;
         return blk_ids[((it.kv_begin + tj * BN + rb) >> a.cache.block_shift) - blk0];
     };
     // The loads of tile tj: NI parts per wave, each one K and one V load instruction.  tile_src
@@ -322,9 +330,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     };
     auto issue_part = [&](const TileSrc &ts, int tj, int i) {
         const uint32_t st = lds_base + (uint32_t)((tj % STAGES) * STAGE_BYTES);
-        int r = 4 * (NW * i + wave) + slot_row;
+        int r = RPI * (NW * i + wave) + slot_row;
+        const int k_chunk = NW * RPI % 16 ? slot_chunk ^ k_swz(r) : k_chunk0;
         r = r < ts.max_r ? r : ts.max_r;
-        const uint32_t dst = __builtin_amdgcn_readfirstlane(st + (uint32_t)(4 * (NW * i + wave) * ROW_BYTES));  // (wave-uniform)
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(st + (uint32_t)(RPI * (NW * i + wave) * ROW_BYTES));  // (wave-uniform)
         if (SRC != SRC_PAGED) {
             // (uniform_ptr again: should the compiler have moved the address to vector registers, it
             // comes back to scalar ones, which the instruction needs; otherwise this folds away)
@@ -356,21 +365,22 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     // smallest limit among the wave's rows (rows are ordered by query token)
     const int wave_limit = it.ctx_len + (it.m0 + 32 * wave_r) / g + 1;
 
-    // B operand of S^T = K Q^T: lane holds Q[m][16 ks + 8 h .. +7] for ks = 0..7, rotated by
-    // `rel` positions and multiplied by log2(e)/sqrt(d).  Element 16 ks + 8 h + j (ks < 4)
-    // pairs with the same slot of ks + 4, so the rotation stays inside the lane.
-    bf16x8 qf[8];
+    // B operand of S^T = K Q^T: lane holds Q[m][16 ks + 8 h .. +7] for every k-step ks, rotated by
+    // `rel` positions and multiplied by log2(e)/sqrt(d).  Element 16 ks + 8 h + j (ks < NKS / 2)
+    // pairs with the same slot of ks + NKS / 2, so the rotation stays inside the lane.
+    constexpr int NKH = NKS / 2;
+    bf16x8 qf[NKS];
     const bf16_t *qp = (const bf16_t *)a.q + ((int64_t)(it.q_off + t) * a.n_q_heads + hq) * D + 8 * h;
     const int q_pos = a.prerotated ? 0 : it.pos0 + t;  // rotation the query still needs
-    u32x4_t qraw[8], csraw[16];
-    auto q_issue = [&](int delta) {  // 24 loads: the raw query row and the (cos, sin) of its rotation
+    u32x4_t qraw[NKS], csraw[4 * NKH];
+    auto q_issue = [&](int delta) {  // 3 D / 16 loads: the raw query row and the (cos, sin) of its rotation
         const bf16_t *qsrc = row_ok ? qp : (const bf16_t *)a.q + 8 * h;  // idle lanes read row 0 (and drop it)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qraw[ks] = load16_nowait(qsrc + 16 * ks);
+        for (int ks = 0; ks < NKS; ++ks) qraw[ks] = load16_nowait(qsrc + 16 * ks);
         const int rel = row_ok ? q_pos - delta : 0;
-        const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * 64 + 8 * h);
+        const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * (D / 2) + 8 * h);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < NKH; ++ks)
 #pragma unroll
             for (int j = 0; j < 4; ++j) csraw[4 * ks + j] = load16_nowait(csr + 8 * ks + j);
     };
@@ -382,52 +392,55 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         else wait_vmcnt<0>();
         // the registers are valid from here on: keep every use below this point
 #pragma unroll
-        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(qraw[i]));
+        for (int i = 0; i < NKS; ++i) asm volatile("" : "+v"(qraw[i]));
 #pragma unroll
-        for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(csraw[i]));
+        for (int i = 0; i < 4 * NKH; ++i) asm volatile("" : "+v"(csraw[i]));
         const int rel = row_ok ? q_pos - delta : 0;
         const float sign = rel < 0 ? -1.f : 1.f;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int ks = 0; ks < NKH; ++ks) {
             float4 cs4[4];  // (cos, sin) pairs of elements 16 ks + 8 h + 2 j, + 1
 #pragma unroll
             for (int j = 0; j < 4; ++j) cs4[j] = __builtin_bit_cast(float4, csraw[4 * ks + j]);
-            uint4 lo = __builtin_bit_cast(uint4, qraw[ks]), hi = __builtin_bit_cast(uint4, qraw[ks + 4]);
+            uint4 lo = __builtin_bit_cast(uint4, qraw[ks]), hi = __builtin_bit_cast(uint4, qraw[ks + NKH]);
             if (!row_ok) lo = hi = make_uint4(0, 0, 0, 0);
             uint4 olo, ohi;
             rotate_chunk_pair<false>(lo, hi, cs4, sign, a.scale_log2e, olo, ohi);
             qf[ks] = __builtin_bit_cast(bf16x8, olo);
-            qf[ks + 4] = __builtin_bit_cast(bf16x8, ohi);
+            qf[ks + NKH] = __builtin_bit_cast(bf16x8, ohi);
         }
         // pinned: nothing of this is recomputed or waited for inside the tile loop
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
+        for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[ks]));
     };
-    // Re-rotation inside the tile loop (in-place packet reads, at every packet boundary): plain
-    // loads, whose wait the compiler places (it drains the tile loads in flight as well).
+    // Re-rotation inside the tile loop (in-place packet reads, at every packet boundary; and the only
+    // rotation of 256 columns): plain loads, whose wait the compiler places (it drains the tile loads in flight as well).
     auto reload_q = [&](int delta) {
-        uint4 qr[8];
+        uint4 qr[NKS];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qr[ks] = row_ok ? *(const uint4 *)(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
+        for (int ks = 0; ks < NKS; ++ks) qr[ks] = row_ok ? *(const uint4 *)(qp + 16 * ks) : make_uint4(0, 0, 0, 0);
         const int rel = row_ok ? q_pos - delta : 0;
         const float sign = rel < 0 ? -1.f : 1.f;
-        const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * 64 + 8 * h);
+        const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * (D / 2) + 8 * h);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int ks = 0; ks < NKH; ++ks) {
             float4 cs4[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) cs4[j] = csr[8 * ks + j];
             uint4 olo, ohi;
-            rotate_chunk_pair<false>(qr[ks], qr[ks + 4], cs4, sign, a.scale_log2e, olo, ohi);
+            rotate_chunk_pair<false>(qr[ks], qr[ks + NKH], cs4, sign, a.scale_log2e, olo, ohi);
             qf[ks] = __builtin_bit_cast(bf16x8, olo);
-            qf[ks + 4] = __builtin_bit_cast(bf16x8, ohi);
+            qf[ks + NKH] = __builtin_bit_cast(bf16x8, ohi);
         }
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
+        for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[ks]));
     };
     int cur_delta = SRC == SRC_PACKETS && n_tiles > 0 ? load_tile_record(a.tiles, it.kv_begin).pos : 0;
     KVP_STAMP(1);
-    q_issue(cur_delta);  // first, so that the query arrives ahead of the tiles
+    // (256 columns: the loads in flight would not fit the vector registers, and one the compiler moved
+    // to an accumulation register before its data has arrived would be lost: plain loads there)
+    constexpr bool OWN_WAIT = D <= 128;
+    if (OWN_WAIT) q_issue(cur_delta);  // first, so that the query arrives ahead of the tiles
     if (SRC == SRC_PAGED) {  // the block ids travel while the query does
         const int nb = (kv_last >> a.cache.block_shift) - blk0 + 1;
         for (int i = tid; i < nb; i += NT)
@@ -454,7 +467,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         if (n_tail > 0) {
             bf16_t *kcw = SRC == SRC_PACKETS ? (bf16_t *)a.k_tail : (bf16_t *)a.cache.k;
             bf16_t *vcw = (bf16_t *)a.cache.v;
-            // Work units: 8 K chunk pairs per row (rotate, store) and, with a cache, 16 V chunks per
+            // Work units: CH / 2 K chunk pairs per row (rotate, store) and, with a cache, CH V chunks per
             // row (copy).  A thread takes two K units and four V units per trip and issues all their
             // loads before it uses the first, so the append costs one memory round trip per trip
             // (32 query rows: one trip) instead of one per unit.
@@ -466,7 +479,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 const int slot = row & ((1 << a.cache.block_shift) - 1);
                 return paged_base + ((((int64_t)b * a.n_kv + it.kv_head) << a.cache.block_shift) + slot) * D;
             };
-            const int n_k = n_tail * 8, n_v = SRC == SRC_PACKETS ? 0 : n_tail * 16;
+            const int n_k = n_tail * (CH / 2), n_v = SRC == SRC_PACKETS ? 0 : n_tail * CH;
             // (loads are unconditional, from units clamped into range; only the stores are guarded)
             for (int s0 = 0; 2 * s0 * NT < n_k || 4 * s0 * NT < n_v; ++s0) {
                 if (4 * s0 * NT + tid >= n_v && 2 * s0 * NT + tid >= n_k) continue;  // (a thread without a unit: few query rows)
@@ -475,7 +488,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 auto v_load = [&](int j, uint4 &vv, int64_t &vd) -> bool {
                     const int idx = (4 * s0 + j) * NT + tid;
                     const int ic = idx < n_v ? idx : (n_v > 0 ? n_v - 1 : 0);
-                    const int qr = tail_lo + ic / 16, e = 8 * (ic % 16);
+                    const int qr = tail_lo + ic / CH, e = 8 * (ic % CH);
                     const int64_t src = ((int64_t)(it.q_off + qr) * a.n_kv + it.kv_head) * D;
                     vd = unit_dst(qr, src) + e;
                     vv = n_v > 0 ? *(const uint4 *)((const bf16_t *)a.v_new + src + e) : make_uint4(0, 0, 0, 0);
@@ -487,13 +500,13 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                     KUnit u;
                     const int idx = (2 * s0 + j) * NT + tid;
                     const int ic = idx < n_k ? idx : n_k - 1;
-                    const int qr = tail_lo + ic / 8, e = 8 * (ic % 8);
+                    const int qr = tail_lo + ic / (CH / 2), e = 8 * (ic % (CH / 2));
                     const int pos = it.pos0 + qr;     // the token's position
                     const int64_t src = ((int64_t)(it.q_off + qr) * a.n_kv + it.kv_head) * D;
                     u.dst = unit_dst(qr, src) + e;
                     u.ulo = *(const uint4 *)((const bf16_t *)a.k_new + src + e);
-                    u.uhi = *(const uint4 *)((const bf16_t *)a.k_new + src + 64 + e);
-                    const float4 *csr = (const float4 *)(a.cs + (int64_t)pos * 64 + e);
+                    u.uhi = *(const uint4 *)((const bf16_t *)a.k_new + src + D / 2 + e);
+                    const float4 *csr = (const float4 *)(a.cs + (int64_t)pos * (D / 2) + e);
                     u.c0 = csr[0]; u.c1 = csr[1]; u.c2 = csr[2]; u.c3 = csr[3];
                     u.on = idx < n_k;
                     return u;
@@ -510,7 +523,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                     uint4 olo, ohi;
                     rotate_chunk_pair<true>(u.ulo, u.uhi, cs4, 1.f, 1.f, olo, ohi);
                     *(uint4 *)(kcw + u.dst) = olo;
-                    *(uint4 *)(kcw + u.dst + 64) = ohi;
+                    *(uint4 *)(kcw + u.dst + D / 2) = ohi;
                 };
                 k_store(k0);
                 k_store(k1);
@@ -529,20 +542,21 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     for (int s = 0; s < KS * PR; ++s)
         if (s < n_tiles && !(s == 0 && early0)) issue(s);
 
-    q_finish(cur_delta, n_tiles < KS * PR ? n_tiles : KS * PR);
+    if (OWN_WAIT) q_finish(cur_delta, n_tiles < KS * PR ? n_tiles : KS * PR);
+    else reload_q(cur_delta);
     KVP_STAMP(2);
 
-    floatx16 oacc[4];
+    floatx16 oacc[EB];
 #pragma unroll
-    for (int eb = 0; eb < 4; ++eb)
+    for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[eb][r] = 0.f;
     float m_ref = -INFINITY, l_i = 0.f;  // reference max (log2 units) and running sum
     // -m_ref in all 16 slots (every accumulator of a lane belongs to the same query row): the
     // first S MFMA of a tile takes it as its C operand, so S - m_ref costs no extra instruction.
     // Rewritten only when the reference moves; pinned so that it is not rebuilt per tile.
-    // (The in-place packet variant has no registers to spare and rebuilds it per tile.)
-    constexpr bool KEEP_CINIT = SRC != SRC_PACKETS;
+    // (The in-place packet variant and 256 columns have no registers to spare and rebuild it per tile.)
+    constexpr bool KEEP_CINIT = SRC != SRC_PACKETS && D <= 128;
     floatx16 cinit;
 #pragma unroll
     for (int r = 0; r < 16; ++r) cinit[r] = 0.f;
@@ -614,15 +628,15 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         // pair: the matrix pipe is busy for 64 cycles per pair, about what a part takes to issue.
         {
             constexpr int AHEAD = 2;  // (2, 3, 4, 6 and 8 k-steps measured: 2 is the fastest by a little, and holds the fewest registers)
-            constexpr int N_PARTS = KS * NI;                   // <= 4
-            static_assert(N_PARTS <= 8, "one part per k-step");
+            constexpr int N_PARTS = KS * NI;
+            static_assert(N_PARTS <= NKS, "one part per k-step");
             TileSrc rsrc[KS];
 #pragma unroll
             for (int k2 = 0; k2 < KS; ++k2)
                 if (KS * (rd + PR) + k2 < n_tiles) rsrc[k2] = tile_src(KS * (rd + PR) + k2);
             uint4 kf[2 * AHEAD];
             auto read_k = [&](int kstep) {
-                const int coff = 16 * ((2 * kstep + h) ^ (n & 15));
+                const int coff = 16 * ((2 * kstep + h) ^ k_swz(n));
                 kf[2 * (kstep % AHEAD)] = *(const uint4 *)(kl + n * ROW_BYTES + coff);
                 kf[2 * (kstep % AHEAD) + 1] = *(const uint4 *)(kl + (32 + n) * ROW_BYTES + coff);
             };
@@ -630,12 +644,12 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             for (int i = 0; i < AHEAD; ++i) read_k(i);
             __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the matrix code
 #pragma unroll
-            for (int kstep = 0; kstep < 8; ++kstep) {
+            for (int kstep = 0; kstep < NKS; ++kstep) {
                 const bool head = kstep == 0;  // compile-time: the tile's first k-step
                 const int sl = 2 * (kstep % AHEAD);
                 sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[sl]), qf[kstep], head ? cinit : sacc[0], 0, 0, 0);
                 sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[sl + 1]), qf[kstep], head ? cinit : sacc[1], 0, 0, 0);
-                if (kstep + AHEAD < 8) read_k(kstep + AHEAD);
+                if (kstep + AHEAD < NKS) read_k(kstep + AHEAD);
                 if (kstep < N_PARTS) {
                     const int k2 = kstep / NI, tj = KS * (rd + PR) + k2;
                     if (tj < n_tiles) issue_part(rsrc[k2], tj, kstep % NI);
@@ -685,7 +699,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) sacc[kb][r] -= delta;
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb)
+            for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) oacc[eb][r] *= alpha;
             if (KEEP_CINIT) {
@@ -705,12 +719,12 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         float rs0 = 0.f, rs1 = 0.f;
         const bf16x2 bf16_ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
         typedef __attribute__((address_space(3))) short4v *lds_s4;
-        short4v vfr[2][8];  // V fragments of one k-step: [buffer][2 eb + lo/hi]
+        short4v vfr[2][2 * EB];  // V fragments of one k-step: [buffer][2 eb + lo/hi]
         auto read_v = [&](int step, int buf) {  // step = 2 kb + j
             const char *vp = vl + (16 * step + 4 * h + tr_row) * ROW_BYTES + tr_half;
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb) {
-                const int coff = 16 * (4 * (eb ^ tr_row) + tr_x);
+            for (int eb = 0; eb < EB; ++eb) {
+                const int coff = 16 * (4 * (eb ^ v_swz(tr_row)) + tr_x);
                 vfr[buf][2 * eb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(vp + coff));
                 vfr[buf][2 * eb + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(vp + 8 * ROW_BYTES + coff));
             }
@@ -736,7 +750,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 uint4 pu = make_uint4(pk[4 * j], pk[4 * j + 1], pk[4 * j + 2], pk[4 * j + 3]);
                 bf16x8 pf = __builtin_bit_cast(bf16x8, pu);
 #pragma unroll
-                for (int eb = 0; eb < 4; ++eb) {
+                for (int eb = 0; eb < EB; ++eb) {
                     union { short4v s[2]; bf16x8 v; } vf;
                     vf.s[0] = vfr[step & 1][2 * eb];
                     vf.s[1] = vfr[step & 1][2 * eb + 1];
@@ -752,6 +766,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     KVP_STAMP(30);
 
     if (KS == 2) {
+        static_assert(KS == 1 || D == 128, "the two-group shape's LDS layout");
         // ---- merge the two groups' (m, l, O) of each row through LDS (the tile stages are free
         // once every wave has left the loop): group 1 writes, group 0 folds it in and goes on.
         wg_barrier();
@@ -759,7 +774,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         float *xm = xo + 16 * RW * 64 * 4;             // [RW][64] m, then [RW][64] l
         if (grp == 1) {
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb)
+            for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4)
                     *(float4 *)(xo + (((4 * eb + q4) * RW + wave_r) * 64 + lane) * 4) =
@@ -776,7 +791,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         m_ref = mm;
         l_i = l_i * a0 + l1 * a1;
 #pragma unroll
-        for (int eb = 0; eb < 4; ++eb)
+        for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const float4 o1 = *(const float4 *)(xo + (((4 * eb + q4) * RW + wave_r) * 64 + lane) * 4);
@@ -793,7 +808,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             bf16_t *op = (bf16_t *)a.out + ((int64_t)(it.q_off + t) * a.n_q_heads + hq) * D;
             const float inv = 1.f / l_i;
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb)
+            for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
                     uint2 u;
@@ -813,7 +828,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         char *pp = (char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 1);
         float amax = 0.f;
 #pragma unroll
-        for (int eb = 0; eb < 4; ++eb)
+        for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) amax = fmaxf(amax, __builtin_fabsf(oacc[eb][r]));
         amax = xhalf_max(amax);
@@ -828,22 +843,22 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                               __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, halfx2)));
         };
         // The rows go through LDS so that they leave as whole 256-byte rows (four per store
-        // instruction) instead of 16-byte pieces: each wave parks its 32 x 128 halves in 8 KiB of its
-        // own in the (now idle) tile stages, 8-byte chunk c of row n at chunk c ^ n, and reads them
-        // back row by row.  (KS = 2: the merge above has used the first 66 KiB; the rows go behind.)
+        // instruction) instead of 16-byte pieces: each wave parks its 32 x D halves in a region of its
+        // own in the (now idle) tile stages, 8-byte chunk c of row n at chunk c ^ n (n mod the chunks of
+        // a row), and reads them back row by row.  (KS = 2: the merge above has used the first 66 KiB; the rows go behind.)
         if (KS == 1) wg_barrier();  // every wave is done with the tiles
         char *reg = lds + (KS == 2 ? 68 * 1024 : 0) + wave_r * (32 * D * 2);
 #pragma unroll
-        for (int eb = 0; eb < 4; ++eb)
+        for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) *(uint2 *)(reg + n * (D * 2) + 8 * ((8 * eb + 2 * q4 + h) ^ n)) = pack4(eb, q4);
+            for (int q4 = 0; q4 < 4; ++q4) *(uint2 *)(reg + n * (D * 2) + 8 * ((8 * eb + 2 * q4 + h) ^ (n & (2 * CH - 1)))) = pack4(eb, q4);
         // (a wave reads only what it wrote itself: no barrier, the compiler orders the two)
-        const int c = lane & 15;
+        const int c = lane % CH;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int r = 4 * j + (lane >> 4);
+        for (int j = 0; j < 32 / RPI; ++j) {
+            const int r = RPI * j + lane / CH;
             // logical 8-byte chunks 2c and 2c + 1 of row r sit in the 16-byte unit c ^ (r >> 1), swapped when r is odd
-            uint4 f = *(const uint4 *)(reg + r * (D * 2) + 16 * (c ^ (r >> 1)));
+            uint4 f = *(const uint4 *)(reg + r * (D * 2) + 16 * (c ^ ((r >> 1) & (CH - 1))));
             if (r & 1) f = make_uint4(f.z, f.w, f.x, f.y);
             if (32 * wave_r + r < it.n_rows) *(uint4 *)(pp + (int64_t)(32 * wave_r + r) * (D * 2) + 16 * c) = f;
         }
@@ -856,10 +871,11 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     KVP_STAMP(31);
 }
 
-template <int STAGES, int SRC, int NW, int KS, bool NTL>
-__global__ __launch_bounds__(64 * NW, 2) void attention_mfma_kernel(AttnArgs a)
+// (256 columns: twice the accumulators and query registers, one wave per SIMD)
+template <int D, int STAGES, int SRC, int NW, int KS, bool NTL>
+__global__ __launch_bounds__(64 * NW, D == 256 ? 1 : 2) void attention_mfma_kernel(AttnArgs a)
 {
-    attention_body<STAGES, SRC, NW, KS, NTL>(a);
+    attention_body<D, STAGES, SRC, NW, KS, NTL>(a);
 }
 
 // 8 waves, 4 stages, the row block chosen item by item: 256 packed rows, or (AttnItem::half_block)
@@ -870,8 +886,8 @@ template <int SRC>
 __global__ __launch_bounds__(512, 2) void attention_mfma_mixed_kernel(AttnArgs a)
 {
     const bool half = a.inl.n ? false : a.items[blockIdx.x].half_block != 0;  // (regular launches have no half blocks)
-    if (half) attention_body<4, SRC, 8, 2, false>(a);
-    else attention_body<4, SRC, 8, 1, false>(a);
+    if (half) attention_body<128, 4, SRC, 8, 2, false>(a);
+    else attention_body<128, 4, SRC, 8, 1, false>(a);
 }
 
 template <typename K> static int launch_kernel(K kernel, bool &attr_set, int lds_bytes, int threads, const AttnArgs &a, void *stream)
@@ -885,11 +901,11 @@ template <typename K> static int launch_kernel(K kernel, bool &attr_set, int lds
     return (int)hipGetLastError();
 }
 
-template <int SRC, int NW, int KS, int STAGES, bool NTL> static int launch_variant_nt(const AttnArgs &a, void *stream)
+template <int D, int SRC, int NW, int KS, int STAGES, bool NTL> static int launch_variant_nt(const AttnArgs &a, void *stream)
 {
-    constexpr int lds_bytes = STAGES * STAGE_BYTES + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
+    constexpr int lds_bytes = STAGES * stage_bytes(D) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
     static bool attr_set = false;
-    return launch_kernel(attention_mfma_kernel<STAGES, SRC, NW, KS, NTL>, attr_set, lds_bytes, 64 * NW, a, stream);
+    return launch_kernel(attention_mfma_kernel<D, STAGES, SRC, NW, KS, NTL>, attr_set, lds_bytes, 64 * NW, a, stream);
 }
 
 // The streaming hint on the tile loads (a.nt_loads) exists for the 8-wave shapes, which stream
@@ -897,13 +913,13 @@ template <int SRC, int NW, int KS, int STAGES, bool NTL> static int launch_varia
 // share their rows).
 template <int SRC, int NW, int KS, int STAGES> static int launch_variant(const AttnArgs &a, void *stream)
 {
-    if (NW == 8 && a.nt_loads) return launch_variant_nt<SRC, NW, KS, STAGES, NW == 8>(a, stream);
-    return launch_variant_nt<SRC, NW, KS, STAGES, false>(a, stream);
+    if (NW == 8 && a.nt_loads) return launch_variant_nt<128, SRC, NW, KS, STAGES, NW == 8>(a, stream);
+    return launch_variant_nt<128, SRC, NW, KS, STAGES, false>(a, stream);
 }
 
 template <int SRC> static int launch_mixed(const AttnArgs &a, void *stream)
 {
-    constexpr int lds_bytes = 4 * STAGE_BYTES + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
+    constexpr int lds_bytes = 4 * stage_bytes(128) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
     static bool attr_set = false;
     return launch_kernel(attention_mfma_mixed_kernel<SRC>, attr_set, lds_bytes, 512, a, stream);
 }
@@ -915,13 +931,26 @@ template <int NW, int KS, int STAGES> static int launch_nw(const AttnArgs &a, vo
                                : launch_variant<SRC_CONTIG, NW, KS, STAGES>(a, stream);
 }
 
-// a.bm selects the row block: 256 packed rows (8 waves; a.mixed: with half blocks among them,
+// Head dims 64 and 256: 128-row blocks of 4 waves.  A tile of 64 columns is half as large, so four
+// stages fit where two of 128 columns do; of 256 columns two stages fill the CU's LDS.  (The generic
+// kernel served these dims before: four requests of 2K-row paged contexts, 64 columns, 16-64 query
+// rows took 3800 us per layer there -- a lane reduction and a block-table walk per score -- and take 16 here.)
+template <int D, int STAGES> static int launch_other_dim(const AttnArgs &a, void *stream)
+{
+    if (a.bm != 128 || a.tiles) return (int)hipErrorInvalidValue;
+    return a.cache.layout != 0 ? launch_variant_nt<D, SRC_PAGED, 4, 1, STAGES, false>(a, stream)
+                               : launch_variant_nt<D, SRC_CONTIG, 4, 1, STAGES, false>(a, stream);
+}
+
+// a.bm selects the row block (128 columns): 256 packed rows (8 waves; a.mixed: with half blocks among them,
 // see above) or 128.  128-row blocks run as 4 waves
 // with two tile stages (two workgroups per CU), or -- a.split_in_wg, chosen when the launch
 // has at most one item per CU -- as 8 waves in two groups that take alternate tiles.
 int launch_attention_mfma(const AttnArgs &a, void *stream)
 {
-    if (a.d != D || (a.bm != 128 && a.bm != 256)) return (int)hipErrorInvalidValue;
+    if (a.d == 64) return launch_other_dim<64, 4>(a, stream);
+    if (a.d == 256) return launch_other_dim<256, 2>(a, stream);
+    if (a.d != 128 || (a.bm != 128 && a.bm != 256)) return (int)hipErrorInvalidValue;
     if (a.bm == 256 && a.mixed) {
         if (a.tiles) return launch_mixed<SRC_PACKETS>(a, stream);
         return a.cache.layout != 0 ? launch_mixed<SRC_PAGED>(a, stream) : launch_mixed<SRC_CONTIG>(a, stream);

@@ -198,7 +198,7 @@ int launch_append(int dtype, const AppendArgs &a, void *stream);
 int launch_attention(int dtype, const AttnArgs &a, int kernel_kind, void *stream);
 int launch_combine(int dtype, const AttnArgs &a, void *stream);
 
-// GENERIC: any shape, fp32 vector arithmetic.  MFMA: bf16, head_dim 128.  F32: fp32, head_dim 64, 128, 256.
+// GENERIC: any shape, fp32 vector arithmetic.  MFMA: bf16, F32: fp32, both for head_dim 64, 128, 256.
 enum { ATTN_GENERIC = 0, ATTN_MFMA = 1, ATTN_F32 = 2 };
 constexpr int ATTN_F32_BM = 32;  // packed rows of a work item of the fp32 kernel
 

@@ -1190,8 +1190,8 @@ int attn_kind(const kvp_store *s, const kvp_cache_t *c)
 {
     const kvp_config_t &g = s->cfg;
     if (s->force_generic || (c && c->layout == KVP_PAGED && c->block_size < MFMA_MIN_BLOCK_SIZE)) return ATTN_GENERIC;
-    if (g.dtype == KVP_BF16) return g.head_dim == 128 ? ATTN_MFMA : ATTN_GENERIC;
-    return g.head_dim == 64 || g.head_dim == 128 || g.head_dim == 256 ? ATTN_F32 : ATTN_GENERIC;
+    if (g.head_dim != 64 && g.head_dim != 128 && g.head_dim != 256) return ATTN_GENERIC;
+    return g.dtype == KVP_BF16 ? ATTN_MFMA : ATTN_F32;
 }
 
 // Packed rows per row block (the MFMA kernel's smaller one).
@@ -1210,14 +1210,15 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int n_req, const
                               : INT32_MAX;
     p.kind = kind;
     p.bm = base_bm(kind);
-    if (mfma) {  // row blocks of 256 when some request has that many packed rows
+    if (mfma && g.head_dim == 128) {  // row blocks of 256 when some request has that many packed rows
         for (int r = 0; r < n_req; ++r)
             if ((int64_t)(q_off[r + 1] - q_off[r]) * gq >= 2 * MFMA_BM) p.bm = 2 * MFMA_BM;
         if (s->force_bm == 128 || s->force_bm == 256) p.bm = s->force_bm;
     }
     // The fp32 kernel deals a range's 32-row tiles to four waves: ranges of whole rounds of four, and
     // no shorter than a tile takes longer than a combine launch (a tile: 2 us and more).
-    const int min_split = kind == ATTN_GENERIC ? 64 : kind == ATTN_F32 && s->target_items > 0 ? 64 : 256;
+    const bool fine = s->target_items > 0 && (kind == ATTN_F32 || g.head_dim != 128);  // (the test knob: as finely as the kernel can)
+    const int min_split = kind == ATTN_GENERIC || fine ? 64 : 256;
     if (kind == ATTN_F32 && s->target_items == 0) p.bn = 128;
     p.reqs.resize(n_req);
     int64_t n_groups = 0;
@@ -1232,10 +1233,10 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int n_req, const
     for (int r = 0; r < n_req; ++r)
         tiles += (int64_t)g.n_kv_heads * (((int64_t)p.reqs[r].n_q * gq + p.bm - 1) / p.bm) * ((p.reqs[r].ctx_len + p.reqs[r].n_q + 63) / 64);
     // (the fp32 kernel is bound by the matrix pipe from the first tile on: an item for every CU)
-    const int target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s, tiles, mfma ? p.bm : 0);
+    const int target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s, tiles, mfma && g.head_dim == 128 ? p.bm : 0);
     int want = (int)std::min<int64_t>(MAX_SPLITS, (target + n_groups - 1) / n_groups);
     if (want < 1) want = 1;
-    p.split_in_wg = mfma && streams_many_tiles(s, tiles, p.bm);
+    p.split_in_wg = mfma && g.head_dim == 128 && streams_many_tiles(s, tiles, p.bm);
     for (int r = 0; r < n_req; ++r) {
         const ReqMeta &rq = p.reqs[r];
         if (rq.n_q == 0) continue;
@@ -1490,7 +1491,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         }
         {
             kvp_store::DebugPlan &dp = s->dbg_plan;
-            const int64_t head[6] = {p.kind == ATTN_MFMA ? 1 : 0, p.bm, (int64_t)p.groups.size(), (int64_t)p.items.size(), p.n_slots, (int64_t)need};
+            const int64_t head[6] = {p.kind == ATTN_MFMA && g.head_dim == 128 ? 1 : 0, p.bm, (int64_t)p.groups.size(), (int64_t)p.items.size(), p.n_slots, (int64_t)need};
             memcpy(dp.head, head, sizeof head);
             dp.groups.swap(p.groups);  // (already copied into the plan buffer above)
             dp.items.swap(p.items);

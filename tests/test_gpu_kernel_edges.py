@@ -28,3 +28,15 @@ def test_fp32_matrix_kernel(gpu_device, monkeypatch, d, g, ctx, n_q, paged, targ
         monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)  # ranges of 64 rows: waves without a tile, many partial rows
     w = _request("f32", d, g, ctx, n_q, paged=paged)
     compare(w, run_workload(w), oracle_workload(w))
+
+
+@pytest.mark.parametrize("d,g,ctx,n_q,paged,target", [
+    (64, 1, 0, 1, False, None), (64, 4, 1, 33, True, None), (64, 7, 63, 5, False, None), (64, 4, 64, 32, True, None),
+    (64, 4, 255, 65, False, None), (64, 7, 1300, 19, True, "4000"), (64, 2, 2000, 64, False, None), (256, 1, 0, 1, True, None),
+    (256, 4, 63, 32, False, None), (256, 2, 65, 70, True, None), (256, 7, 900, 20, False, "4000"), (256, 4, 1500, 9, True, None),
+])
+def test_bf16_head_dims_64_and_256(gpu_device, monkeypatch, d, g, ctx, n_q, paged, target):
+    if target:
+        monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
+    w = _request("bf16", d, g, ctx, n_q, paged=paged, n_req=2)
+    compare(w, run_workload(w), oracle_workload(w))
