@@ -24,10 +24,12 @@
 // The query side of the layer is part of it: every workgroup rotates its own query rows, and those
 // whose range reaches the query rows append K_new / V_new first.  (Several may: same bytes.)
 //
-// Measured (2.9K rows of context, 32 query rows, 32 / 8 heads of 128 columns): 25 us per layer, of which
+// Measured (2.9K rows of context, 32 query rows, 32 / 8 heads of 128 columns): 27 us per layer, of which
 // the three tiles of a wave are 12; one wave per row with fp32 vector arithmetic and a lane
-// reduction per score took 1062.
+// reduction per score took 1062.  Error against float64 there: 2.0e-7 of the result, 7.0e-7 before.
 #include "kvp_device.h"
+
+#include <type_traits>
 
 namespace kvp {
 
@@ -166,25 +168,36 @@ __global__ __launch_bounds__(64 * F32_WAVES, 1) void attention_f32_kernel(AttnAr
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[eb][r] = 0.f;
     float m_i = -INFINITY, l_i = 0.f;
+    constexpr bool ALL_FINITE = D == 256;  // every tile that way (two copies of the loop body do not fit the registers)
+    bool dropped = false;  // infinities or NaNs of V were left out
     for (int ti = wave; ti < n_tiles; ti += F32_WAVES) {
 #pragma unroll
         for (int r = 0; r < VA; ++r) load_v(ti, r);  // arrive under the S MFMAs
         const float *kp = k_row(ti);
         const float *kn = k_row(ti + F32_WAVES < n_tiles ? ti + F32_WAVES : ti);  // (the last tile loads itself again, from the L2)
         __builtin_amdgcn_sched_barrier(0);
-        f32x16 s;
+        // (four partial sums over the columns, two at 256: a chain of 64 additions each would round
+        // further from the exact score than the generic kernel's tree of lanes)
+        constexpr int NS = D == 256 ? 2 : 4;
+        f32x16 sp[NS];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        for (int c = 0; c < NS; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sp[c][r] = 0.f;
 #pragma unroll
         for (int j = 0; j < NK; ++j) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(kr[j % KA], i), comp(qr[j], i), s, 0, 0, 0);
+            for (int i = 0; i < 4; ++i) sp[i % NS] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(kr[j % KA], i), comp(qr[j], i), sp[i % NS], 0, 0, 0);
             kr[j % KA] = *(const float4 *)(j + KA < NK ? kp + 8 * (j + KA) : kn + 8 * (j + KA - NK));
             __builtin_amdgcn_sched_barrier(0);
         }
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = NS == 4 ? (sp[0][r] + sp[1][r]) + (sp[2 % NS][r] + sp[3 % NS][r]) : sp[0][r] + sp[1][r];
 
         const int kv0 = it.kv_begin + ti * F32_TILE;
-        if (kv0 + F32_TILE > wave_limit || kv0 + F32_TILE > it.kv_end) {  // wave-uniform: last tiles only
+        const bool masked = kv0 + F32_TILE > wave_limit || kv0 + F32_TILE > it.kv_end;  // wave-uniform: last tiles only
+        if (masked) {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 if (kv0 + 8 * (r >> 2) + 4 * h + (r & 3) >= limit) s[r] = -INFINITY;
@@ -210,15 +223,36 @@ __global__ __launch_bounds__(64 * F32_WAVES, 1) void attention_f32_kernel(AttnAr
             sum += p[r];
         }
         l_i += sum;
+        // A masked tile's zero probabilities times an infinity or NaN of V would be NaN: there such elements
+        // stay out of the matrix product (as zeros) and are added at the end to the rows that see them.
+        uint32_t bad = 0;
+        auto pv = [&](auto drop) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < 16; ++r) {
+                if (decltype(drop)::value) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int eb = 0; eb < EB; ++eb)
-                oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(vr[r % VA][eb / VW], eb % VW), p[r], oacc[eb], 0, 0, 0);
-            if (VA < 16 && r + VA < 16) {
-                load_v(ti, r + VA);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int eb = 0; eb < EB; ++eb) {
+                    float v = comp(vr[r % VA][eb / VW], eb % VW);
+                    if (decltype(drop)::value) {
+                        // all ones if the exponent is: in integer arithmetic, a compare mask per element is a scalar pair
+                        uint32_t nf = 0u - ((__builtin_amdgcn_ubfe(__float_as_uint(v), 23, 8) + 1u) >> 8);
+                        asm("" : "+v"(nf));
+                        bad |= nf;
+                        v = __uint_as_float(__float_as_uint(v) & ~nf);
+                    }
+                    oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, p[r], oacc[eb], 0, 0, 0);
+                }
+                if (VA < 16 && r + VA < 16) {
+                    load_v(ti, r + VA);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
+        };
+        if (ALL_FINITE || masked) {
+            pv(std::true_type{});
+            dropped |= __any(bad != 0);
+        } else {
+            pv(std::false_type{});
         }
     }
     l_i += __shfl_xor(l_i, 32, 64);  // the lane halves saw different kv rows
@@ -238,7 +272,9 @@ __global__ __launch_bounds__(64 * F32_WAVES, 1) void attention_f32_kernel(AttnAr
         xm[wave * 32 + n] = m_i;
         xl[wave * 32 + n] = l_i;
     }
-    __syncthreads();
+    dropped = __syncthreads_or(dropped);
+    const int seen_end = wave_limit < it.kv_end ? wave_limit : it.kv_end;  // the masked tiles start with the tile this row is in
+    const int masked0 = it.kv_begin + (!ALL_FINITE && seen_end > it.kv_begin ? (seen_end - it.kv_begin) / F32_TILE * F32_TILE : 0);
     for (int u = tid; u < it.n_rows * (D / 4); u += 64 * F32_WAVES) {
         const int rr = u / (D / 4), e = 4 * (u % (D / 4));
         float mm = -INFINITY, l = 0.f;
@@ -251,7 +287,18 @@ __global__ __launch_bounds__(64 * F32_WAVES, 1) void attention_f32_kernel(AttnAr
             const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - mm);
             const float4 o = *(const float4 *)(f32_lds + (w * 32 + rr) * LS + e);
             l += xl[w * 32 + rr] * wt;
-            acc.x += o.x * wt; acc.y += o.y * wt; acc.z += o.z * wt; acc.w += o.w * wt;
+            if (wt != 0.f) { acc.x += o.x * wt; acc.y += o.y * wt; acc.z += o.z * wt; acc.w += o.w * wt; }
+        }
+        if (dropped) {
+            const int end = it.ctx_len + (it.m0 + rr) / a.g + 1 < it.kv_end ? it.ctx_len + (it.m0 + rr) / a.g + 1 : it.kv_end;
+#pragma unroll 1
+            for (int kv = masked0; kv < end; ++kv) {
+                const float4 x = *(const float4 *)((const float *)a.cache.v + row_off(kv) + e);
+                acc.x += __builtin_fabsf(x.x) < INFINITY ? 0.f : x.x;
+                acc.y += __builtin_fabsf(x.y) < INFINITY ? 0.f : x.y;
+                acc.z += __builtin_fabsf(x.z) < INFINITY ? 0.f : x.z;
+                acc.w += __builtin_fabsf(x.w) < INFINITY ? 0.f : x.w;
+            }
         }
         if (it.part_slot < 0) {
             const int mr = it.m0 + rr;

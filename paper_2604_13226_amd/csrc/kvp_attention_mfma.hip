@@ -31,6 +31,8 @@
 // HBM traffic: every K/V row of the range is read once per group of 128 packed rows.
 #include "kvp_device.h"
 
+#include <type_traits>
+
 namespace kvp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -132,6 +134,20 @@ __device__ __forceinline__ void load_to_lds_16(const void *gptr, uint32_t lds_ad
 // harmless in fp32 accumulators and scale-free in bf16); the final (m, l, O) stay consistent
 // because all three are relative to the same reference.
 constexpr float RESCALE_SLACK = 8.f;
+
+// v with zeros in place of its infinities and NaNs; `dropped` becomes non-zero if there are any
+__device__ __forceinline__ bf16x8 drop_nonfinite(const bf16x8 &v, uint32_t &dropped)
+{
+    const uint4 u = __builtin_bit_cast(uint4, v);
+    uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t bad = ((w[i] & 0x7F80u) == 0x7F80u ? 0xFFFFu : 0u) | ((w[i] & 0x7F800000u) == 0x7F800000u ? 0xFFFF0000u : 0u);
+        dropped |= bad;
+        w[i] &= ~bad;
+    }
+    return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+}
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
@@ -240,6 +256,9 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     constexpr int NI = BN / RPI / NW;  // K (and V) load instructions per wave per tile
     constexpr int PR = STAGES / KS - 1;  // rounds (of KS tiles) loaded ahead
     static_assert(STAGES % KS == 0 && PR >= 1, "stages");
+    // Head dims other than 128: a probability goes into the product as two bf16 numbers, its leading eight
+    // bits and the rest (16 bits together); the row sum and the partial rows are fp32.
+    constexpr bool SPLIT_P = D != 128;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     KVP_STAMP(0);
     const AttnItem it = a.inl.n ? attn_inline_item(a.inl, blockIdx.x, a.n_kv, a.part_stride) : a.items[blockIdx.x];
@@ -567,6 +586,11 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     const int tr_half = 8 * (lane & 1);
 
 
+    // Head dims other than 128, tiles with rows that some of the wave do not see: a zero probability times
+    // an infinity or NaN of V would be NaN, so there such elements stay out of the matrix product (as
+    // zeros) and are added at the end to the rows that see them.
+    uint32_t dropped = 0;
+
     const int n_rounds = (n_tiles + KS - 1) / KS;
     KVP_PHASE_DECL;
     for (int rd = 0; rd < n_rounds; ++rd) {
@@ -659,6 +683,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         }
         KVP_PHASE(2);
 
+        bool masked = false;  // some of the tile's rows are invisible to some of the wave's rows (cache modes)
         // ---- online softmax; accumulator r of block kb is tile row 32 kb + 8 (r/4) + 4 h + r%4
         if (SRC == SRC_PACKETS) {
             if (td.kind != 0 || td.n_rows < BN) {  // wave-uniform: query tiles and ragged packet ends
@@ -671,6 +696,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                         if (32 * kb + 8 * (r >> 2) + 4 * h + (r & 3) >= lim) sacc[kb][r] = -INFINITY;
             }
         } else if (kv0 + BN > wave_limit || kv0 + BN > it.kv_end) {  // wave-uniform: tail tiles only
+            masked = true;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -729,35 +755,54 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 vfr[buf][2 * eb + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(vp + 8 * ROW_BYTES + coff));
             }
         };
-        read_v(0, 0);
+        auto pv = [&](auto finite_v) {
+            constexpr bool FINITE_V = decltype(finite_v)::value;
+            read_v(0, 0);
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            uint32_t pk[8];
+            for (int kb = 0; kb < 2; ++kb) {
+                uint32_t pk[8], pl[8];
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                float p0 = __builtin_amdgcn_exp2f(sacc[kb][r]);
-                float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1]);
-                pk[r >> 1] = pack_bf16_hw(p0, p1);
-                // the row sum takes the rounded values, i.e. exactly what multiplies V
-                const bf16x2 pp = __builtin_bit_cast(bf16x2, pk[r >> 1]);
-                if (r & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs1, false);
-                else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs0, false);
-            }
+                for (int r = 0; r < 16; r += 2) {
+                    float p0 = __builtin_amdgcn_exp2f(sacc[kb][r]);
+                    float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1]);
+                    if (SPLIT_P) {
+                        // cut, not rounded: the rest is positive (and kept so), and both parts times an infinity of V agree
+                        pk[r >> 1] = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302);
+                        const float q0 = p0 - __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u);
+                        const float q1 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
+                        pl[r >> 1] = pack_bf16_hw(fmaxf(q0, 0x1p-126f), fmaxf(q1, 0x1p-126f));
+                        rs0 += p0;
+                        rs1 += p1;
+                        continue;
+                    }
+                    pk[r >> 1] = pack_bf16_hw(p0, p1);
+                    // the row sum takes the rounded values, i.e. exactly what multiplies V
+                    const bf16x2 pp = __builtin_bit_cast(bf16x2, pk[r >> 1]);
+                    if (r & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs1, false);
+                    else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs0, false);
+                }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int step = 2 * kb + j;
-                if (step + 1 < 4) read_v(step + 1, (step + 1) & 1);  // next k-step's V lands under these MFMAs
-                uint4 pu = make_uint4(pk[4 * j], pk[4 * j + 1], pk[4 * j + 2], pk[4 * j + 3]);
-                bf16x8 pf = __builtin_bit_cast(bf16x8, pu);
+                for (int j = 0; j < 2; ++j) {
+                    const int step = 2 * kb + j;
+                    if (step + 1 < 4) read_v(step + 1, (step + 1) & 1);  // next k-step's V lands under these MFMAs
+                    uint4 pu = make_uint4(pk[4 * j], pk[4 * j + 1], pk[4 * j + 2], pk[4 * j + 3]);
+                    bf16x8 pf = __builtin_bit_cast(bf16x8, pu);
+                    bf16x8 pg = pf;
+                    if (SPLIT_P) pg = __builtin_bit_cast(bf16x8, make_uint4(pl[4 * j], pl[4 * j + 1], pl[4 * j + 2], pl[4 * j + 3]));
 #pragma unroll
-                for (int eb = 0; eb < EB; ++eb) {
-                    union { short4v s[2]; bf16x8 v; } vf;
-                    vf.s[0] = vfr[step & 1][2 * eb];
-                    vf.s[1] = vfr[step & 1][2 * eb + 1];
-                    oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, oacc[eb], 0, 0, 0);
+                    for (int eb = 0; eb < EB; ++eb) {
+                        union { short4v s[2]; bf16x8 v; } vf;
+                        vf.s[0] = vfr[step & 1][2 * eb];
+                        vf.s[1] = vfr[step & 1][2 * eb + 1];
+                        if (FINITE_V) vf.v = drop_nonfinite(vf.v, dropped);
+                        oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, oacc[eb], 0, 0, 0);
+                        if (SPLIT_P) oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pg, oacc[eb], 0, 0, 0);
+                    }
                 }
             }
-        }
+        };
+        if (SPLIT_P && masked) pv(std::true_type{});
+        else pv(std::false_type{});
         l_i += rs0 + rs1;  // this lane's half of the row; the halves are added once, at the end
         KVP_PHASE(4);
     }
@@ -802,6 +847,26 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             }
     }
 
+    if (SPLIT_P && __any(dropped != 0)) {
+        const int seen_end = wave_limit < it.kv_end ? wave_limit : it.kv_end;  // (the masked tiles start with the tile this row is in)
+        const int end = limit < it.kv_end ? limit : it.kv_end;
+#pragma unroll 1
+        for (int kv = it.kv_begin + (seen_end > it.kv_begin ? (seen_end - it.kv_begin) / BN * BN : 0); kv < end; ++kv) {
+            int64_t off = contig_off + (int64_t)(kv - it.kv_begin) * D;
+            if (SRC == SRC_PAGED) {
+                const int64_t b = blk_ids[(kv >> a.cache.block_shift) - blk0];
+                off = paged_base + (((b * a.n_kv + it.kv_head) << a.cache.block_shift) + (kv & ((1 << a.cache.block_shift) - 1))) * D;
+            }
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float x = ld_elem(vc + off + 32 * eb + 8 * (r >> 2) + 4 * h + (r & 3));
+                    oacc[eb][r] += __builtin_fabsf(x) < INFINITY ? 0.f : x;
+                }
+        }
+    }
+
     // ---- epilogue: lane holds O[m][32 eb + 8 (r/4) + 4 h + r%4]
     if (row_ok) {
         if (it.part_slot < 0) {
@@ -818,7 +883,21 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 }
         }
     }
-    if (it.part_slot >= 0) {
+    if (SPLIT_P) {
+        if (it.part_slot >= 0 && row_ok) {  // fp32 rows, then m and l of each row
+            float *pp = (float *)((char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 0));
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *(float4 *)(pp + (int64_t)rr * D + 32 * eb + 8 * q4 + 4 * h) =
+                        make_float4(oacc[eb][4 * q4], oacc[eb][4 * q4 + 1], oacc[eb][4 * q4 + 2], oacc[eb][4 * q4 + 3]);
+            if (h == 0) {
+                pp[(int64_t)a.bm * D + rr] = m_ref;
+                pp[(int64_t)a.bm * D + a.bm + rr] = l_i;
+            }
+        }
+    } else if (it.part_slot >= 0) {
         // A slot holds a.bm rows of D fp16 values (the launch's largest row block; BM <= a.bm), then
         // m and l of each row in fp32.  A row of the split's unnormalised O goes out as fp16 scaled
         // by a power of two 2^-e that brings its largest magnitude below 1; m + e and l 2^-e go with
@@ -934,7 +1013,8 @@ template <int NW, int KS, int STAGES> static int launch_nw(const AttnArgs &a, vo
 // Head dims 64 and 256: 128-row blocks of 4 waves.  A tile of 64 columns is half as large, so four
 // stages fit where two of 128 columns do; of 256 columns two stages fill the CU's LDS.  (The generic
 // kernel served these dims before: four requests of 2K-row paged contexts, 64 columns, 16-64 query
-// rows took 3800 us per layer there -- a lane reduction and a block-table walk per score -- and take 16 here.)
+// rows took 3800 us per layer there -- a lane reduction and a block-table walk per score -- and take 20 here,
+// 4 of them for what keeps its precision: the second bf16 part of P and fp32 partial rows.)
 template <int D, int STAGES> static int launch_other_dim(const AttnArgs &a, void *stream)
 {
     if (a.bm != 128 || a.tiles) return (int)hipErrorInvalidValue;

@@ -207,7 +207,7 @@ struct kvp_store {
         // between the kernels and a microsecond of host time); the entry remembers that work
         // newer than its event may still read the plan, and settles that when it is replaced.
         bool used_since_event = false;
-        uint64_t need = 0;
+        uint64_t need = 0, best_need = 0;  // workspace of this plan; of the kernel the shape prefers
     };
     uint64_t serial = 0;  // distinguishes this store from any other the process has had
     std::deque<PrefillCached> pf_set;  // kvp_query_prefill
@@ -1197,12 +1197,14 @@ int attn_kind(const kvp_store *s, const kvp_cache_t *c)
 // Packed rows per row block (the MFMA kernel's smaller one).
 int base_bm(int kind) { return kind == ATTN_MFMA ? MFMA_BM : kind == ATTN_F32 ? ATTN_F32_BM : GENERIC_BM; }
 
-void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
+// Partial rows in scaled fp16: the MFMA kernel at 128 columns (elsewhere they are fp32).
+int part_f16_of(int kind, int d) { return kind == ATTN_MFMA && d == 128 ? 1 : 0; }
+
+void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
                   PrefillPlan &p)
 {
     const kvp_config_t &g = s->cfg;
     const int gq = g.n_q_heads / g.n_kv_heads;
-    const int kind = attn_kind(s, cache);
     const bool mfma = kind == ATTN_MFMA;
     // paged + matrix-core kernel: an item's blocks must fit the kernel's LDS id table
     const int max_split = (kind != ATTN_GENERIC && cache->layout == KVP_PAGED)
@@ -1433,7 +1435,12 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         found = find_plan(s, s->pf_set, sig, hip_stream, sig_hash, hit);
     }
     kvp_store::PrefillCached &pf = *found;
-    const uint64_t qrb = attn_kind(s, cache) != ATTN_GENERIC ? 0 : q_rot_bytes(s, tot_q);  // (the matrix-core kernels rotate the query in registers)
+    // fp32 stores and head dims 64 and 256: the matrix kernels' fp32 partial rows come in blocks of 32 and
+    // 128 rows, the generic kernel's in blocks of 8, so a workspace may hold the one and not the other.
+    // Such a call takes the generic kernel, as it does wherever the matrix kernels cannot go.
+    const int best_kind = attn_kind(s, cache);
+    const bool may_fall_back = best_kind != ATTN_GENERIC && !part_f16_of(best_kind, g.head_dim);
+    if (hit && may_fall_back && !in_capture && !pf.captured && (pf.kind == best_kind ? workspace_bytes < pf.need : workspace_bytes >= pf.best_need)) hit = false;
     if (in_capture && !hit)
         return fail(s, KVP_E_INVAL, "kvp_query_prefill under stream capture needs the plan of an earlier call with the same "
                                     "geometry on the same stream (call it once before capturing)");
@@ -1442,9 +1449,17 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
 
     if (!hit) {
         PrefillPlan p;
-        plan_prefill(s, cache, n_req, rows.data(), cache->ctx_len, q_offsets, p);
-        // (the MFMA kernel's partial rows are fp16: half the bytes of the generic kernel's)
-        const uint64_t need = qrb + (uint64_t)p.n_slots * (uint64_t)part_slot_bytes(p.bm, g.head_dim, p.kind == ATTN_MFMA ? 1 : 0);
+        auto plan_need = [&]() -> uint64_t {  // (the matrix kernels rotate the query in registers)
+            return (p.kind == ATTN_GENERIC ? q_rot_bytes(s, tot_q) : 0) +
+                   (uint64_t)p.n_slots * (uint64_t)part_slot_bytes(p.bm, g.head_dim, part_f16_of(p.kind, g.head_dim));
+        };
+        plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+        const uint64_t best_need = plan_need();
+        if (may_fall_back && !s->dry && workspace_bytes < best_need) {
+            p = PrefillPlan();
+            plan_prefill(s, cache, ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+        }
+        const uint64_t need = plan_need();
         const uint64_t bytes = p.reqs.size() * sizeof(ReqMeta) + p.row_req.size() * 4 + p.groups.size() * sizeof(AttnGroup) +
                                p.items.size() * sizeof(AttnItem) + (uint64_t)n_req * bt_stride * 4 + 6 * 64;
         // every check comes before the entry is touched: a call that fails has changed nothing
@@ -1513,6 +1528,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         pf.part_stride = p.part_stride;
         pf.max_group_rows = p.max_group_rows;
         pf.need = need;
+        pf.best_need = best_need;
         pf.sig = sig;
         pf.sig_hash = sig_hash;
         pf.stream = hip_stream;
@@ -1570,8 +1586,8 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     at.reqs = pf.reqs_dev;
     at.groups = pf.groups_dev;
     at.items = pf.items_dev;
-    at.partials = (float *)((char *)workspace + qrb);
-    at.part_f16 = pf.kind == ATTN_MFMA ? 1 : 0;
+    at.partials = (float *)((char *)workspace + (pf.kind == ATTN_GENERIC ? q_rot_bytes(s, tot_q) : 0));
+    at.part_f16 = part_f16_of(pf.kind, g.head_dim);
     at.out = out;
     at.n_items = pf.n_items;
     at.n_groups = pf.n_groups;

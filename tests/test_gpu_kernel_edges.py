@@ -1,9 +1,11 @@
 """GPU parity at the sizes where a kernel's tiling can go wrong: one row either side of a tile, a row
 block and a round of waves, the smallest call, ranges split as finely as they can be."""
+import numpy as np
 import pytest
+import torch
 
 import kvp_workloads as W
-from tests.gpu_harness import oracle_workload, run_workload
+from tests.gpu_harness import build_store, make_cache, oracle_workload, run_workload
 from tests.test_gpu_parity import compare
 
 pytestmark = pytest.mark.gpu
@@ -40,3 +42,63 @@ def test_bf16_head_dims_64_and_256(gpu_device, monkeypatch, d, g, ctx, n_q, page
         monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
     w = _request("bf16", d, g, ctx, n_q, paged=paged, n_req=2)
     compare(w, run_workload(w), oracle_workload(w))
+
+
+@pytest.mark.parametrize("dtype,d,g,ctx,n_q,paged,target", [
+    ("f32", 64, 2, 40, 20, False, None), ("f32", 128, 4, 100, 33, True, "4000"), ("f32", 256, 1, 30, 70, False, None),
+    ("bf16", 64, 4, 70, 40, True, None), ("bf16", 64, 7, 0, 65, False, "4000"), ("bf16", 256, 2, 100, 30, False, None),
+])
+def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypatch, dtype, d, g, ctx, n_q, paged, target):
+    import paper_2604_13226_amd as kvp
+    if target:
+        monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
+    w = _request(dtype, d, g, ctx, n_q, paged=paged)
+    store = build_store(w, kvp)
+    q_off = np.array([0, n_q], np.int32)
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, n_q, ctx + n_q))
+
+    def call(change):
+        cache = make_cache(w, kvp, store)
+        kvp.kvp_assemble(store, [(rq.packet_ids, 0) for rq in w.requests], cache)
+        q, kn, vn = w.query(0, 0, "cuda:0")
+        change(vn)
+        out = torch.empty_like(q)
+        kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, ws, out)
+        return out.float().cpu()
+
+    at, col = (2 * n_q) // 3, d // 2 + 3
+    clean = call(lambda vn: None)
+    for value in (float("inf"), float("nan")):
+        def change(vn):
+            vn[at, 0, col] = value
+        got = call(change)
+        assert torch.equal(got[:at], clean[:at])                     # rows before it: untouched
+        hit = torch.zeros(clean.shape, dtype=torch.bool)
+        hit[at:, :g, col] = True                                      # the query heads of KV head 0
+        assert torch.equal(got[~hit], clean[~hit])
+        assert bool((torch.isinf(got[hit]) if value == float("inf") else torch.isnan(got[hit])).all())
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 256)])
+def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkeypatch, dtype, d):
+    """The matrix kernels' partial rows come in larger blocks: a call whose workspace holds the generic
+    kernel's and not theirs is served all the same, and the next call with room enough as before it."""
+    import paper_2604_13226_amd as kvp
+    monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", "4000")               # ranges of 64 rows with either kernel
+    w = _request(dtype, d, 2, 900, 3)
+    store = build_store(w, kvp)
+    q_off = np.array([0, 3], np.int32)
+    full = kvp.kvp_prefill_workspace_bytes(store, 1, 3, 903)
+    outs = []
+    for size in (full, 30 * 8 * (d + 2) * 4 + (1 << 14), full):    # 15 ranges, 2 heads: 30 slots of 8 rows, and the query
+        cache = make_cache(w, kvp, store)
+        kvp.kvp_assemble(store, [(rq.packet_ids, 0) for rq in w.requests], cache)
+        q, kn, vn = w.query(0, 0, "cuda:0")
+        out = torch.full_like(q, float("nan"))
+        kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, kvp.alloc_workspace(size), out)
+        outs.append(out.float().cpu())
+    assert torch.equal(outs[0], outs[2])
+    # one computation in two orders: the tolerance of the parity tests
+    assert float((outs[0] - outs[1]).abs().max()) <= (1e-5 if dtype == "f32" else 2e-2)
+    with pytest.raises(kvp.KvpError):
+        kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, kvp.alloc_workspace(256), out)
