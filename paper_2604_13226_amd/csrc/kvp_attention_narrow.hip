@@ -1,0 +1,393 @@
+// kvp_attention_narrow.hip -- K3 for requests of at most 32 packed rows (bf16, head_dim 128): tokens
+// being generated, short questions (Sec. 4.2.1 step 4; Fig. 2(d)).
+//
+// Bound: HBM, and below some ten thousand rows of context the chain of latencies from launch to
+// output.  Every row block of the 128-row kernel would be mostly padding here, one wave of four
+// computing, and its tiles are shared by the waves of a workgroup: a barrier per tile and two to six
+// tiles one after the other.
+//
+// One workgroup = 8 wavefronts = one work item: all packed rows of one (request, KV head) over one kv
+// range.  Every wave owns all the rows and takes every eighth 32-row tile of the range through 16 KB of
+// LDS of its own: no barrier in the loop, 128 KB on their way per compute unit, and at 8K rows of
+// context every tile but one in eight of the launch is requested before the first arrives.  The next
+// K tile is requested as soon as the scores are done, the next V tile after the output product.  The
+// waves' (m, l, O) are merged through LDS.
+//
+//   S^T = K Q^T, online softmax, O^T += V^T P^T: the operand layouts, swizzles and the precision of
+//   every step are those of the 128-row kernel; the partial rows are fp32 (they are few).
+//
+// No two work items read the same rows, so the tile loads carry the streaming hint (8K rows of context,
+// 32 layers: 14.5 us per layer without it, 14.0 with; the caches of 1 to 16 layers, which the last-level
+// cache holds in part: within 0.3 us of each other; 8 contexts of 16.9K rows: 99 and 88).
+//
+// Measured per layer, one token: 8K rows of context 16.8 -> 14.0 us (this kernel 9.9 of it, 4.2 at nominal
+// HBM rate).
+//
+// The query side of the layer: four waves rotate the query rows once, into LDS.  A wave whose tile
+// reaches the query rows rotates those rows of K_new itself, writes them and V_new to the cache and
+// puts them straight into its tile: nothing waits for a store to come back as a load.
+#include "kvp_mfma_device.h"
+
+namespace kvp {
+
+constexpr int NARROW_WAVES = 8;
+constexpr int NARROW_TILE = 32;                               // kv rows per tile
+constexpr int NARROW_HALF = NARROW_TILE * 256;                // bytes of a K (or V) tile
+constexpr int NARROW_ML = NARROW_WAVES * 2 * NARROW_HALF;     // after the tiles: m and l of every wave's rows,
+constexpr int NARROW_Q = NARROW_ML + 2 * NARROW_WAVES * 32 * 4;  // then the rotated query
+constexpr int NARROW_LDS = NARROW_Q + 8 * 64 * 16;
+
+template <int SRC>
+__global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(AttnArgs a)
+{
+    constexpr int D = 128, ROW_BYTES = 2 * D, CH = D / 8, NKS = D / 16, EB = D / 32, NW = NARROW_WAVES, TN = NARROW_TILE;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const AttnItem it = a.inl.n ? attn_inline_item(a.inl, blockIdx.x, a.n_kv, a.part_stride) : a.items[blockIdx.x];
+    if (it.n_rows <= 0) return;  // padding item of the launch order
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, h = lane >> 5;
+    const int n_tiles = (it.kv_end - it.kv_begin + TN - 1) / TN;
+
+    // ---- this lane's query row
+    const bool row_ok = n < it.n_rows;
+    const int m = it.m0 + (row_ok ? n : 0);
+    const int t = m / a.g, hq = it.kv_head * a.g + m % a.g;
+    const int limit = row_ok ? it.ctx_len + t + 1 : 0;      // kv rows [0, limit) are visible
+    const int wave_limit = it.ctx_len + it.m0 / a.g + 1;    // the smallest limit of the block (rows are ordered by token)
+
+    // Rotated query, elements 16 ks + 8 h .. +7 of row n for k-step ks: wave w < 4 loads and rotates
+    // k-steps w and w + 4 (partners).
+    uint4 q_lo = make_uint4(0, 0, 0, 0), q_hi = q_lo;
+    float4 q_cs[4] = {};
+    if (wave < NKS / 2 && row_ok) {
+        const bf16_t *qp = (const bf16_t *)a.q + ((int64_t)(it.q_off + t) * a.n_q_heads + hq) * D + 16 * wave + 8 * h;
+        q_lo = *(const uint4 *)qp;
+        q_hi = *(const uint4 *)(qp + D / 2);
+        const float4 *cs = (const float4 *)(a.cs + (int64_t)(a.prerotated ? 0 : it.pos0 + t) * (D / 2) + 16 * wave + 8 * h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q_cs[j] = cs[j];
+    }
+
+    // ---- tiles.  Load instruction i fills rows 4 i .. 4 i + 3 of a tile; this lane's 16 bytes are those
+    // of row 4 i + lane / 16, K chunk c at place c ^ (row & 15), V chunk c at c ^ 4 (row & 3).
+    char *const kl = lds + wave * 2 * NARROW_HALF, *const vl = kl + NARROW_HALF;
+    const uint32_t lds_k = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)kl);
+    const int slot_row = lane >> 4, slot_chunk = lane & 15;
+    const bf16_t *kc = (const bf16_t *)a.cache.k, *vc = (const bf16_t *)a.cache.v;
+    const int shift = a.cache.block_shift;
+    // byte address of tile ti's first row (contiguous), or of the first rows of the two blocks that
+    // rows 0..15 and 16..31 are in (blocks hold at least 16 rows, tiles start at multiples of 32)
+    struct TileAt { int64_t off[2]; };  // elements
+    auto tile_at = [&](int ti) -> TileAt {
+        TileAt ta;
+        const int row0 = it.kv_begin + ti * TN;
+        if (SRC == SRC_CONTIG) {
+            ta.off[0] = (int64_t)it.req * a.cache.req_stride + (int64_t)a.layer * a.cache.layer_stride + ((int64_t)it.kv_head * a.cache.t_cap + row0) * D;
+            ta.off[1] = ta.off[0] + 16 * D;
+        } else {
+            // (read through the scalar cache: the table is written before the launch, and an ordinary load
+            // would bring a wait of the compiler's that drains the tile loads)
+            typedef const __attribute__((address_space(4))) int32_t *const_i32_p;
+            const_i32_p table = (const_i32_p)(uintptr_t)uniform_ptr(a.cache.block_table + (int64_t)it.req * a.cache.max_blocks);
+            const int last = it.kv_end - 1, row1 = row0 + 16 <= last ? row0 + 16 : last;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int row = u ? row1 : row0;
+                const int b = table[__builtin_amdgcn_readfirstlane(row >> shift)];
+                ta.off[u] = (int64_t)a.layer * a.cache.layer_stride + ((((int64_t)b * a.n_kv + it.kv_head) << shift) + ((row0 + 16 * u) & ((1 << shift) - 1))) * D;
+            }
+        }
+        return ta;
+    };
+    // rows past `max_r` repeat it; in the second half of a tile that ends in its first half, those of the first
+    auto lane_off = [&](int i, int max_r, int chunk) -> uint32_t {
+        int r = 4 * i + slot_row;
+        r = r < max_r ? r : max_r;
+        return (uint32_t)((r & 15) * ROW_BYTES + 16 * chunk);
+    };
+    auto half_of = [&](int i, int max_r) -> int { return i >= 4 && max_r >= 16 ? 1 : 0; };
+    // (rows 16.. of a tile whose last row is below 16 read that row: the clamp makes (r & 15) its place in half 0;
+    // a clamp inside half 1 keeps to half 1)
+    auto issue_k = [&](const TileAt &ta, int max_r, int i) {
+        const int chunk = slot_chunk ^ ((4 * i + slot_row) & 15);
+        load_to_lds_16<true>(uniform_ptr(kc + ta.off[half_of(i, max_r)]), lane_off(i, max_r, chunk), lds_k + 1024 * i);
+    };
+    auto issue_v = [&](const TileAt &ta, int max_r, int i) {
+        load_to_lds_16<true>(uniform_ptr(vc + ta.off[half_of(i, max_r)]), lane_off(i, max_r, slot_chunk ^ (4 * slot_row)), lds_k + NARROW_HALF + 1024 * i);
+    };
+    // The first tile's loads, through the builtin: the compiler counts these, so its wait for the query
+    // loads issued before them does not take them along (they are waited for before the loop).
+    auto issue_first = [&](const TileAt &ta, int max_r) {
+        typedef const __attribute__((address_space(1))) void *global_p;
+        constexpr int AUX = 2;  // the streaming hint
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int hf = half_of(i, max_r);
+            const char *kp = uniform_ptr(kc + ta.off[hf]) + lane_off(i, max_r, slot_chunk ^ ((4 * i + slot_row) & 15));
+            const char *vp = uniform_ptr(vc + ta.off[hf]) + lane_off(i, max_r, slot_chunk ^ (4 * slot_row));
+            __builtin_amdgcn_global_load_lds((global_p)(uintptr_t)kp, (lds_void_p)(lds_k + 1024 * i), 16, 0, AUX);
+            __builtin_amdgcn_global_load_lds((global_p)(uintptr_t)vp, (lds_void_p)(lds_k + NARROW_HALF + 1024 * i), 16, 0, AUX);
+        }
+    };
+    auto rows_of = [&](int ti) -> int {  // rows of tile ti that are in the range
+        const int left = it.kv_end - it.kv_begin - ti * TN;
+        return left < TN ? left : TN;
+    };
+    // Query rows inside tile ti: rotate K_new, append it and V_new to the cache, and put both into the
+    // tile, whose other rows have landed.  64 units per trip: 16 chunks of V per row, 8 pairs of K chunks.
+    struct TailUnit { uint4 v, klo, khi; float4 cs[4]; };
+    auto tail_load = [&](int tail0, int count, int trip) -> TailUnit {
+        TailUnit u;
+        const int iv = trip * 64 + lane < count * CH ? trip * 64 + lane : count * CH - 1;
+        const int ik = trip * 64 + lane < count * (CH / 2) ? trip * 64 + lane : count * (CH / 2) - 1;
+        const int rv = tail0 + iv / CH, rk = tail0 + ik / (CH / 2), e = 8 * (ik % (CH / 2));  // query rows
+        u.v = *(const uint4 *)((const bf16_t *)a.v_new + ((int64_t)(it.q_off + rv) * a.n_kv + it.kv_head) * D + 8 * (iv % CH));
+        const bf16_t *kn = (const bf16_t *)a.k_new + ((int64_t)(it.q_off + rk) * a.n_kv + it.kv_head) * D + e;
+        u.klo = *(const uint4 *)kn;
+        u.khi = *(const uint4 *)(kn + D / 2);
+        const float4 *cs = (const float4 *)(a.cs + (int64_t)(it.pos0 + rk) * (D / 2) + e);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u.cs[j] = cs[j];
+        return u;
+    };
+    auto tail_put = [&](const TileAt &ta, int first, int count, int trip, const TailUnit &u) {  // first: the tile row of the first query row
+        const int iu = trip * 64 + lane;
+        if (iu < count * CH) {
+            const int r = first + iu / CH, c = iu % CH;
+            *(uint4 *)((bf16_t *)a.cache.v + (r < 16 ? ta.off[0] : ta.off[1]) + (r & 15) * D + 8 * c) = u.v;
+            *(uint4 *)(vl + r * ROW_BYTES + 16 * (c ^ (4 * (r & 3)))) = u.v;
+        }
+        if (iu < count * (CH / 2)) {
+            const int r = first + iu / (CH / 2), c = iu % (CH / 2);
+            const float4 one = make_float4(1.f, 0.f, 1.f, 0.f);
+            const float4 cs4[4] = {a.prerotated ? one : u.cs[0], a.prerotated ? one : u.cs[1], a.prerotated ? one : u.cs[2], a.prerotated ? one : u.cs[3]};
+            uint4 lo, hi;
+            rotate_chunk_pair<true>(u.klo, u.khi, cs4, 1.f, 1.f, lo, hi);
+            bf16_t *kd = (bf16_t *)a.cache.k + (r < 16 ? ta.off[0] : ta.off[1]) + (r & 15) * D + 8 * c;
+            *(uint4 *)kd = lo;
+            *(uint4 *)(kd + D / 2) = hi;
+            *(uint4 *)(kl + r * ROW_BYTES + 16 * (c ^ (r & 15))) = lo;
+            *(uint4 *)(kl + r * ROW_BYTES + 16 * ((c + CH / 2) ^ (r & 15))) = hi;
+        }
+    };
+    // A tile with query rows is brought in whole before it is used (it is the last of the range or
+    // one of its last few); the others are only requested.
+    auto fetch_with_tail = [&](int ti) {
+        const TileAt ta = tile_at(ti);
+        const int row0 = it.kv_begin + ti * TN, rows = rows_of(ti);
+        const int first = it.ctx_len > row0 ? it.ctx_len - row0 : 0, count = rows - first, tail0 = row0 + first - it.ctx_len;
+        const TailUnit u0 = tail_load(tail0, count, 0);
+        if (first > 0)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                issue_k(ta, first - 1, i);
+                issue_v(ta, first - 1, i);
+            }
+        // rows past the range repeat the last one there is: zeros do as well, their scores are masked
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), for the compiler's own count too
+        asm volatile("" ::: "memory");
+        if (rows < TN)
+            for (int i = lane; i < (TN - rows) * CH; i += 64) {
+                *(uint4 *)(kl + rows * ROW_BYTES + 16 * i) = make_uint4(0, 0, 0, 0);
+                *(uint4 *)(vl + rows * ROW_BYTES + 16 * i) = make_uint4(0, 0, 0, 0);
+            }
+        tail_put(ta, first, count, 0, u0);
+        for (int trip = 1; trip * 64 < count * CH; ++trip) tail_put(ta, first, count, trip, tail_load(tail0, count, trip));
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    };
+    auto has_tail = [&](int ti) -> bool { return it.kv_begin + ti * TN + rows_of(ti) > it.ctx_len; };
+
+    if (wave < n_tiles) {
+        if (has_tail(wave)) fetch_with_tail(wave);
+        else issue_first(tile_at(wave), rows_of(wave) - 1);
+    }
+    if (wave < NKS / 2) {
+        uint4 lo, hi;
+        rotate_chunk_pair<false>(q_lo, q_hi, q_cs, 1.f, a.scale_log2e, lo, hi);
+        *(uint4 *)(lds + NARROW_Q + (wave * 64 + lane) * 16) = lo;
+        *(uint4 *)(lds + NARROW_Q + ((wave + NKS / 2) * 64 + lane) * 16) = hi;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wg_barrier();
+    bf16x8 qf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)(lds + NARROW_Q + (ks * 64 + lane) * 16);
+
+    floatx16 oacc[EB];
+#pragma unroll
+    for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[eb][r] = 0.f;
+    float m_ref = -INFINITY, l_i = 0.f;  // reference maximum (log2 units) and running sum
+    const int tr_row = (lane & 15) >> 2;
+    const int tr_x = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);  // 16-byte chunk inside the 64-byte column group
+    const int tr_half = 8 * (lane & 1);
+
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the first tile
+    asm volatile("" ::: "memory");
+    bool whole = true;  // all of the tile that comes next is there
+    for (int ti = wave; ti < n_tiles; ti += NW) {
+        const int tn = ti + NW;
+        const bool more = tn < n_tiles && !has_tail(tn);  // the next tile is requested ahead
+        const TileAt tan = more ? tile_at(tn) : TileAt{};
+        const int max_n = more ? rows_of(tn) - 1 : 0;
+
+        if (!whole) wait_vmcnt<8>();  // K is there, the eight loads of V behind it may not be
+        uint4 kf[NKS];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) kf[ks] = *(const uint4 *)(kl + n * ROW_BYTES + 16 * ((2 * ks + h) ^ (n & 15)));
+        floatx16 s;
+        const float c0 = m_ref == -INFINITY ? 0.f : -m_ref;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = c0;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), qf[ks], s, 0, 0, 0);
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K tile has been read
+#pragma unroll
+            for (int i = 0; i < 8; ++i) issue_k(tan, max_n, i);
+        }
+
+        // accumulator r is tile row 8 (r / 4) + 4 h + r % 4
+        const int kv0 = it.kv_begin + ti * TN;
+        if (kv0 + TN > wave_limit || kv0 + TN > it.kv_end) {  // wave-uniform: last tiles only
+            const int end = limit < it.kv_end ? limit : it.kv_end;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (kv0 + 8 * (r >> 2) + 4 * h + (r & 3) >= end) s[r] = -INFINITY;
+        }
+        float mx = max3(s[0], s[1], s[2]);
+#pragma unroll
+        for (int r = 3; r < 15; r += 2) mx = max3(mx, s[r], s[r + 1]);
+        mx = xhalf_max(fmaxf(mx, s[15]));
+        const bool first = m_ref == -INFINITY;
+        const bool move = first ? mx > -INFINITY : mx > RESCALE_SLACK;
+        if (__any(move)) {
+            const float delta = move ? mx : 0.f;
+            const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-delta);  // first: O = l = 0
+            m_ref = first ? (move ? mx : -INFINITY) : m_ref + delta;
+            l_i *= alpha;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] -= delta;
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[eb][r] *= alpha;
+        }
+        uint32_t pk[8];
+        float rs0 = 0.f, rs1 = 0.f;
+        const bf16x2 bf16_ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            pk[r >> 1] = pack_bf16_hw(__builtin_amdgcn_exp2f(s[r]), __builtin_amdgcn_exp2f(s[r + 1]));
+            const bf16x2 pp = __builtin_bit_cast(bf16x2, pk[r >> 1]);  // the row sum takes what multiplies V
+            if (r & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs1, false);
+            else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs0, false);
+        }
+        l_i += rs0 + rs1;
+
+        if (!whole) {
+            if (more) wait_vmcnt<8>();  // V is there (the next K may not be)
+            else wait_vmcnt<0>();
+        }
+        typedef __attribute__((address_space(3))) short4v *lds_s4;
+        short4v vf[2][2 * EB];
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            const char *vp = vl + (16 * st + 4 * h + tr_row) * ROW_BYTES + tr_half;
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb) {
+                const int coff = 16 * (4 * (eb ^ tr_row) + tr_x);
+                vf[st][2 * eb] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(vp + coff));
+                vf[st][2 * eb + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(vp + 8 * ROW_BYTES + coff));
+            }
+        }
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            const bf16x8 pf = __builtin_bit_cast(bf16x8, make_uint4(pk[4 * st], pk[4 * st + 1], pk[4 * st + 2], pk[4 * st + 3]));
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb) {
+                union { short4v s[2]; bf16x8 v; } u;
+                u.s[0] = vf[st][2 * eb];
+                u.s[1] = vf[st][2 * eb + 1];
+                oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u.v, pf, oacc[eb], 0, 0, 0);
+            }
+        }
+        whole = false;
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the V tile has been read
+#pragma unroll
+            for (int i = 0; i < 8; ++i) issue_v(tan, max_n, i);
+        } else if (tn < n_tiles) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            fetch_with_tail(tn);
+            whole = true;
+        }
+    }
+    l_i = xhalf_sum(l_i);  // the lane halves saw different kv rows
+
+    // ---- merge the waves' (m, l, O): a wave parks its rows where its tiles were, 16-byte piece c of row n at c ^ n
+    float *xm = (float *)(lds + NARROW_ML), *xl = xm + NW * 32;
+    if (row_ok) {
+#pragma unroll
+        for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                *(float4 *)(kl + n * (D * 4) + 16 * ((8 * eb + 2 * q4 + h) ^ n)) =
+                    make_float4(oacc[eb][4 * q4], oacc[eb][4 * q4 + 1], oacc[eb][4 * q4 + 2], oacc[eb][4 * q4 + 3]);
+    }
+    if (h == 0) {
+        xm[wave * 32 + n] = m_ref;
+        xl[wave * 32 + n] = l_i;
+    }
+    __syncthreads();
+    for (int u = tid; u < it.n_rows * (D / 4); u += 64 * NW) {
+        const int rr = u / (D / 4), c = u % (D / 4);
+        float mm = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mm = fmaxf(mm, xm[w * 32 + rr]);
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float mw = xm[w * 32 + rr];
+            const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - mm);
+            const float4 o = *(const float4 *)(lds + w * 2 * NARROW_HALF + rr * (D * 4) + 16 * (c ^ rr));
+            l += xl[w * 32 + rr] * wt;
+            if (wt != 0.f) { acc.x += o.x * wt; acc.y += o.y * wt; acc.z += o.z * wt; acc.w += o.w * wt; }
+        }
+        if (it.part_slot < 0) {
+            const int mr = it.m0 + rr;
+            const float inv = 1.f / l;  // the row always sees itself, so l > 0
+            bf16_t *op = (bf16_t *)a.out + ((int64_t)(it.q_off + mr / a.g) * a.n_q_heads + it.kv_head * a.g + mr % a.g) * D + 4 * c;
+            *(uint2 *)op = make_uint2(pack_bf16_hw(acc.x * inv, acc.y * inv), pack_bf16_hw(acc.z * inv, acc.w * inv));
+        } else {
+            float *pp = (float *)((char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 0));
+            *(float4 *)(pp + (int64_t)rr * D + 4 * c) = acc;
+            if (c == 0) {
+                pp[(int64_t)a.bm * D + rr] = mm;
+                pp[(int64_t)a.bm * D + a.bm + rr] = l;
+            }
+        }
+    }
+}
+
+template <int SRC> static int launch_narrow(const AttnArgs &a, void *stream)
+{
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)attention_narrow_kernel<SRC>, hipFuncAttributeMaxDynamicSharedMemorySize, NARROW_LDS);
+        if (e != hipSuccess) return (int)e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(attention_narrow_kernel<SRC>, dim3(a.n_items), dim3(64 * NARROW_WAVES), NARROW_LDS, (hipStream_t)stream, a);
+    return (int)hipGetLastError();
+}
+
+int launch_attention_narrow(const AttnArgs &a, void *stream)
+{
+    if (a.d != 128 || a.bm != ATTN_NARROW_BM || a.tiles) return (int)hipErrorInvalidValue;
+    return a.cache.layout != 0 ? launch_narrow<SRC_PAGED>(a, stream) : launch_narrow<SRC_CONTIG>(a, stream);
+}
+
+}  // namespace kvp

@@ -199,7 +199,9 @@ int launch_attention(int dtype, const AttnArgs &a, int kernel_kind, void *stream
 int launch_combine(int dtype, const AttnArgs &a, void *stream);
 
 // GENERIC: any shape, fp32 vector arithmetic.  MFMA: bf16, F32: fp32, both for head_dim 64, 128, 256.
-enum { ATTN_GENERIC = 0, ATTN_MFMA = 1, ATTN_F32 = 2 };
+// NARROW: bf16, head_dim 128, requests of at most ATTN_NARROW_BM packed rows, from a cache.
+enum { ATTN_GENERIC = 0, ATTN_MFMA = 1, ATTN_F32 = 2, ATTN_NARROW = 3 };
+constexpr int ATTN_NARROW_BM = 32;  // packed rows of a work item of the narrow kernel
 constexpr int ATTN_F32_BM = 32;  // packed rows of a work item of the fp32 kernel
 
 // Matrix-core kernels, paged layout: an item's block ids live in LDS, so one item may span at most

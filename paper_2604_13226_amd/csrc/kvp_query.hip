@@ -447,11 +447,13 @@ int launch_combine(int dtype, const AttnArgs &a, void *stream)
 
 int launch_attention_mfma(const AttnArgs &a, void *stream);  // kvp_attention_mfma.hip
 int launch_attention_f32(const AttnArgs &a, void *stream);   // kvp_attention_f32.hip
+int launch_attention_narrow(const AttnArgs &a, void *stream);  // kvp_attention_narrow.hip
 
 int launch_attention(int dtype, const AttnArgs &a, int kernel_kind, void *stream)
 {
     if (a.n_items == 0) return 0;
     if (kernel_kind == ATTN_MFMA) return launch_attention_mfma(a, stream);
+    if (kernel_kind == ATTN_NARROW) return dtype == 1 ? launch_attention_narrow(a, stream) : (int)hipErrorInvalidValue;
     if (kernel_kind == ATTN_F32) return dtype == 0 ? launch_attention_f32(a, stream) : (int)hipErrorInvalidValue;
     if (dtype == 1) hipLaunchKernelGGL((attention_generic_kernel<bf16_t>), dim3(a.n_items), dim3(256), 0, (hipStream_t)stream, a);
     else hipLaunchKernelGGL((attention_generic_kernel<float>), dim3(a.n_items), dim3(256), 0, (hipStream_t)stream, a);

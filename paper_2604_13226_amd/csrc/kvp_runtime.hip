@@ -1195,7 +1195,29 @@ int attn_kind(const kvp_store *s, const kvp_cache_t *c)
 }
 
 // Packed rows per row block (the MFMA kernel's smaller one).
-int base_bm(int kind) { return kind == ATTN_MFMA ? MFMA_BM : kind == ATTN_F32 ? ATTN_F32_BM : GENERIC_BM; }
+int base_bm(int kind)
+{
+    return kind == ATTN_MFMA ? MFMA_BM : kind == ATTN_F32 ? ATTN_F32_BM : kind == ATTN_NARROW ? ATTN_NARROW_BM : GENERIC_BM;
+}
+
+// The kernel of a call whose requests have `rows` cache rows and the query rows q_off: NARROW takes over
+// from MFMA when every request fits its 32 packed rows (one row more and a wave would need two row blocks;
+// mixed batches stay with MFMA, whose launch the longer requests fill anyway) and the launch is not one
+// that streams many tiles per compute unit: there HBM bounds both (8 contexts of 16.9K rows, one token:
+// 87.9 us here, 89.1 there; one context of 8K: 14.0 and 16.8).
+int call_kind(const kvp_store *s, const kvp_cache_t *c, int n_req, const int32_t *rows, const int32_t *q_off)
+{
+    const kvp_config_t &g = s->cfg;
+    const int kind = attn_kind(s, c);
+    if (kind != ATTN_MFMA || g.head_dim != 128 || s->force_bm || s->force_split_in_wg >= 0) return kind;
+    int64_t tiles = 0;
+    for (int r = 0; r < n_req; ++r) {
+        const int n_q = q_off[r + 1] - q_off[r];
+        if ((int64_t)n_q * (g.n_q_heads / g.n_kv_heads) > ATTN_NARROW_BM) return kind;
+        if (n_q > 0) tiles += (int64_t)g.n_kv_heads * ((rows[r] + n_q + 63) / 64);
+    }
+    return streams_many_tiles(s, tiles, MFMA_BM) ? kind : ATTN_NARROW;
+}
 
 // Partial rows in scaled fp16: the MFMA kernel at 128 columns (elsewhere they are fp32).
 int part_f16_of(int kind, int d) { return kind == ATTN_MFMA && d == 128 ? 1 : 0; }
@@ -1222,6 +1244,7 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
     const bool fine = s->target_items > 0 && (kind == ATTN_F32 || g.head_dim != 128);  // (the test knob: as finely as the kernel can)
     const int min_split = kind == ATTN_GENERIC || fine ? 64 : 256;
     if (kind == ATTN_F32 && s->target_items == 0) p.bn = 128;
+    if (kind == ATTN_NARROW) p.bn = 32;
     p.reqs.resize(n_req);
     int64_t n_groups = 0;
     for (int r = 0; r < n_req; ++r) {
@@ -1234,7 +1257,9 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
     int64_t tiles = 0;  // 64-row tiles all the items together will read
     for (int r = 0; r < n_req; ++r)
         tiles += (int64_t)g.n_kv_heads * (((int64_t)p.reqs[r].n_q * gq + p.bm - 1) / p.bm) * ((p.reqs[r].ctx_len + p.reqs[r].n_q + 63) / 64);
-    // (the fp32 kernel is bound by the matrix pipe from the first tile on: an item for every CU)
+    // (the fp32 kernel is bound by the matrix pipe from the first tile on: an item for every CU.  The narrow
+    // kernel keeps to three quarters: one token at 8K took 14.5 us per layer with 176-200 items, 15.1 with
+    // 232, whose combine needs a second round of loads, and 15.0 with 128.)
     const int target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s, tiles, mfma && g.head_dim == 128 ? p.bm : 0);
     int want = (int)std::min<int64_t>(MAX_SPLITS, (target + n_groups - 1) / n_groups);
     if (want < 1) want = 1;
@@ -1437,8 +1462,9 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     kvp_store::PrefillCached &pf = *found;
     // fp32 stores and head dims 64 and 256: the matrix kernels' fp32 partial rows come in blocks of 32 and
     // 128 rows, the generic kernel's in blocks of 8, so a workspace may hold the one and not the other.
-    // Such a call takes the generic kernel, as it does wherever the matrix kernels cannot go.
-    const int best_kind = attn_kind(s, cache);
+    // Such a call takes the generic kernel, as it does wherever the matrix kernels cannot go.  The narrow
+    // kernel cuts finer than the 128-row kernel, and steps back to that one.
+    const int best_kind = call_kind(s, cache, n_req, rows.data(), q_offsets);
     const bool may_fall_back = best_kind != ATTN_GENERIC && !part_f16_of(best_kind, g.head_dim);
     if (hit && may_fall_back && !in_capture && !pf.captured && (pf.kind == best_kind ? workspace_bytes < pf.need : workspace_bytes >= pf.best_need)) hit = false;
     if (in_capture && !hit)
@@ -1457,7 +1483,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         const uint64_t best_need = plan_need();
         if (may_fall_back && !s->dry && workspace_bytes < best_need) {
             p = PrefillPlan();
-            plan_prefill(s, cache, ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, p);
         }
         const uint64_t need = plan_need();
         const uint64_t bytes = p.reqs.size() * sizeof(ReqMeta) + p.row_req.size() * 4 + p.groups.size() * sizeof(AttnGroup) +
@@ -1475,7 +1501,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         if (rc) return rc;
         AttnInline inl;
         inl.n = 0;
-        if (p.kind == ATTN_MFMA)
+        if (p.kind == ATTN_MFMA || p.kind == ATTN_NARROW)
             fill_inline_items(s, n_req, p.reqs.data(), p.groups, p.items, p.bm, p.part_stride, p.split_len0,
                               g.n_q_heads / g.n_kv_heads, inl);
         if (fixed && bytes > KVP_STATIC_PLAN_BYTES)
@@ -1506,7 +1532,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         }
         {
             kvp_store::DebugPlan &dp = s->dbg_plan;
-            const int64_t head[6] = {p.kind == ATTN_MFMA && g.head_dim == 128 ? 1 : 0, p.bm, (int64_t)p.groups.size(), (int64_t)p.items.size(), p.n_slots, (int64_t)need};
+            const int64_t head[6] = {(p.kind == ATTN_MFMA && g.head_dim == 128) || p.kind == ATTN_NARROW ? 1 : 0, p.bm, (int64_t)p.groups.size(), (int64_t)p.items.size(), p.n_slots, (int64_t)need};
             memcpy(dp.head, head, sizeof head);
             dp.groups.swap(p.groups);  // (already copied into the plan buffer above)
             dp.items.swap(p.items);

@@ -102,3 +102,17 @@ def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkey
     assert float((outs[0] - outs[1]).abs().max()) <= (1e-5 if dtype == "f32" else 2e-2)
     with pytest.raises(kvp.KvpError):
         kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, kvp.alloc_workspace(256), out)
+
+
+@pytest.mark.parametrize("g,ctx,n_q,paged,target,n_req", [
+    (1, 0, 1, False, None, 1), (4, 1, 1, True, None, 2), (4, 31, 1, False, None, 1), (7, 32, 4, True, None, 3), (4, 255, 8, False, None, 1),
+    (8, 257, 4, True, "4000", 1), (1, 1000, 32, False, "4000", 2), (2, 16, 16, True, None, 1), (4, 5000, 1, False, None, 1),
+    (4, 2047, 2, True, "1", 2), (7, 3000, 3, False, "40", 1), (32, 700, 1, False, None, 1),
+])
+def test_bf16_requests_of_few_packed_rows(gpu_device, monkeypatch, g, ctx, n_q, paged, target, n_req):
+    """At most 32 packed rows: eight waves with tiles of their own; "1": one range, so every wave takes
+    several tiles and the query rows come in a later one."""
+    if target:
+        monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
+    w = _request("bf16", 128, g, ctx, n_q, paged=paged, n_req=n_req)
+    compare(w, run_workload(w), oracle_workload(w))
