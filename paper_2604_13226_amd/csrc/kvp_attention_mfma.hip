@@ -93,7 +93,7 @@ __device__ unsigned long long *kvp_timing_phases;  // [item][8 waves][8]
 //   NW 8, KS 2, 4 stages: 128 rows, the two groups take alternate tiles of the item's range
 //                         (an in-workgroup split-KV that halves the serial chain of a
 //                         latency-bound item) and merge their (m, l, O) through LDS.
-template <int D, int STAGES, int SRC, int NW, int KS, bool NTL>
+template <int D, int STAGES, int SRC, int NW, int KS, bool NTL, bool QUAD>
 __device__ __forceinline__ void attention_body(const AttnArgs &a)
 {
     constexpr int ROW_BYTES = D * 2;
@@ -239,19 +239,43 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     // B operand of S^T = K Q^T: lane holds Q[m][16 ks + 8 h .. +7] for every k-step ks, rotated by
     // `rel` positions and multiplied by log2(e)/sqrt(d).  Element 16 ks + 8 h + j (ks < NKS / 2)
     // pairs with the same slot of ks + NKS / 2, so the rotation stays inside the lane.
+    // KS = 2: the two groups hold the same rows; each loads and rotates half of the k-steps, and they
+    // exchange the results through LDS.
     constexpr int NKH = NKS / 2;
+    constexpr int NQP = NKH / KS;  // partner pairs of k-steps a wave rotates: grp NQP .. + NQP - 1
     bf16x8 qf[NKS];
     const bf16_t *qp = (const bf16_t *)a.q + ((int64_t)(it.q_off + t) * a.n_q_heads + hq) * D + 8 * h;
     const int q_pos = a.prerotated ? 0 : it.pos0 + t;  // rotation the query still needs
-    u32x4_t qraw[NKS], csraw[4 * NKH];
-    auto q_issue = [&](int delta) {  // 3 D / 16 loads: the raw query row and the (cos, sin) of its rotation
-        const bf16_t *qsrc = row_ok ? qp : (const bf16_t *)a.q + 8 * h;  // idle lanes read row 0 (and drop it)
+    // QUAD, a multiple of four query heads to a KV head: the four lanes of a quad hold rows of one token: each
+    // loads a quarter of its (cos, sin) pairs, scales it, and the rotation takes the rest from its
+    // neighbours.  (A workgroup of 128 rows pulls 48 KB through the CU's texture unit before it can start,
+    // not 96.  Four heads, 128 rows, per layer: 2.9K rows 20.2 -> 20.0 us, 8K 29.9 -> 29.8, pruned 26.6 ->
+    // 26.3.  A template argument: chosen at run time, the in-place variant held both versions' registers
+    // and spilled.)
+    auto rotate_k_step = [&](const uint4 &lo, const uint4 &hi, const float4 &cs_own, uint4 &olo, uint4 &ohi) {  // cs_own: scaled
+        const float4 cs4[4] = {quad_lane<0>(cs_own), quad_lane<1>(cs_own), quad_lane<2>(cs_own), quad_lane<3>(cs_own)};
+        rotate_query_pair<true>(lo, hi, cs4, 1.f, olo, ohi);
+    };
+    auto directed = [&](const float4 &v, float sign) -> float4 {  // (only a packet can lie ahead of the query's own position)
+        return SRC == SRC_PACKETS ? make_float4(v.x, v.y * sign, v.z, v.w * sign) : v;
+    };
+    u32x4_t qraw[2 * NQP], csraw[4 * NQP];
+    auto q_issue = [&](int delta) {  // 3 D / 16 / KS loads: the raw query row and the (cos, sin) of its rotation
+        const bf16_t *qsrc = (row_ok ? qp : (const bf16_t *)a.q + 8 * h) + 16 * NQP * grp;  // idle lanes read row 0 (and drop it)
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) qraw[ks] = load16_nowait(qsrc + 16 * ks);
+        for (int ks = 0; ks < NQP; ++ks) {
+            qraw[ks] = load16_nowait(qsrc + 16 * ks);
+            qraw[ks + NQP] = load16_nowait(qsrc + 16 * (ks + NKH));
+        }
         const int rel = row_ok ? q_pos - delta : 0;
-        const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * (D / 2) + 8 * h);
+        const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * (D / 2) + 8 * h + 16 * NQP * grp);
+        if (QUAD) {
 #pragma unroll
-        for (int ks = 0; ks < NKH; ++ks)
+            for (int ks = 0; ks < NQP; ++ks) csraw[ks] = load16_nowait(csr + 8 * ks + (lane & 3));
+            return;
+        }
+#pragma unroll
+        for (int ks = 0; ks < NQP; ++ks)
 #pragma unroll
             for (int j = 0; j < 4; ++j) csraw[4 * ks + j] = load16_nowait(csr + 8 * ks + j);
     };
@@ -263,22 +287,47 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         else wait_vmcnt<0>();
         // the registers are valid from here on: keep every use below this point
 #pragma unroll
-        for (int i = 0; i < NKS; ++i) asm volatile("" : "+v"(qraw[i]));
+        for (int i = 0; i < 2 * NQP; ++i) asm volatile("" : "+v"(qraw[i]));
 #pragma unroll
-        for (int i = 0; i < 4 * NKH; ++i) asm volatile("" : "+v"(csraw[i]));
+        for (int i = 0; i < 4 * NQP; ++i) asm volatile("" : "+v"(csraw[i]));
         const int rel = row_ok ? q_pos - delta : 0;
         const float sign = rel < 0 ? -1.f : 1.f;
+        char *qx = lds + (STAGES - 1) * STAGE_BYTES + wave_r * (64 * 16) + lane * 16;  // KS = 2: [NKS][RW][64 lanes]; no tile is in this stage yet
+        static_assert(KS == 1 || KS * PR < STAGES, "the last stage is free until the loop");
+        auto keep = [&](int ks, const uint4 &olo, const uint4 &ohi) {
+            if (KS == 2) {
+                *(uint4 *)(qx + (ks + NQP * grp) * (RW * 64 * 16)) = olo;
+                *(uint4 *)(qx + (ks + NQP * grp + NKH) * (RW * 64 * 16)) = ohi;
+            } else {
+                qf[ks] = __builtin_bit_cast(bf16x8, olo);
+                qf[ks + NKH] = __builtin_bit_cast(bf16x8, ohi);
+            }
+        };
+        const float sc = row_ok ? a.scale_log2e : 0.f;  // (idle lanes: zeros, whatever their registers hold)
+        if (QUAD) {
 #pragma unroll
-        for (int ks = 0; ks < NKH; ++ks) {
-            float4 cs4[4];  // (cos, sin) pairs of elements 16 ks + 8 h + 2 j, + 1
+            for (int ks = 0; ks < NQP; ++ks) {
+                uint4 olo, ohi;
+                rotate_k_step(__builtin_bit_cast(uint4, qraw[ks]), __builtin_bit_cast(uint4, qraw[ks + NQP]),
+                              scale_cs(__builtin_bit_cast(float4, csraw[ks]), sc, sc * sign), olo, ohi);
+                keep(ks, olo, ohi);
+            }
+        } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) cs4[j] = __builtin_bit_cast(float4, csraw[4 * ks + j]);
-            uint4 lo = __builtin_bit_cast(uint4, qraw[ks]), hi = __builtin_bit_cast(uint4, qraw[ks + NKH]);
-            if (!row_ok) lo = hi = make_uint4(0, 0, 0, 0);
-            uint4 olo, ohi;
-            rotate_chunk_pair<false>(lo, hi, cs4, sign, a.scale_log2e, olo, ohi);
-            qf[ks] = __builtin_bit_cast(bf16x8, olo);
-            qf[ks + NKH] = __builtin_bit_cast(bf16x8, ohi);
+            for (int ks = 0; ks < NQP; ++ks) {
+                float4 cs4[4];  // (cos, sin) pairs of elements 16 ks + 8 h + 2 j, + 1
+#pragma unroll
+                for (int j = 0; j < 4; ++j) cs4[j] = directed(__builtin_bit_cast(float4, csraw[4 * ks + j]), sign);
+                uint4 olo, ohi;
+                rotate_query_pair<false>(__builtin_bit_cast(uint4, qraw[ks]), __builtin_bit_cast(uint4, qraw[ks + NQP]), cs4, sc, olo, ohi);
+                keep(ks, olo, ohi);
+            }
+        }
+        if (KS == 2) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            wg_barrier();
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const bf16x8 *)(qx + ks * (RW * 64 * 16));
         }
         // pinned: nothing of this is recomputed or waited for inside the tile loop
 #pragma unroll
@@ -293,13 +342,27 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         const int rel = row_ok ? q_pos - delta : 0;
         const float sign = rel < 0 ? -1.f : 1.f;
         const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * (D / 2) + 8 * h);
+        const float sc = a.scale_log2e;
+        float4 own[NKH];
+        if (QUAD) {
+#pragma unroll
+            for (int ks = 0; ks < NKH; ++ks) own[ks] = csr[8 * ks + (lane & 3)];
+        }
 #pragma unroll
         for (int ks = 0; ks < NKH; ++ks) {
             float4 cs4[4];
+            if (QUAD) {
+                own[ks] = scale_cs(own[ks], sc, sc * sign);
+                cs4[0] = quad_lane<0>(own[ks]);
+                cs4[1] = quad_lane<1>(own[ks]);
+                cs4[2] = quad_lane<2>(own[ks]);
+                cs4[3] = quad_lane<3>(own[ks]);
+            } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) cs4[j] = csr[8 * ks + j];
+                for (int j = 0; j < 4; ++j) cs4[j] = directed(csr[8 * ks + j], sign);
+            }
             uint4 olo, ohi;
-            rotate_chunk_pair<false>(qr[ks], qr[ks + NKH], cs4, sign, a.scale_log2e, olo, ohi);
+            rotate_query_pair<QUAD>(qr[ks], qr[ks + NKH], cs4, sc, olo, ohi);
             qf[ks] = __builtin_bit_cast(bf16x8, olo);
             qf[ks + NKH] = __builtin_bit_cast(bf16x8, ohi);
         }
@@ -392,7 +455,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                     const float4 one = make_float4(1.f, 0.f, 1.f, 0.f);
                     const float4 cs4[4] = {a.prerotated ? one : u.c0, a.prerotated ? one : u.c1, a.prerotated ? one : u.c2, a.prerotated ? one : u.c3};
                     uint4 olo, ohi;
-                    rotate_chunk_pair<true>(u.ulo, u.uhi, cs4, 1.f, 1.f, olo, ohi);
+                    rotate_chunk_pair(u.ulo, u.uhi, cs4, olo, ohi);
                     *(uint4 *)(kcw + u.dst) = olo;
                     *(uint4 *)(kcw + u.dst + D / 2) = ohi;
                 };
@@ -662,41 +725,50 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     l_i = xhalf_sum(l_i);
     KVP_STAMP(30);
 
+    // KS = 2: both groups go on with half of the columns each (EBO blocks from column col0 on).  (Shared query
+    // and halves, against one group that merges and writes everything: 8K context as two-group items 31.3 ->
+    // 30.0 us per layer; one token over 8 contexts of 16.9K rows 89.3 -> 87.8.)
+    constexpr int EBO = EB / KS;
+    const int col0 = KS == 2 ? 32 * EBO * grp : 0;
     if (KS == 2) {
         static_assert(KS == 1 || D == 128, "the two-group shape's LDS layout");
-        // ---- merge the two groups' (m, l, O) of each row through LDS (the tile stages are free
-        // once every wave has left the loop): group 1 writes, group 0 folds it in and goes on.
+        // ---- merge the two groups' (m, l, O) of each row through LDS (the tile stages are free once
+        // every wave has left the loop): each group hands over the columns the other goes on with.
         wg_barrier();
-        float *xo = (float *)lds;                      // [16][RW][64 lanes][4]
-        float *xm = xo + 16 * RW * 64 * 4;             // [RW][64] m, then [RW][64] l
-        if (grp == 1) {
+        float *xo = (float *)lds;                      // [2][4 EBO][RW][64 lanes][4]
+        float *xm = xo + 2 * 4 * EBO * RW * 64 * 4;    // [2][RW][64] m, then [2][RW][64] l
+        auto hand_over = [&](const floatx16 *o) {
 #pragma unroll
-            for (int eb = 0; eb < EB; ++eb)
+            for (int q = 0; q < 4 * EBO; ++q)
+                *(float4 *)(xo + (((grp * 4 * EBO + q) * RW + wave_r) * 64 + lane) * 4) =
+                    make_float4(o[q >> 2][4 * (q & 3)], o[q >> 2][4 * (q & 3) + 1], o[q >> 2][4 * (q & 3) + 2], o[q >> 2][4 * (q & 3) + 3]);
+        };
+        if (grp == 0) {
+            hand_over(oacc + EBO % EB);
+        } else {
+            hand_over(oacc);
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    *(float4 *)(xo + (((4 * eb + q4) * RW + wave_r) * 64 + lane) * 4) =
-                        make_float4(oacc[eb][4 * q4], oacc[eb][4 * q4 + 1], oacc[eb][4 * q4 + 2], oacc[eb][4 * q4 + 3]);
-            xm[wave_r * 64 + lane] = m_ref;
-            xm[RW * 64 + wave_r * 64 + lane] = l_i;
+            for (int eb = 0; eb < EBO; ++eb) oacc[eb] = oacc[eb + EB - EBO];
         }
+        xm[(grp * RW + wave_r) * 64 + lane] = m_ref;
+        xm[((2 + grp) * RW + wave_r) * 64 + lane] = l_i;
         __syncthreads();
-        if (grp == 1) return;
-        const float m1 = xm[wave_r * 64 + lane], l1 = xm[RW * 64 + wave_r * 64 + lane];
+        const float m1 = xm[((1 - grp) * RW + wave_r) * 64 + lane], l1 = xm[((3 - grp) * RW + wave_r) * 64 + lane];
         const float mm = fmaxf(m_ref, m1);
         const float a0 = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - mm);
         const float a1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - mm);
         m_ref = mm;
-        l_i = l_i * a0 + l1 * a1;
+        l_i = grp == 0 ? l_i * a0 + l1 * a1 : l1 * a1 + l_i * a0;
 #pragma unroll
-        for (int eb = 0; eb < EB; ++eb)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const float4 o1 = *(const float4 *)(xo + (((4 * eb + q4) * RW + wave_r) * 64 + lane) * 4);
-                oacc[eb][4 * q4] = oacc[eb][4 * q4] * a0 + o1.x * a1;
-                oacc[eb][4 * q4 + 1] = oacc[eb][4 * q4 + 1] * a0 + o1.y * a1;
-                oacc[eb][4 * q4 + 2] = oacc[eb][4 * q4 + 2] * a0 + o1.z * a1;
-                oacc[eb][4 * q4 + 3] = oacc[eb][4 * q4 + 3] * a0 + o1.w * a1;
-            }
+        for (int q = 0; q < 4 * EBO; ++q) {
+            const float4 o1 = *(const float4 *)(xo + ((((1 - grp) * 4 * EBO + q) * RW + wave_r) * 64 + lane) * 4);
+            floatx16 &o = oacc[q >> 2];
+            const int r = 4 * (q & 3);
+            o[r] = o[r] * a0 + o1.x * a1;
+            o[r + 1] = o[r + 1] * a0 + o1.y * a1;
+            o[r + 2] = o[r + 2] * a0 + o1.z * a1;
+            o[r + 3] = o[r + 3] * a0 + o1.w * a1;
+        }
     }
 
     if (SPLIT_P && __any(dropped != 0)) {
@@ -725,13 +797,13 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             bf16_t *op = (bf16_t *)a.out + ((int64_t)(it.q_off + t) * a.n_q_heads + hq) * D;
             const float inv = 1.f / l_i;
 #pragma unroll
-            for (int eb = 0; eb < EB; ++eb)
+            for (int eb = 0; eb < EBO; ++eb)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
                     uint2 u;
                     u.x = pack_bf16_hw(oacc[eb][4 * q4] * inv, oacc[eb][4 * q4 + 1] * inv);
                     u.y = pack_bf16_hw(oacc[eb][4 * q4 + 2] * inv, oacc[eb][4 * q4 + 3] * inv);
-                    *(uint2 *)(op + 32 * eb + 8 * q4 + 4 * h) = u;
+                    *(uint2 *)(op + col0 + 32 * eb + 8 * q4 + 4 * h) = u;
                 }
         }
     }
@@ -759,10 +831,16 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         char *pp = (char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 1);
         float amax = 0.f;
 #pragma unroll
-        for (int eb = 0; eb < EB; ++eb)
+        for (int eb = 0; eb < EBO; ++eb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) amax = fmaxf(amax, __builtin_fabsf(oacc[eb][r]));
         amax = xhalf_max(amax);
+        if (KS == 2) {  // the row's other columns are with the other group
+            float *xa = (float *)(lds + 68 * 1024);
+            xa[(grp * RW + wave_r) * 64 + lane] = amax;
+            __syncthreads();
+            amax = fmaxf(amax, xa[((1 - grp) * RW + wave_r) * 64 + lane]);
+        }
         int e = amax > 0.f ? __builtin_amdgcn_frexp_expf(amax) : 0;  // amax = f 2^e with f in [0.5, 1)
         e = e < -100 ? -100 : (e > 120 ? 120 : e);                   // (keeps l 2^-e and 2^-e itself in range)
         const float sc = __builtin_ldexpf(1.f, -e);
@@ -776,24 +854,25 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         // The rows go through LDS so that they leave as whole 256-byte rows (four per store
         // instruction) instead of 16-byte pieces: each wave parks its 32 x D halves in a region of its
         // own in the (now idle) tile stages, 8-byte chunk c of row n at chunk c ^ n (n mod the chunks of
-        // a row), and reads them back row by row.  (KS = 2: the merge above has used the first 66 KiB; the rows go behind.)
+        // a row), and reads them back row by row.  (KS = 2: half rows, behind the first 70 KiB that the merge has used.)
         if (KS == 1) wg_barrier();  // every wave is done with the tiles
-        char *reg = lds + (KS == 2 ? 68 * 1024 : 0) + wave_r * (32 * D * 2);
+        constexpr int CHO = CH / KS, OB = 16 * CHO;  // 16-byte chunks and bytes of a row that this wave writes
+        char *reg = lds + (KS == 2 ? 70 * 1024 : 0) + wave * (32 * OB);
 #pragma unroll
-        for (int eb = 0; eb < EB; ++eb)
+        for (int eb = 0; eb < EBO; ++eb)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) *(uint2 *)(reg + n * (D * 2) + 8 * ((8 * eb + 2 * q4 + h) ^ (n & (2 * CH - 1)))) = pack4(eb, q4);
+            for (int q4 = 0; q4 < 4; ++q4) *(uint2 *)(reg + n * OB + 8 * ((8 * eb + 2 * q4 + h) ^ (n & (2 * CHO - 1)))) = pack4(eb, q4);
         // (a wave reads only what it wrote itself: no barrier, the compiler orders the two)
-        const int c = lane % CH;
+        const int c = lane % CHO;
 #pragma unroll
-        for (int j = 0; j < 32 / RPI; ++j) {
-            const int r = RPI * j + lane / CH;
+        for (int j = 0; j < CHO / 2; ++j) {
+            const int r = 64 / CHO * j + lane / CHO;
             // logical 8-byte chunks 2c and 2c + 1 of row r sit in the 16-byte unit c ^ (r >> 1), swapped when r is odd
-            uint4 f = *(const uint4 *)(reg + r * (D * 2) + 16 * (c ^ ((r >> 1) & (CH - 1))));
+            uint4 f = *(const uint4 *)(reg + r * OB + 16 * (c ^ ((r >> 1) & (CHO - 1))));
             if (r & 1) f = make_uint4(f.z, f.w, f.x, f.y);
-            if (32 * wave_r + r < it.n_rows) *(uint4 *)(pp + (int64_t)(32 * wave_r + r) * (D * 2) + 16 * c) = f;
+            if (32 * wave_r + r < it.n_rows) *(uint4 *)(pp + (int64_t)(32 * wave_r + r) * (D * 2) + 2 * col0 + 16 * c) = f;
         }
-        if (row_ok && h == 0) {
+        if (row_ok && h == 0 && grp == 0) {
             float *ml = (float *)(pp + part_rows_bytes(a.bm, D, 1));
             ml[rr] = m_ref == -INFINITY ? -INFINITY : m_ref + (float)e;
             ml[a.bm + rr] = l_i * sc;
@@ -803,22 +882,22 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
 }
 
 // (256 columns: twice the accumulators and query registers, one wave per SIMD)
-template <int D, int STAGES, int SRC, int NW, int KS, bool NTL>
+template <int D, int STAGES, int SRC, int NW, int KS, bool NTL, bool QUAD>
 __global__ __launch_bounds__(64 * NW, D == 256 ? 1 : 2) void attention_mfma_kernel(AttnArgs a)
 {
-    attention_body<D, STAGES, SRC, NW, KS, NTL>(a);
+    attention_body<D, STAGES, SRC, NW, KS, NTL, QUAD>(a);
 }
 
 // 8 waves, 4 stages, the row block chosen item by item: 256 packed rows, or (AttnItem::half_block)
 // at most 128 rows handled by two wave groups that take alternate tiles.  A launch of 256-row
 // blocks uses it when some groups -- the last rows of a request -- fill at most half a block:
 // such an item then holds its compute unit for half the time.
-template <int SRC>
+template <int SRC, bool QUAD>
 __global__ __launch_bounds__(512, 2) void attention_mfma_mixed_kernel(AttnArgs a)
 {
     const bool half = a.inl.n ? false : a.items[blockIdx.x].half_block != 0;  // (regular launches have no half blocks)
-    if (half) attention_body<128, 4, SRC, 8, 2, false>(a);
-    else attention_body<128, 4, SRC, 8, 1, false>(a);
+    if (half) attention_body<128, 4, SRC, 8, 2, false, QUAD>(a);
+    else attention_body<128, 4, SRC, 8, 1, false, QUAD>(a);
 }
 
 template <typename K> static int launch_kernel(K kernel, bool &attr_set, int lds_bytes, int threads, const AttnArgs &a, void *stream)
@@ -832,11 +911,11 @@ template <typename K> static int launch_kernel(K kernel, bool &attr_set, int lds
     return (int)hipGetLastError();
 }
 
-template <int D, int SRC, int NW, int KS, int STAGES, bool NTL> static int launch_variant_nt(const AttnArgs &a, void *stream)
+template <int D, int SRC, int NW, int KS, int STAGES, bool NTL, bool QUAD> static int launch_variant_nt(const AttnArgs &a, void *stream)
 {
     constexpr int lds_bytes = STAGES * stage_bytes(D) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
     static bool attr_set = false;
-    return launch_kernel(attention_mfma_kernel<D, STAGES, SRC, NW, KS, NTL>, attr_set, lds_bytes, 64 * NW, a, stream);
+    return launch_kernel(attention_mfma_kernel<D, STAGES, SRC, NW, KS, NTL, QUAD>, attr_set, lds_bytes, 64 * NW, a, stream);
 }
 
 // The streaming hint on the tile loads (a.nt_loads) exists for the 8-wave shapes, which stream
@@ -844,15 +923,22 @@ template <int D, int SRC, int NW, int KS, int STAGES, bool NTL> static int launc
 // share their rows).
 template <int SRC, int NW, int KS, int STAGES> static int launch_variant(const AttnArgs &a, void *stream)
 {
-    if (NW == 8 && a.nt_loads) return launch_variant_nt<128, SRC, NW, KS, STAGES, NW == 8>(a, stream);
-    return launch_variant_nt<128, SRC, NW, KS, STAGES, false>(a, stream);
+    const bool quad = a.g % 4 == 0;
+    if (NW == 8 && a.nt_loads)
+        return quad ? launch_variant_nt<128, SRC, NW, KS, STAGES, NW == 8, true>(a, stream) : launch_variant_nt<128, SRC, NW, KS, STAGES, NW == 8, false>(a, stream);
+    return quad ? launch_variant_nt<128, SRC, NW, KS, STAGES, false, true>(a, stream) : launch_variant_nt<128, SRC, NW, KS, STAGES, false, false>(a, stream);
+}
+
+template <int SRC, bool QUAD> static int launch_mixed_as(const AttnArgs &a, void *stream)
+{
+    constexpr int lds_bytes = 4 * stage_bytes(128) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
+    static bool attr_set = false;
+    return launch_kernel(attention_mfma_mixed_kernel<SRC, QUAD>, attr_set, lds_bytes, 512, a, stream);
 }
 
 template <int SRC> static int launch_mixed(const AttnArgs &a, void *stream)
 {
-    constexpr int lds_bytes = 4 * stage_bytes(128) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
-    static bool attr_set = false;
-    return launch_kernel(attention_mfma_mixed_kernel<SRC>, attr_set, lds_bytes, 512, a, stream);
+    return a.g % 4 == 0 ? launch_mixed_as<SRC, true>(a, stream) : launch_mixed_as<SRC, false>(a, stream);
 }
 
 template <int NW, int KS, int STAGES> static int launch_nw(const AttnArgs &a, void *stream)
@@ -870,8 +956,8 @@ template <int NW, int KS, int STAGES> static int launch_nw(const AttnArgs &a, vo
 template <int D, int STAGES> static int launch_other_dim(const AttnArgs &a, void *stream)
 {
     if (a.bm != 128 || a.tiles) return (int)hipErrorInvalidValue;
-    return a.cache.layout != 0 ? launch_variant_nt<D, SRC_PAGED, 4, 1, STAGES, false>(a, stream)
-                               : launch_variant_nt<D, SRC_CONTIG, 4, 1, STAGES, false>(a, stream);
+    return a.cache.layout != 0 ? launch_variant_nt<D, SRC_PAGED, 4, 1, STAGES, false, false>(a, stream)
+                               : launch_variant_nt<D, SRC_CONTIG, 4, 1, STAGES, false, false>(a, stream);
 }
 
 // a.bm selects the row block (128 columns): 256 packed rows (8 waves; a.mixed: with half blocks among them,

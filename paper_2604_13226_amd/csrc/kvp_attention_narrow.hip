@@ -163,7 +163,7 @@ __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(
             const float4 one = make_float4(1.f, 0.f, 1.f, 0.f);
             const float4 cs4[4] = {a.prerotated ? one : u.cs[0], a.prerotated ? one : u.cs[1], a.prerotated ? one : u.cs[2], a.prerotated ? one : u.cs[3]};
             uint4 lo, hi;
-            rotate_chunk_pair<true>(u.klo, u.khi, cs4, 1.f, 1.f, lo, hi);
+            rotate_chunk_pair(u.klo, u.khi, cs4, lo, hi);
             bf16_t *kd = (bf16_t *)a.cache.k + (r < 16 ? ta.off[0] : ta.off[1]) + (r & 15) * D + 8 * c;
             *(uint4 *)kd = lo;
             *(uint4 *)(kd + D / 2) = hi;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(
     }
     if (wave < NKS / 2) {
         uint4 lo, hi;
-        rotate_chunk_pair<false>(q_lo, q_hi, q_cs, 1.f, a.scale_log2e, lo, hi);
+        rotate_query_pair<false>(q_lo, q_hi, q_cs, a.scale_log2e, lo, hi);
         *(uint4 *)(lds + NARROW_Q + (wave * 64 + lane) * 16) = lo;
         *(uint4 *)(lds + NARROW_Q + ((wave + NKS / 2) * 64 + lane) * 16) = hi;
     }

@@ -117,13 +117,12 @@ __device__ __forceinline__ bf16x8 drop_nonfinite(const bf16x8 &v, uint32_t &drop
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// One 16-byte chunk pair of a head vector rotated by the (cos, sin) pairs in cs4 (Eq. 1):
-// element i of the low chunk pairs with element i of the high chunk.
-template <bool EXACT>
-__device__ __forceinline__ void rotate_chunk_pair(const uint4 &ulo, const uint4 &uhi, const float4 (&cs4)[4], float sign,
-                                                  float scale, uint4 &olo, uint4 &ohi)
+// One 16-byte chunk pair of a head vector rotated by the (cos, sin) pairs in cs4 (Eq. 1): element i of
+// the low chunk pairs with element i of the high chunk.  Products and sums are rounded separately, as
+// in the gather kernel.
+__device__ __forceinline__ void rotate_chunk_pair(const uint4 &ulo, const uint4 &uhi, const float4 (&cs4)[4], uint4 &olo, uint4 &ohi)
 {
-#pragma clang fp contract(off)  // EXACT: separately rounded products and sums, as the gather kernel
+#pragma clang fp contract(off)
     const uint32_t wl[4] = {ulo.x, ulo.y, ulo.z, ulo.w}, wh[4] = {uhi.x, uhi.y, uhi.z, uhi.w};
     uint32_t ol[4], oh[4];
 #pragma unroll
@@ -133,22 +132,49 @@ __device__ __forceinline__ void rotate_chunk_pair(const uint4 &ulo, const uint4 
         for (int u = 0; u < 2; ++u) {
             const float x = __uint_as_float(u ? (wl[j] & 0xFFFF0000u) : (wl[j] << 16));
             const float y = __uint_as_float(u ? (wh[j] & 0xFFFF0000u) : (wh[j] << 16));
-            const float c = u ? cs4[j].z : cs4[j].x, sn = (u ? cs4[j].w : cs4[j].y) * sign;
+            const float c = u ? cs4[j].z : cs4[j].x, sn = u ? cs4[j].w : cs4[j].y;
             const float xc = x * c, ys = y * sn, yc = y * c, xs = x * sn;
             lo2[u] = xc - ys;
             hi2[u] = yc + xs;
-            if (!EXACT) { lo2[u] *= scale; hi2[u] *= scale; }
         }
-        if (EXACT) {
-            ol[j] = (uint32_t)f32_to_bf16(lo2[0]) | ((uint32_t)f32_to_bf16(lo2[1]) << 16);
-            oh[j] = (uint32_t)f32_to_bf16(hi2[0]) | ((uint32_t)f32_to_bf16(hi2[1]) << 16);
-        } else {
-            ol[j] = pack_bf16_hw(lo2[0], lo2[1]);
-            oh[j] = pack_bf16_hw(hi2[0], hi2[1]);
-        }
+        ol[j] = (uint32_t)f32_to_bf16(lo2[0]) | ((uint32_t)f32_to_bf16(lo2[1]) << 16);
+        oh[j] = (uint32_t)f32_to_bf16(hi2[0]) | ((uint32_t)f32_to_bf16(hi2[1]) << 16);
     }
     olo = make_uint4(ol[0], ol[1], ol[2], ol[3]);
     ohi = make_uint4(oh[0], oh[1], oh[2], oh[3]);
+}
+
+// The same for the query, which nothing is compared with bit for bit: sums are fused.  SCALED: cs4 holds
+// the pairs times the score scale already (where one lane scales them for four), else the results are
+// multiplied.
+template <bool SCALED>
+__device__ __forceinline__ void rotate_query_pair(const uint4 &ulo, const uint4 &uhi, const float4 (&cs4)[4], float scale, uint4 &olo, uint4 &ohi)
+{
+    const float k = SCALED ? 1.f : scale;
+    const uint32_t wl[4] = {ulo.x, ulo.y, ulo.z, ulo.w}, wh[4] = {uhi.x, uhi.y, uhi.z, uhi.w};
+    uint32_t ol[4], oh[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float x0 = __uint_as_float(wl[j] << 16), x1 = __uint_as_float(wl[j] & 0xFFFF0000u);
+        const float y0 = __uint_as_float(wh[j] << 16), y1 = __uint_as_float(wh[j] & 0xFFFF0000u);
+        const float l0 = __builtin_fmaf(x0, cs4[j].x, -(y0 * cs4[j].y)), l1 = __builtin_fmaf(x1, cs4[j].z, -(y1 * cs4[j].w));
+        const float h0 = __builtin_fmaf(y0, cs4[j].x, x0 * cs4[j].y), h1 = __builtin_fmaf(y1, cs4[j].z, x1 * cs4[j].w);
+        ol[j] = SCALED ? pack_bf16_hw(l0, l1) : pack_bf16_hw(l0 * k, l1 * k);
+        oh[j] = SCALED ? pack_bf16_hw(h0, h1) : pack_bf16_hw(h0 * k, h1 * k);
+    }
+    olo = make_uint4(ol[0], ol[1], ol[2], ol[3]);
+    ohi = make_uint4(oh[0], oh[1], oh[2], oh[3]);
+}
+__device__ __forceinline__ float4 scale_cs(const float4 &v, float scale, float sin_scale)
+{
+    return make_float4(v.x * scale, v.y * sin_scale, v.z * scale, v.w * sin_scale);
+}
+
+// v of lane J of this lane's group of four
+template <int J> __device__ __forceinline__ float4 quad_lane(const float4 &v)
+{
+    auto bc = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x55 * J, 0xF, 0xF, true)); };
+    return make_float4(bc(v.x), bc(v.y), bc(v.z), bc(v.w));
 }
 
 enum { SRC_CONTIG = 0, SRC_PAGED = 1, SRC_PACKETS = 2 };
