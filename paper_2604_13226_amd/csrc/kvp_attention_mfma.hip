@@ -918,14 +918,12 @@ template <int D, int SRC, int NW, int KS, int STAGES, bool NTL, bool QUAD> stati
     return launch_kernel(attention_mfma_kernel<D, STAGES, SRC, NW, KS, NTL, QUAD>, attr_set, lds_bytes, 64 * NW, a, stream);
 }
 
-// The streaming hint on the tile loads (a.nt_loads) exists for the 8-wave shapes, which stream
-// long contexts; the planner asks for it nowhere else (launches of 4-wave workgroups are short or
-// share their rows).
+// (a.nt_loads: the streaming hint on the tile loads, streams_rows in the planner)
 template <int SRC, int NW, int KS, int STAGES> static int launch_variant(const AttnArgs &a, void *stream)
 {
     const bool quad = a.g % 4 == 0;
-    if (NW == 8 && a.nt_loads)
-        return quad ? launch_variant_nt<128, SRC, NW, KS, STAGES, NW == 8, true>(a, stream) : launch_variant_nt<128, SRC, NW, KS, STAGES, NW == 8, false>(a, stream);
+    if (a.nt_loads)
+        return quad ? launch_variant_nt<128, SRC, NW, KS, STAGES, true, true>(a, stream) : launch_variant_nt<128, SRC, NW, KS, STAGES, true, false>(a, stream);
     return quad ? launch_variant_nt<128, SRC, NW, KS, STAGES, false, true>(a, stream) : launch_variant_nt<128, SRC, NW, KS, STAGES, false, false>(a, stream);
 }
 

@@ -103,7 +103,7 @@ static_assert(sizeof(AttnTile) == 32, "AttnTile is 32 bytes");
 
 // The work items of a launch for ONE request whose packed rows fit one row block are a regular
 // pattern -- kv head h, split sp, all splits the same length but the last -- in a known launch
-// order (the full splits of every head, head by head, then the heads' shorter last splits).  A
+// order (split by split, the heads of a split next to each other).  A
 // workgroup of such a launch rebuilds its AttnItem from its index with scalar arithmetic and
 // starts its query and tile loads one memory round trip earlier than one that first has to fetch
 // its item.  The host fills this only after it has rebuilt every planned item with the same
@@ -114,21 +114,14 @@ struct AttnInline {
     int32_t ctx_len, pos0, n_q;  // the request
     int32_t split_len;           // kv rows (in-place path: tiles) per split
     int32_t vis;                 // end of the kv range the rows may see
-    int32_t ns, n_front;         // splits per head; how many of them come in the front part of the launch order
+    int32_t ns;                  // splits per head
     int32_t n_rows;              // packed rows (n_q x heads per kv head)
 };
 
 __host__ __device__ inline AttnItem attn_inline_item(const AttnInline &t, int i, int n_kv, int part_stride)
 {
     AttnItem it{};
-    int h, sp;
-    if (i < n_kv * t.n_front) {
-        h = i / t.n_front;
-        sp = i - h * t.n_front;
-    } else {  // (n_front = ns - 1: the last splits follow, one per head)
-        h = i - n_kv * t.n_front;
-        sp = t.ns - 1;
-    }
+    const int sp = i / n_kv, h = i - sp * n_kv;
     it.group = h;
     it.split = sp;
     it.kv_begin = sp * t.split_len;

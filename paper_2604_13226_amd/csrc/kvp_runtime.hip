@@ -1020,10 +1020,15 @@ void assign_part_slots(std::vector<AttnGroup> &groups, std::vector<AttnItem> &it
 // of unequal size are padded with null items (n_rows = 0: the workgroup exits at once).
 // Cohorts go out longest first (kv rows x query rows of their largest member): workgroups
 // start in index order as compute units fall free, so the long items of a ragged batch start
-// early and the short ones fill the end of the launch.
-bool xcd_order(std::vector<AttnItem> &items)  // returns whether any two items share their K/V rows
+// early and the short ones fill the end of the launch.  With a multiple of eight KV heads, cohorts of
+// equal work go out split by split: head h then stays on XCD h % 8, where the combine's workgroups of that
+// head run too and find its partial rows in the L2 (per layer: 2.9K rows 20.0 -> 19.1 us, one token at 8K
+// 13.9 -> 13.5, in place 21.6 -> 21.2, pruned 26.2 -> 25.5).  Four heads have two XCDs each, whatever the
+// order, and measured 2 % slower split by split.
+bool xcd_order(std::vector<AttnItem> &items, int n_kv)  // returns whether any two items share their K/V rows
 {
     constexpr int XCDS = 8;
+    const bool by_split = n_kv % XCDS == 0;
     const int n = (int)items.size();
     // items by cohort key, original order inside a cohort
     struct Ref { int64_t key; int idx; };
@@ -1033,7 +1038,7 @@ bool xcd_order(std::vector<AttnItem> &items)  // returns whether any two items s
         refs[i] = Ref{((int64_t)it.req << 40) ^ ((int64_t)it.kv_head << 28) ^ (int64_t)it.split, i};
     }
     std::sort(refs.begin(), refs.end(), [](const Ref &x, const Ref &y) { return x.key != y.key ? x.key < y.key : x.idx < y.idx; });
-    struct Cohort { int first, count, order; int64_t work; };  // refs[first .. first + count); order = its first item's index
+    struct Cohort { int first, count; int64_t order, work; };  // refs[first .. first + count)
     std::vector<Cohort> cohorts;
     bool shared = false;
     for (int i = 0; i < n;) {
@@ -1043,11 +1048,12 @@ bool xcd_order(std::vector<AttnItem> &items)  // returns whether any two items s
             const AttnItem &it = items[refs[j].idx];
             work = std::max(work, (int64_t)(it.kv_end - it.kv_begin) * it.n_rows);
         }
-        cohorts.push_back(Cohort{i, j - i, refs[i].idx, work});
+        const AttnItem &it = items[refs[i].idx];
+        cohorts.push_back(Cohort{i, j - i, by_split ? ((int64_t)it.req << 40) ^ ((int64_t)it.split << 16) ^ (int64_t)it.kv_head : (int64_t)refs[i].idx, work});
         shared |= j - i > 1;
         i = j;
     }
-    // longest first; equal work keeps the planner's order
+    // longest first; equal work: request by request, split by split, the heads of a split next to each other
     std::sort(cohorts.begin(), cohorts.end(),
               [](const Cohort &x, const Cohort &y) { return x.work != y.work ? x.work > y.work : x.order < y.order; });
     std::vector<AttnItem> out;
@@ -1155,7 +1161,7 @@ struct PrefillPlan {
     bool mixed = false;  // MFMA kernel, 256-row blocks: some groups are half blocks
     bool split_in_wg = false;  // MFMA kernel, 128-row blocks: 8 waves in two groups on alternate tiles
     bool shared_rows = false;  // some work items read the same K/V rows (several row blocks per request and head),
-                               // or the launch is short: either way no streaming hint on the tile loads
+                               // or the rows are few (streams_rows): either way no streaming hint on the tile loads
     int split_len0 = 0;        // kv rows per split of request 0
 };
 
@@ -1171,6 +1177,20 @@ constexpr int MAX_SPLITS = 64;
 bool streams_many_tiles(const kvp_store *s, int64_t tiles, int bm)
 {
     return bm == 128 && tiles >= 16 * (int64_t)s->n_cu;
+}
+
+// Whether a call's tile loads carry the streaming hint, provided that no two work items read the same
+// rows: long launches, and calls whose rows over all layers of the store (a forward pass reads every
+// layer's once) would not stay in the 256 MB last-level cache anyway.  There the rows only push the
+// partial results out of the L2s (per layer, without and with the hint: 8K context over 32 layers 29.4
+// and 28.0 us, in place 21.2 and 19.4, 2.9K rows 19.0 and 18.4; over 8 layers of 8K, 270 MB, 30.1 and
+// 28.6).  Rows that do stay are better kept (2.9K rows over 8 layers, 95 MB: 16.9 and 17.2; one layer of
+// four in-place requests of 8K, 135 MB: 39.3 and 42).
+bool streams_rows(const kvp_store *s, int64_t rows, int64_t tiles)
+{
+    const kvp_config_t &g = s->cfg;
+    const int64_t bytes = rows * g.n_layers * 2 * g.n_kv_heads * g.head_dim * (int64_t)s->esize;
+    return tiles >= 16 * (int64_t)s->n_cu || bytes >= (int64_t)192 << 20;
 }
 
 // Work items a launch should have.  Three quarters of the CU count when the call reads little
@@ -1318,7 +1338,9 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
             }
     }
     assign_part_slots(p.groups, p.items, p.any_split ? p.part_stride : 0, p.n_slots);
-    p.shared_rows = xcd_order(p.items) || tiles < 16 * (int64_t)s->n_cu;  // (short launches: the hint measured slower)
+    int64_t rows = 0;
+    for (int r = 0; r < n_req; ++r) rows += p.reqs[r].n_q > 0 ? p.reqs[r].ctx_len + p.reqs[r].n_q : 0;
+    p.shared_rows = xcd_order(p.items, g.n_kv_heads) || !streams_rows(s, rows, tiles);
 }
 
 // The items of a one-request MFMA launch as a formula in the kernel arguments (AttnInline), if
@@ -1341,23 +1363,16 @@ void fill_inline_items(const kvp_store *s, int n_req, const ReqMeta *reqs, const
     t.vis = 0;
     for (const AttnItem &it : items) t.vis = std::max(t.vis, it.kv_end);
     if ((int64_t)n_kv * t.ns != (int64_t)items.size()) return;
-    for (int n_front : {t.ns, t.ns - 1}) {  // the last splits in place, or behind all the others
-        if (n_front < 1 && t.ns > 1) continue;
-        t.n_front = n_front;
-        bool same = true;
-        for (size_t i = 0; i < items.size() && same; ++i) {
-            const AttnItem &want = items[i];
-            const AttnItem got = attn_inline_item(t, (int)i, n_kv, part_stride);
-            same = got.group == want.group && got.split == want.split && got.kv_begin == want.kv_begin && got.kv_end == want.kv_end &&
-                   got.req == want.req && got.kv_head == want.kv_head && got.m0 == want.m0 && got.n_rows == want.n_rows &&
-                   got.ctx_len == want.ctx_len && got.q_off == want.q_off && got.part_slot == want.part_slot && got.n_q == want.n_q &&
-                   got.pos0 == want.pos0 && got.half_block == want.half_block;
-        }
-        if (same) {
-            t.n = (int32_t)items.size();
+    for (size_t i = 0; i < items.size(); ++i) {
+        const AttnItem &want = items[i];
+        const AttnItem got = attn_inline_item(t, (int)i, n_kv, part_stride);
+        if (got.group != want.group || got.split != want.split || got.kv_begin != want.kv_begin || got.kv_end != want.kv_end ||
+            got.req != want.req || got.kv_head != want.kv_head || got.m0 != want.m0 || got.n_rows != want.n_rows ||
+            got.ctx_len != want.ctx_len || got.q_off != want.q_off || got.part_slot != want.part_slot || got.n_q != want.n_q ||
+            got.pos0 != want.pos0 || got.half_block != want.half_block)
             return;
-        }
     }
+    t.n = (int32_t)items.size();
 }
 
 uint64_t q_rot_bytes(const kvp_store *s, int64_t tot_q)
@@ -1855,7 +1870,11 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
                 }
         }
         assign_part_slots(groups, items, any_split ? part_stride : 0, n_slots);
-        const bool shared_rows = xcd_order(items) || n_tiles_total < 16 * (int64_t)s->n_cu;  // (short launches: the hint measured slower)
+        int64_t rows_total = 0;
+        for (int r = 0; r < n_req; ++r)
+            if (metas[r].n_q > 0)
+                for (int i = 0; i < n_pkt_tiles[r]; ++i) rows_total += tiles[tile_begin[r] + i].n_rows;
+        const bool shared_rows = xcd_order(items, g.n_kv_heads) || !streams_rows(s, rows_total, n_tiles_total);
         AttnInline inl;
         inl.n = 0;
         if (n_req == 1 && metas[0].n_q > 0) {
