@@ -20,8 +20,8 @@
 // 32 layers: 14.5 us per layer without it, 14.0 with; the caches of 1 to 16 layers, which the last-level
 // cache holds in part: within 0.3 us of each other; 8 contexts of 16.9K rows: 99 and 88).
 //
-// Measured per layer, one token: 8K rows of context 16.8 -> 14.0 us (this kernel 9.9 of it, 4.2 at nominal
-// HBM rate).
+// Measured per layer, one token: 8K rows of context 16.8 -> 14.0 us (4.2 at nominal HBM rate), 13.7 since
+// the splits of a head stay on one XCD; this kernel is 9.7 of it.
 //
 // The query side of the layer: four waves rotate the query rows once, into LDS.  A wave whose tile
 // reaches the query rows rotates those rows of K_new itself, writes them and V_new to the cache and
