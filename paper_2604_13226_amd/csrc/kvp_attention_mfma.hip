@@ -681,11 +681,14 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                     float p0 = __builtin_amdgcn_exp2f(sacc[kb][r]);
                     float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1]);
                     if (SPLIT_P) {
-                        // cut, not rounded: the rest is positive (and kept so), and both parts times an infinity of V agree
+                        // Cut, not rounded, so that the rest is never negative; 2^-23 of p on top keeps it above zero
+                        // where p is (both parts times an infinity of V then agree), and only there: a masked
+                        // entry's p is zero, and so is what its row of V, however large, is multiplied by.
+                        constexpr float ABOVE = 1.f + 0x1p-23f;
                         pk[r >> 1] = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302);
-                        const float q0 = p0 - __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u);
-                        const float q1 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
-                        pl[r >> 1] = pack_bf16_hw(fmaxf(q0, 0x1p-126f), fmaxf(q1, 0x1p-126f));
+                        const float q0 = __builtin_fmaf(p0, ABOVE, -__uint_as_float(__float_as_uint(p0) & 0xFFFF0000u));
+                        const float q1 = __builtin_fmaf(p1, ABOVE, -__uint_as_float(__float_as_uint(p1) & 0xFFFF0000u));
+                        pl[r >> 1] = pack_bf16_hw(q0, q1);
                         rs0 += p0;
                         rs1 += p1;
                         continue;

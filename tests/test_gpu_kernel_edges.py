@@ -79,6 +79,34 @@ def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypa
         assert bool((torch.isinf(got[hit]) if value == float("inf") else torch.isnan(got[hit])).all())
 
 
+@pytest.mark.parametrize("d,g,ctx,n_q,paged", [
+    (64, 1, 0, 2, False), (64, 4, 70, 40, True), (64, 2, 63, 65, False), (256, 1, 0, 2, True), (256, 2, 100, 30, False),
+])
+@pytest.mark.parametrize("value", [3.3895313892515355e38, -3.3895313892515355e38])
+def test_the_largest_v_of_a_later_token_stays_out_of_earlier_rows(gpu_device, d, g, ctx, n_q, paged, value):
+    """The largest bf16 times any positive weight a masked entry could be given would show: the rows
+    before the token, and the columns beside it, keep every bit."""
+    import paper_2604_13226_amd as kvp
+    w = _request("bf16", d, g, ctx, n_q, paged=paged)
+    store = build_store(w, kvp)
+    q_off = np.array([0, n_q], np.int32)
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, n_q, ctx + n_q))
+    outs = []
+    for large in (False, True):
+        cache = make_cache(w, kvp, store)
+        kvp.kvp_assemble(store, [(rq.packet_ids, 0) for rq in w.requests], cache)
+        q, kn, vn = w.query(0, 0, "cuda:0")
+        if large:
+            vn[n_q - 1, 0, d // 2 + 3] = value
+        out = torch.empty_like(q)
+        kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, ws, out)
+        outs.append(out.float().cpu())
+    changed = outs[0] != outs[1]
+    assert bool(changed[n_q - 1, :g, d // 2 + 3].all())
+    changed[n_q - 1, :g, d // 2 + 3] = False
+    assert not bool(changed.any())
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 256)])
 def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkeypatch, dtype, d):
     """The matrix kernels' partial rows come in larger blocks: a call whose workspace holds the generic
