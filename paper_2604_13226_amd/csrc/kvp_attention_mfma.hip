@@ -74,7 +74,7 @@ __device__ unsigned long long *kvp_timing_phases;  // [item][8 waves][8]
 #define KVP_PHASE_WRITE do {} while (0)
 #endif
 
-// The query is held rotated and multiplied by log2(e)/sqrt(d), so S = K Q^T is in log2
+// The query is held rotated and (128 columns) multiplied by log2(e)/sqrt(d), so S = K Q^T is in log2
 // units.  The S accumulators start at -m_ref: after the MFMAs they hold s - m_ref and the
 // probabilities are exp2 of them with no further arithmetic.
 //
@@ -109,8 +109,12 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     constexpr int PR = STAGES / KS - 1;  // rounds (of KS tiles) loaded ahead
     static_assert(STAGES % KS == 0 && PR >= 1, "stages");
     // Head dims other than 128: a probability goes into the product as two bf16 numbers, its leading eight
-    // bits and the rest (16 bits together); the row sum and the partial rows are fp32.
+    // bits and the rest (16 bits together); the row sum and the partial rows are fp32.  The query is rotated
+    // only, and the scores are scaled as they leave the matrix cores (one multiplication per score): scaled
+    // before it is rounded to bf16, a query that came rotated, or a column that turns so slowly that
+    // its values hardly change, would be rounded where the product can take it exactly.
     constexpr bool SPLIT_P = D != 128;
+    const float q_scale = SPLIT_P ? 1.f : a.scale_log2e, s_scale = SPLIT_P ? a.scale_log2e : 1.f;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     KVP_STAMP(0);
     const AttnItem it = a.inl.n ? attn_inline_item(a.inl, blockIdx.x, a.n_kv, a.part_stride) : a.items[blockIdx.x];
@@ -237,7 +241,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     const int wave_limit = it.ctx_len + (it.m0 + 32 * wave_r) / g + 1;
 
     // B operand of S^T = K Q^T: lane holds Q[m][16 ks + 8 h .. +7] for every k-step ks, rotated by
-    // `rel` positions and multiplied by log2(e)/sqrt(d).  Element 16 ks + 8 h + j (ks < NKS / 2)
+    // `rel` positions and multiplied by q_scale.  Element 16 ks + 8 h + j (ks < NKS / 2)
     // pairs with the same slot of ks + NKS / 2, so the rotation stays inside the lane.
     // KS = 2: the two groups hold the same rows; each loads and rotates half of the k-steps, and they
     // exchange the results through LDS.
@@ -303,7 +307,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 qf[ks + NKH] = __builtin_bit_cast(bf16x8, ohi);
             }
         };
-        const float sc = row_ok ? a.scale_log2e : 0.f;  // (idle lanes: zeros, whatever their registers hold)
+        const float sc = row_ok ? q_scale : 0.f;  // (idle lanes: zeros, whatever their registers hold)
         if (QUAD) {
 #pragma unroll
             for (int ks = 0; ks < NQP; ++ks) {
@@ -342,7 +346,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         const int rel = row_ok ? q_pos - delta : 0;
         const float sign = rel < 0 ? -1.f : 1.f;
         const float4 *csr = (const float4 *)(a.cs + (int64_t)(rel < 0 ? -rel : rel) * (D / 2) + 8 * h);
-        const float sc = a.scale_log2e;
+        const float sc = q_scale;
         float4 own[NKH];
         if (QUAD) {
 #pragma unroll
@@ -485,7 +489,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[eb][r] = 0.f;
-    float m_ref = -INFINITY, l_i = 0.f;  // reference max (log2 units) and running sum
+    float m_ref = -INFINITY, l_i = 0.f;  // reference max (in the accumulators' units) and running sum
     // -m_ref in all 16 slots (every accumulator of a lane belongs to the same query row): the
     // first S MFMA of a tile takes it as its C operand, so S - m_ref costs no extra instruction.
     // Rewritten only when the reference moves; pinned so that it is not rebuilt per tile.
@@ -629,10 +633,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         // The reference moves when a row sees its first visible entry (it becomes that
         // tile's maximum) and afterwards only when the maximum outgrows the slack.
         const bool first = m_ref == -INFINITY;
-        const bool move = first ? mx > -INFINITY : mx > RESCALE_SLACK;
+        const bool move = first ? mx > -INFINITY : mx * s_scale > RESCALE_SLACK;
         if (__any(move)) {  // wave-uniform; rare once the maxima settle
             const float delta = move ? mx : 0.f;
-            const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-delta);  // first: O = l = 0
+            const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-delta * s_scale);  // first: O = l = 0
             m_ref = first ? (move ? mx : -INFINITY) : m_ref + delta;
             l_i *= alpha;
 #pragma unroll
@@ -678,8 +682,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 uint32_t pk[8], pl[8];
 #pragma unroll
                 for (int r = 0; r < 16; r += 2) {
-                    float p0 = __builtin_amdgcn_exp2f(sacc[kb][r]);
-                    float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1]);
+                    float p0 = __builtin_amdgcn_exp2f(sacc[kb][r] * s_scale);
+                    float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1] * s_scale);
                     if (SPLIT_P) {
                         // Cut, not rounded, so that the rest is never negative; 2^-23 of p on top keeps it above zero
                         // where p is (both parts times an infinity of V then agree), and only there: a masked
@@ -726,6 +730,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     }
     KVP_PHASE_WRITE;
     l_i = xhalf_sum(l_i);
+    m_ref *= s_scale;  // log2 units from here on
     KVP_STAMP(30);
 
     // KS = 2: both groups go on with half of the columns each (EBO blocks from column col0 on).  (Shared query

@@ -107,6 +107,34 @@ def test_the_largest_v_of_a_later_token_stays_out_of_earlier_rows(gpu_device, d,
     assert not bool(changed.any())
 
 
+@pytest.mark.parametrize("d", [64, 256])
+def test_a_prerotated_query_enters_the_scores_as_it_is(gpu_device, d):
+    """Queries x * ones for 128 values of x against a key y * ones and keys of zeros: the value behind a zero
+    key comes out as exp(-S) with S = x y sqrt(d), 14 to 28, so that one more rounding of x to bf16 (2^-8 of it at
+    most) would be up to ten per cent.  Bound: the output's own rounding, 2^-8 of a value just above a
+    power of two, and 2^-10 for the fp32 score (28 times at most 256 roundings of 2^-24)."""
+    import paper_2604_13226_amd as kvp
+    n_q, g, y = 32, 4, 1.734375 * 8 / d ** 0.5
+    store = kvp.kvp_store_create(1, g, 1, d, "bf16", 5.0e5, 4096, kvp.packet_bytes(1, 1, d, "bf16", 2))
+    k = torch.zeros((1, 1, 2, d), dtype=torch.bfloat16, device="cuda:0")
+    v = torch.zeros_like(k)
+    k[0, 0, 0], v[0, 0, 1] = y, 1.0
+    kvp.kvp_store_put(store, 0, k, v)
+    cache = kvp.Cache.contiguous(store, 1, 2 + n_q)
+    kvp.kvp_assemble(store, [([0], 0)], cache)                          # Delta = 0: nothing is rotated
+    x = 1.0 + torch.arange(128, dtype=torch.float64) / 128
+    q = x.view(n_q, g, 1).expand(n_q, g, d).to(device="cuda:0", dtype=torch.bfloat16).contiguous()
+    zero = torch.zeros((n_q, 1, d), dtype=torch.bfloat16, device="cuda:0")
+    out = torch.empty_like(q)
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, n_q, 2 + n_q))
+    kvp.kvp_query_prefill(store, cache, 0, q, zero, zero, np.array([0, n_q], np.int32), ws, out, kvp.KVP_PREROTATED)
+    s = x * float(k[0, 0, 0, 0]) * d ** 0.5
+    seen = 1.0 + torch.arange(n_q, dtype=torch.float64).repeat_interleave(g) + 1.0   # keys of zeros: one stored, t + 1 of the query
+    want = torch.exp(-s) / (1.0 + seen * torch.exp(-s))
+    got = out.double().cpu().view(128, d)
+    assert float((got / want[:, None] - 1).abs().max()) <= 2.0 ** -8 + 2.0 ** -10
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 256)])
 def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkeypatch, dtype, d):
     """The matrix kernels' partial rows come in larger blocks: a call whose workspace holds the generic
