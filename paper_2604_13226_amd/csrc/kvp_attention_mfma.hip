@@ -115,6 +115,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     // its values hardly change, would be rounded where the product can take it exactly.
     constexpr bool SPLIT_P = D != 128;
     const float q_scale = SPLIT_P ? 1.f : a.scale_log2e, s_scale = SPLIT_P ? a.scale_log2e : 1.f;
+    const float above = RESCALE_SLACK / s_scale;  // the slack in the accumulators' units
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     KVP_STAMP(0);
     const AttnItem it = a.inl.n ? attn_inline_item(a.inl, blockIdx.x, a.n_kv, a.part_stride) : a.items[blockIdx.x];
@@ -632,12 +633,14 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         mx = xhalf_max(mx);  // row max relative to m_ref
         // The reference moves when a row sees its first visible entry (it becomes that
         // tile's maximum) and afterwards only when the maximum outgrows the slack.
+        // (Head dims other than 128 set the reference the slack above the maximum: no weight exceeds one, so V
+        // near the top of bf16's range overflows no earlier than in the generic kernel.)
         const bool first = m_ref == -INFINITY;
-        const bool move = first ? mx > -INFINITY : mx * s_scale > RESCALE_SLACK;
+        const bool move = first ? mx > -INFINITY : mx > (SPLIT_P ? 0.f : RESCALE_SLACK);
         if (__any(move)) {  // wave-uniform; rare once the maxima settle
-            const float delta = move ? mx : 0.f;
+            const float delta = move ? (SPLIT_P ? mx + above : mx) : 0.f;
             const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-delta * s_scale);  // first: O = l = 0
-            m_ref = first ? (move ? mx : -INFINITY) : m_ref + delta;
+            m_ref = first ? (move ? delta : -INFINITY) : m_ref + delta;
             l_i *= alpha;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)

@@ -135,6 +135,29 @@ def test_a_prerotated_query_enters_the_scores_as_it_is(gpu_device, d):
     assert float((got / want[:, None] - 1).abs().max()) <= 2.0 ** -8 + 2.0 ** -10
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 256), ("bf16", 64), ("bf16", 256)])
+def test_v_near_the_top_of_its_range_does_not_overflow(gpu_device, dtype, d):
+    """All of V is 2^121 and one key of the second tile scores 7.9 (log2) above the rest: 103 weights of at most
+    one keep every sum below 2^128, and the output is 2^121; relative to the first tile's maximum that
+    key's weight alone would bring 2^128.9."""
+    import paper_2604_13226_amd as kvp
+    n_q, g, rows = 3, 2, 100
+    store = kvp.kvp_store_create(1, g, 1, d, dtype, 5.0e5, 4096, kvp.packet_bytes(1, 1, d, dtype, rows))
+    k = torch.zeros((1, 1, rows, d), dtype=store.torch_dtype, device="cuda:0")
+    v = torch.full_like(k, 2.0 ** 121)
+    k[0, 0, 90] = 7.9 * np.log(2.0) / d ** 0.5
+    kvp.kvp_store_put(store, 0, k, v)
+    cache = kvp.Cache.contiguous(store, 1, rows + n_q)
+    kvp.kvp_assemble(store, [([0], 0)], cache)
+    q = torch.ones((n_q, g, d), dtype=store.torch_dtype, device="cuda:0")
+    kn, vn = torch.zeros_like(q[:, :1]).contiguous(), torch.full_like(q[:, :1], 2.0 ** 121).contiguous()
+    out = torch.empty_like(q)
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, n_q, rows + n_q))
+    kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, np.array([0, n_q], np.int32), ws, out, kvp.KVP_PREROTATED)
+    # (103 additions, and for bf16 the cut of a probability to 17 bits and the output's rounding)
+    assert float((out.double().cpu() / 2.0 ** 121 - 1).abs().max()) <= (2.0 ** -8 if dtype == "bf16" else 2.0 ** -16)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 256)])
 def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkeypatch, dtype, d):
     """The matrix kernels' partial rows come in larger blocks: a call whose workspace holds the generic
