@@ -35,7 +35,8 @@ constexpr int NARROW_TILE = 32;                               // kv rows per til
 constexpr int NARROW_HALF = NARROW_TILE * 256;                // bytes of a K (or V) tile
 constexpr int NARROW_ML = NARROW_WAVES * 2 * NARROW_HALF;     // after the tiles: m and l of every wave's rows,
 constexpr int NARROW_Q = NARROW_ML + 2 * NARROW_WAVES * 32 * 4;  // then the rotated query
-constexpr int NARROW_LDS = NARROW_Q + 8 * 64 * 16;
+constexpr int NARROW_DROPPED = NARROW_Q + 8 * 64 * 16;           // and a word per wave: it left something of V_new out
+constexpr int NARROW_LDS = NARROW_DROPPED + NARROW_WAVES * 4;
 
 template <int SRC>
 __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(AttnArgs a)
@@ -136,6 +137,10 @@ __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(
     };
     // Query rows inside tile ti: rotate K_new, append it and V_new to the cache, and put both into the
     // tile, whose other rows have landed.  64 units per trip: 16 chunks of V per row, 8 pairs of K chunks.
+    // (Infinities and NaNs of V_new stay out of the tile, as zeros: the zero probability of an earlier row
+    // would make them NaN.  They are added at the end, to the rows that see them.  One token hides from none.)
+    const bool hides = it.n_q > 1 && it.kv_end > it.ctx_len;
+    uint32_t dropped = 0;
     struct TailUnit { uint4 v, klo, khi; float4 cs[4]; };
     auto tail_load = [&](int tail0, int count, int trip) -> TailUnit {
         TailUnit u;
@@ -156,7 +161,9 @@ __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(
         if (iu < count * CH) {
             const int r = first + iu / CH, c = iu % CH;
             *(uint4 *)((bf16_t *)a.cache.v + (r < 16 ? ta.off[0] : ta.off[1]) + (r & 15) * D + 8 * c) = u.v;
-            *(uint4 *)(vl + r * ROW_BYTES + 16 * (c ^ (4 * (r & 3)))) = u.v;
+            uint4 v = u.v;
+            if (hides) v = __builtin_bit_cast(uint4, drop_nonfinite(__builtin_bit_cast(bf16x8, v), dropped));
+            *(uint4 *)(vl + r * ROW_BYTES + 16 * (c ^ (4 * (r & 3)))) = v;
         }
         if (iu < count * (CH / 2)) {
             const int r = first + iu / (CH / 2), c = iu % (CH / 2);
@@ -341,7 +348,16 @@ __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(
         xm[wave * 32 + n] = m_ref;
         xl[wave * 32 + n] = l_i;
     }
+    int *const xd = (int *)(lds + NARROW_DROPPED);
+    if (hides) {
+        if (lane == 0) xd[wave] = 0;
+        if (dropped) xd[wave] = 1;
+    }
     __syncthreads();
+    bool any_dropped = false;
+    if (hides)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) any_dropped |= xd[w] != 0;
     for (int u = tid; u < it.n_rows * (D / 4); u += 64 * NW) {
         const int rr = u / (D / 4), c = u % (D / 4);
         float mm = -INFINITY, l = 0.f;
@@ -355,6 +371,17 @@ __global__ __launch_bounds__(64 * NARROW_WAVES, 2) void attention_narrow_kernel(
             const float4 o = *(const float4 *)(lds + w * 2 * NARROW_HALF + rr * (D * 4) + 16 * (c ^ rr));
             l += xl[w * 32 + rr] * wt;
             if (wt != 0.f) { acc.x += o.x * wt; acc.y += o.y * wt; acc.z += o.z * wt; acc.w += o.w * wt; }
+        }
+        if (any_dropped) {
+            const int t_end = (it.m0 + rr) / a.g < it.kv_end - it.ctx_len - 1 ? (it.m0 + rr) / a.g : it.kv_end - it.ctx_len - 1;
+#pragma unroll 1
+            for (int j = it.kv_begin > it.ctx_len ? it.kv_begin - it.ctx_len : 0; j <= t_end; ++j) {
+                const uint2 x = *(const uint2 *)((const bf16_t *)a.v_new + ((int64_t)(it.q_off + j) * a.n_kv + it.kv_head) * D + 4 * c);
+                acc.x += nonfinite_only(x.x << 16);
+                acc.y += nonfinite_only(x.x & 0xFFFF0000u);
+                acc.z += nonfinite_only(x.y << 16);
+                acc.w += nonfinite_only(x.y & 0xFFFF0000u);
+            }
         }
         if (it.part_slot < 0) {
             const int mr = it.m0 + rr;

@@ -115,6 +115,9 @@ __device__ __forceinline__ bf16x8 drop_nonfinite(const bf16x8 &v, uint32_t &drop
     return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
+// the float of these bits if it is an infinity or a NaN, else zero
+__device__ __forceinline__ float nonfinite_only(uint32_t bits) { return (bits & 0x7F800000u) == 0x7F800000u ? __uint_as_float(bits) : 0.f; }
+
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
 // One 16-byte chunk pair of a head vector rotated by the (cos, sin) pairs in cs4 (Eq. 1): element i of

@@ -47,6 +47,9 @@ def test_bf16_head_dims_64_and_256(gpu_device, monkeypatch, d, g, ctx, n_q, page
 @pytest.mark.parametrize("dtype,d,g,ctx,n_q,paged,target", [
     ("f32", 64, 2, 40, 20, False, None), ("f32", 128, 4, 100, 33, True, "4000"), ("f32", 256, 1, 30, 70, False, None),
     ("bf16", 64, 4, 70, 40, True, None), ("bf16", 64, 7, 0, 65, False, "4000"), ("bf16", 256, 2, 100, 30, False, None),
+    # bf16, 128 columns, at most 32 packed rows: one tile of query rows, two of them, a later tile of a wave, split
+    ("bf16", 128, 4, 40, 8, True, None), ("bf16", 128, 1, 17, 32, False, None), ("bf16", 128, 1, 300, 20, True, "1"),
+    ("bf16", 128, 2, 700, 16, False, "4000"),
 ])
 def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypatch, dtype, d, g, ctx, n_q, paged, target):
     import paper_2604_13226_amd as kvp
