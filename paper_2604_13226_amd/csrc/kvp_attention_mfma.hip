@@ -31,8 +31,6 @@
 // HBM traffic: every K/V row of the range is read once per group of 128 packed rows.
 #include "kvp_mfma_device.h"
 
-#include <type_traits>
-
 namespace kvp {
 
 constexpr int BN = 64;   // kv rows per tile
@@ -143,7 +141,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     const char *k_item = (const char *)(kc + contig_off);
     const char *v_item = (const char *)(vc + contig_off);
     const int64_t paged_base = (int64_t)a.layer * a.cache.layer_stride;
-    // packets: rows of the query's own K (rotated, in a.k_tail) and V (a.v_new) for this head
+    // rows of the query's own V (a.v_new) for this head; packets: and of its K (rotated, in a.k_tail)
     const int64_t tail_off = ((int64_t)it.q_off * a.n_kv + it.kv_head) * D;
 
     // direct HBM -> LDS load of tile tj: wave w, instruction i fills tile rows
@@ -230,6 +228,35 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         const TileSrc ts = tile_src(tj);
 #pragma unroll
         for (int i = 0; i < NI; ++i) issue_part(ts, tj, i);
+    };
+    // Infinities and NaNs of V among the query rows stay out of the tiles, as zeros: times the zero probability
+    // of a row that does not see them, or of the copies that fill a ragged tile, they would be NaN.  The rows
+    // that do see them get them at the end, added to what was written.  The append looks for them while it copies
+    // V_new to the cache (a word per wave, in LDS behind the tiles); without a cache there is no such copy, and
+    // each wave looks at its part of the tiles with query rows as they land.  clean_from: the item's first
+    // tile with query rows, if there is something to look for.  (Cost, per layer: 8K context 28.2 -> 28.4 us, 2.9K
+    // rows 18.4 -> 18.5, in place 19.3 -> 19.4.  Looking at every tile as it lands cost 0.5 to 0.9 us, adding to
+    // the accumulators before they are written 0.2 to 0.4.)
+    int *const found = (int *)(lds + STAGES * STAGE_BYTES + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0));
+    int clean_from = n_tiles;
+    // this wave's part of tile tj, landed and seen by no other wave yet
+    auto clean_v = [&](int tj) {
+        char *vt = lds + (tj % STAGES) * STAGE_BYTES + TILE_BYTES + wave * (RPI * ROW_BYTES) + lane * 16;
+        uint4 v[NI];
+        ushort2_t v_max = {0, 0};
+#pragma unroll
+        for (int i = 0; i < NI; ++i) v[i] = *(const uint4 *)(vt + i * (NW * RPI * ROW_BYTES));
+#pragma unroll
+        for (int i = 0; i < NI; ++i) max_magnitude(v_max, v[i]);
+        if (!__any(v_max[0] >= 0x7F80u || v_max[1] >= 0x7F80u)) return;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            uint32_t bad = 0;
+            const bf16x8 w = drop_nonfinite(__builtin_bit_cast(bf16x8, v[i]), bad);
+            if (bad && (SRC == SRC_PACKETS || it.kv_begin + tj * BN + RPI * (NW * i + wave) + slot_row >= it.ctx_len)) *(bf16x8 *)(vt + i * (NW * RPI * ROW_BYTES)) = w;
+        }
+        if (SRC == SRC_PACKETS) found[wave] = 1;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     // this lane's query row
     const int rr = 32 * wave_r + n;
@@ -419,6 +446,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 return paged_base + ((((int64_t)b * a.n_kv + it.kv_head) << a.cache.block_shift) + slot) * D;
             };
             const int n_k = n_tail * (CH / 2), n_v = SRC == SRC_PACKETS ? 0 : n_tail * CH;
+            ushort2_t v_max = {0, 0};  // largest magnitudes of V_new, as bits
             // (loads are unconditional, from units clamped into range; only the stores are guarded)
             for (int s0 = 0; 2 * s0 * NT < n_k || 4 * s0 * NT < n_v; ++s0) {
                 if (4 * s0 * NT + tid >= n_v && 2 * s0 * NT + tid >= n_k) continue;  // (a thread without a unit: few query rows)
@@ -451,6 +479,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                     return u;
                 };
                 const KUnit k0 = k_load(0), k1 = k_load(1);
+                max_magnitude(v_max, vv0);
+                max_magnitude(v_max, vv1);
+                max_magnitude(v_max, vv2);
+                max_magnitude(v_max, vv3);
                 if (von0) *(uint4 *)(vcw + vd0) = vv0;
                 if (von1) *(uint4 *)(vcw + vd1) = vv1;
                 if (von2) *(uint4 *)(vcw + vd2) = vv2;
@@ -467,6 +499,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 k_store(k0);
                 k_store(k1);
             }
+            const bool nonfinite = __any(v_max[0] >= 0x7F80u || v_max[1] >= 0x7F80u);
+            if (lane == 0) found[wave] = nonfinite;
             wait_vmcnt<0>();   // this wave's stores have reached the L2
             // The same wait once more, in the form the compiler's own wait bookkeeping understands:
             // without it the compiler takes the loads and stores above for still outstanding when the
@@ -474,6 +508,15 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             // waits for every tile load in flight and turns a four-stage ring into a one-deep prefetch.
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), the other counters left alone
             __syncthreads();   // ... and so have every other wave's
+            if (SRC == SRC_PACKETS) {  // (each wave looks at its part of the tiles as they land)
+                const AttnTile last = load_tile_record(a.tiles, it.kv_end - 1);
+                clean_from = n_tiles > last.row0 / BN + 1 ? n_tiles - (last.row0 / BN + 1) : 0;
+            } else {
+                int any = 0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) any |= found[w];
+                if (__builtin_amdgcn_readfirstlane(any)) clean_from = it.ctx_len > it.kv_begin ? (it.ctx_len - it.kv_begin) / BN : 0;
+            }
         }
     }
 
@@ -506,11 +549,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
     const int tr_half = 8 * (lane & 1);
 
 
-    // Head dims other than 128, tiles with rows that some of the wave do not see: a zero probability times
-    // an infinity or NaN of V would be NaN, so there such elements stay out of the matrix product (as
-    // zeros) and are added at the end to the rows that see them.
-    uint32_t dropped = 0;
-
     const int n_rounds = (n_tiles + KS - 1) / KS;
     KVP_PHASE_DECL;
     for (int rd = 0; rd < n_rounds; ++rd) {
@@ -524,6 +562,11 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             else if (younger == 2) wait_vmcnt<2 * 2 * NI>();
             else if (younger == 1) wait_vmcnt<2 * NI>();
             else wait_vmcnt<0>();
+        }
+        if (KS * rd + KS > clean_from) {  // (rare)
+#pragma unroll 1
+            for (int k2 = 0; k2 < KS; ++k2)
+                if (KS * rd + k2 >= clean_from && KS * rd + k2 < n_tiles) clean_v(KS * rd + k2);
         }
         KVP_STAMP(4 + 2 * rd);
         KVP_PHASE(0);
@@ -603,7 +646,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         }
         KVP_PHASE(2);
 
-        bool masked = false;  // some of the tile's rows are invisible to some of the wave's rows (cache modes)
         // ---- online softmax; accumulator r of block kb is tile row 32 kb + 8 (r/4) + 4 h + r%4
         if (SRC == SRC_PACKETS) {
             if (td.kind != 0 || td.n_rows < BN) {  // wave-uniform: query tiles and ragged packet ends
@@ -616,7 +658,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                         if (32 * kb + 8 * (r >> 2) + 4 * h + (r & 3) >= lim) sacc[kb][r] = -INFINITY;
             }
         } else if (kv0 + BN > wave_limit || kv0 + BN > it.kv_end) {  // wave-uniform: tail tiles only
-            masked = true;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -677,57 +718,51 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 vfr[buf][2 * eb + 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(vp + 8 * ROW_BYTES + coff));
             }
         };
-        auto pv = [&](auto finite_v) {
-            constexpr bool FINITE_V = decltype(finite_v)::value;
-            read_v(0, 0);
+        read_v(0, 0);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                uint32_t pk[8], pl[8];
+        for (int kb = 0; kb < 2; ++kb) {
+            uint32_t pk[8], pl[8];
 #pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    float p0 = __builtin_amdgcn_exp2f(sacc[kb][r] * s_scale);
-                    float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1] * s_scale);
-                    if (SPLIT_P) {
-                        // Cut, not rounded, so that the rest is never negative; 2^-23 of p on top keeps it above zero
-                        // where p is (both parts times an infinity of V then agree), and only there: a masked
-                        // entry's p is zero, and so is what its row of V, however large, is multiplied by.
-                        constexpr float ABOVE = 1.f + 0x1p-23f;
-                        pk[r >> 1] = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302);
-                        const float q0 = __builtin_fmaf(p0, ABOVE, -__uint_as_float(__float_as_uint(p0) & 0xFFFF0000u));
-                        const float q1 = __builtin_fmaf(p1, ABOVE, -__uint_as_float(__float_as_uint(p1) & 0xFFFF0000u));
-                        pl[r >> 1] = pack_bf16_hw(q0, q1);
-                        rs0 += p0;
-                        rs1 += p1;
-                        continue;
-                    }
-                    pk[r >> 1] = pack_bf16_hw(p0, p1);
-                    // the row sum takes the rounded values, i.e. exactly what multiplies V
-                    const bf16x2 pp = __builtin_bit_cast(bf16x2, pk[r >> 1]);
-                    if (r & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs1, false);
-                    else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs0, false);
+            for (int r = 0; r < 16; r += 2) {
+                float p0 = __builtin_amdgcn_exp2f(sacc[kb][r] * s_scale);
+                float p1 = __builtin_amdgcn_exp2f(sacc[kb][r + 1] * s_scale);
+                if (SPLIT_P) {
+                    // Cut, not rounded, so that the rest is never negative; 2^-23 of p on top keeps it above zero
+                    // where p is (both parts times an infinity of V then agree), and only there: a masked
+                    // entry's p is zero, and so is what its row of V, however large, is multiplied by.
+                    constexpr float ABOVE = 1.f + 0x1p-23f;
+                    pk[r >> 1] = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302);
+                    const float q0 = __builtin_fmaf(p0, ABOVE, -__uint_as_float(__float_as_uint(p0) & 0xFFFF0000u));
+                    const float q1 = __builtin_fmaf(p1, ABOVE, -__uint_as_float(__float_as_uint(p1) & 0xFFFF0000u));
+                    pl[r >> 1] = pack_bf16_hw(q0, q1);
+                    rs0 += p0;
+                    rs1 += p1;
+                    continue;
                 }
+                pk[r >> 1] = pack_bf16_hw(p0, p1);
+                // the row sum takes the rounded values, i.e. exactly what multiplies V
+                const bf16x2 pp = __builtin_bit_cast(bf16x2, pk[r >> 1]);
+                if (r & 2) rs1 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs1, false);
+                else rs0 = __builtin_amdgcn_fdot2_f32_bf16(pp, bf16_ones, rs0, false);
+            }
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int step = 2 * kb + j;
-                    if (step + 1 < 4) read_v(step + 1, (step + 1) & 1);  // next k-step's V lands under these MFMAs
-                    uint4 pu = make_uint4(pk[4 * j], pk[4 * j + 1], pk[4 * j + 2], pk[4 * j + 3]);
-                    bf16x8 pf = __builtin_bit_cast(bf16x8, pu);
-                    bf16x8 pg = pf;
-                    if (SPLIT_P) pg = __builtin_bit_cast(bf16x8, make_uint4(pl[4 * j], pl[4 * j + 1], pl[4 * j + 2], pl[4 * j + 3]));
+            for (int j = 0; j < 2; ++j) {
+                const int step = 2 * kb + j;
+                if (step + 1 < 4) read_v(step + 1, (step + 1) & 1);  // next k-step's V lands under these MFMAs
+                uint4 pu = make_uint4(pk[4 * j], pk[4 * j + 1], pk[4 * j + 2], pk[4 * j + 3]);
+                bf16x8 pf = __builtin_bit_cast(bf16x8, pu);
+                bf16x8 pg = pf;
+                if (SPLIT_P) pg = __builtin_bit_cast(bf16x8, make_uint4(pl[4 * j], pl[4 * j + 1], pl[4 * j + 2], pl[4 * j + 3]));
 #pragma unroll
-                    for (int eb = 0; eb < EB; ++eb) {
-                        union { short4v s[2]; bf16x8 v; } vf;
-                        vf.s[0] = vfr[step & 1][2 * eb];
-                        vf.s[1] = vfr[step & 1][2 * eb + 1];
-                        if (FINITE_V) vf.v = drop_nonfinite(vf.v, dropped);
-                        oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, oacc[eb], 0, 0, 0);
-                        if (SPLIT_P) oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pg, oacc[eb], 0, 0, 0);
-                    }
+                for (int eb = 0; eb < EB; ++eb) {
+                    union { short4v s[2]; bf16x8 v; } vf;
+                    vf.s[0] = vfr[step & 1][2 * eb];
+                    vf.s[1] = vfr[step & 1][2 * eb + 1];
+                    oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, oacc[eb], 0, 0, 0);
+                    if (SPLIT_P) oacc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pg, oacc[eb], 0, 0, 0);
                 }
             }
-        };
-        if (SPLIT_P && masked) pv(std::true_type{});
-        else pv(std::false_type{});
+        }
         l_i += rs0 + rs1;  // this lane's half of the row; the halves are added once, at the end
         KVP_PHASE(4);
     }
@@ -779,26 +814,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             o[r + 1] = o[r + 1] * a0 + o1.y * a1;
             o[r + 2] = o[r + 2] * a0 + o1.z * a1;
             o[r + 3] = o[r + 3] * a0 + o1.w * a1;
-        }
-    }
-
-    if (SPLIT_P && __any(dropped != 0)) {
-        const int seen_end = wave_limit < it.kv_end ? wave_limit : it.kv_end;  // (the masked tiles start with the tile this row is in)
-        const int end = limit < it.kv_end ? limit : it.kv_end;
-#pragma unroll 1
-        for (int kv = it.kv_begin + (seen_end > it.kv_begin ? (seen_end - it.kv_begin) / BN * BN : 0); kv < end; ++kv) {
-            int64_t off = contig_off + (int64_t)(kv - it.kv_begin) * D;
-            if (SRC == SRC_PAGED) {
-                const int64_t b = blk_ids[(kv >> a.cache.block_shift) - blk0];
-                off = paged_base + (((b * a.n_kv + it.kv_head) << a.cache.block_shift) + (kv & ((1 << a.cache.block_shift) - 1))) * D;
-            }
-#pragma unroll
-            for (int eb = 0; eb < EB; ++eb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float x = ld_elem(vc + off + 32 * eb + 8 * (r >> 2) + 4 * h + (r & 3));
-                    oacc[eb][r] += __builtin_fabsf(x) < INFINITY ? 0.f : x;
-                }
         }
     }
 
@@ -890,6 +905,40 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         }
     }
     KVP_STAMP(31);
+
+    if (clean_from < n_tiles) {
+        // Add what the rows see of the infinities and NaNs left out to what was written (weights are
+        // positive, so an infinity needs none).
+        int j0 = it.kv_begin - it.ctx_len, j1 = it.kv_end - it.ctx_len;  // query rows in the item's range
+        if (SRC == SRC_PACKETS) {
+            const AttnTile last = load_tile_record(a.tiles, it.kv_end - 1);
+            j0 = last.row0 - (n_tiles - 1 - clean_from) * BN;
+            j1 = last.row0 + last.n_rows;
+        }
+        if (j0 < 0) j0 = 0;
+        wait_vmcnt<0>();
+        __syncthreads();  // the rows are written
+        if (SRC == SRC_PACKETS) {
+            int any = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) any |= found[w];
+            if (!__builtin_amdgcn_readfirstlane(any)) return;
+        }
+        char *pp = (char *)a.partials + (it.part_slot < 0 ? 0 : (int64_t)it.part_slot * part_slot_bytes(a.bm, D, SPLIT_P ? 0 : 1));
+#pragma unroll 1
+        for (int u = tid; u < it.n_rows * D; u += NT) {
+            const int r = u / D, e = u % D, tr = (it.m0 + r) / g;
+            float x = 0.f;
+#pragma unroll 1
+            for (int j = j0; j < j1 && j <= tr; ++j)
+                x += nonfinite_only((uint32_t)*((const bf16_t *)a.v_new + tail_off + (int64_t)j * a.n_kv * D + e) << 16);
+            if (x == 0.f) continue;
+            bf16_t *op = (bf16_t *)a.out + ((int64_t)(it.q_off + tr) * a.n_q_heads + it.kv_head * g + (it.m0 + r) % g) * D + e;
+            if (it.part_slot < 0) *op = f32_to_bf16(ld_elem(op) + x);
+            else if (SPLIT_P) *((float *)pp + (int64_t)r * D + e) += x;
+            else *((_Float16 *)pp + (int64_t)r * D + e) += (_Float16)x;
+        }
+    }
 }
 
 // (256 columns: twice the accumulators and query registers, one wave per SIMD)
@@ -924,7 +973,7 @@ template <typename K> static int launch_kernel(K kernel, bool &attr_set, int lds
 
 template <int D, int SRC, int NW, int KS, int STAGES, bool NTL, bool QUAD> static int launch_variant_nt(const AttnArgs &a, void *stream)
 {
-    constexpr int lds_bytes = STAGES * stage_bytes(D) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
+    constexpr int lds_bytes = STAGES * stage_bytes(D) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0) + NW * 4;
     static bool attr_set = false;
     return launch_kernel(attention_mfma_kernel<D, STAGES, SRC, NW, KS, NTL, QUAD>, attr_set, lds_bytes, 64 * NW, a, stream);
 }
@@ -940,7 +989,7 @@ template <int SRC, int NW, int KS, int STAGES> static int launch_variant(const A
 
 template <int SRC, bool QUAD> static int launch_mixed_as(const AttnArgs &a, void *stream)
 {
-    constexpr int lds_bytes = 4 * stage_bytes(128) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0);
+    constexpr int lds_bytes = 4 * stage_bytes(128) + (SRC == SRC_PAGED ? MAX_BLOCK_IDS * 4 : 0) + 8 * 4;
     static bool attr_set = false;
     return launch_kernel(attention_mfma_mixed_kernel<SRC, QUAD>, attr_set, lds_bytes, 512, a, stream);
 }

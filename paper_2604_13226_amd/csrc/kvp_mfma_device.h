@@ -115,6 +115,14 @@ __device__ __forceinline__ bf16x8 drop_nonfinite(const bf16x8 &v, uint32_t &drop
     return __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
+// the largest magnitudes, as bits, of the even and of the odd elements: 0x7F80 and above are infinities and NaNs
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void max_magnitude(ushort2_t &m, const uint4 &v)
+{
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(ushort2_t, w[i] & 0x7FFF7FFFu));
+}
 // the float of these bits if it is an infinity or a NaN, else zero
 __device__ __forceinline__ float nonfinite_only(uint32_t bits) { return (bits & 0x7F800000u) == 0x7F800000u ? __uint_as_float(bits) : 0.f; }
 

@@ -50,6 +50,9 @@ def test_bf16_head_dims_64_and_256(gpu_device, monkeypatch, d, g, ctx, n_q, page
     # bf16, 128 columns, at most 32 packed rows: one tile of query rows, two of them, a later tile of a wave, split
     ("bf16", 128, 4, 40, 8, True, None), ("bf16", 128, 1, 17, 32, False, None), ("bf16", 128, 1, 300, 20, True, "1"),
     ("bf16", 128, 2, 700, 16, False, "4000"),
+    # and more than 32: row blocks of 128 (query rows in one tile, in two), of 256 with a half block, split
+    ("bf16", 128, 4, 70, 40, True, None), ("bf16", 128, 1, 50, 100, False, None), ("bf16", 128, 4, 100, 90, True, None),
+    ("bf16", 128, 7, 900, 20, False, "4000"),
 ])
 def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypatch, dtype, d, g, ctx, n_q, paged, target):
     import paper_2604_13226_amd as kvp
@@ -80,6 +83,45 @@ def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypa
         hit[at:, :g, col] = True                                      # the query heads of KV head 0
         assert torch.equal(got[~hit], clean[~hit])
         assert bool((torch.isinf(got[hit]) if value == float("inf") else torch.isnan(got[hit])).all())
+
+
+@pytest.mark.parametrize("shape", ["128", "two groups", "256"])
+@pytest.mark.parametrize("ctx,n_q,target", [(0, 30, None), (200, 70, None), (700, 33, "4000")])
+def test_an_infinity_in_v_new_in_place(gpu_device, monkeypatch, ctx, n_q, target, shape):
+    """The same without a cache, over the shapes of the 128-row kernel's workgroups."""
+    import paper_2604_13226_amd as kvp
+    if target:
+        monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
+    monkeypatch.setenv("KVP_ATTN_BM", "256" if shape == "256" else "128")
+    if shape == "two groups":
+        monkeypatch.setenv("KVP_ATTN_SPLIT_IN_WG", "1")
+    g, d = 4, 128
+    w = _request("bf16", d, g, ctx, n_q)
+    store = build_store(w, kvp)
+    q_off = np.array([0, n_q], np.int32)
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, n_q, ctx + n_q))
+
+    def calls(change):  # in place, and over a cache
+        q, kn, vn = w.query(0, 0, "cuda:0")
+        change(vn)
+        reqs = [(rq.packet_ids, 0) for rq in w.requests]
+        out, out2, tail = torch.empty_like(q), torch.empty_like(q), torch.empty_like(kn)
+        kvp.kvp_prefill_packets(store, reqs, 0, q, kn, vn, q_off, tail, ws, out)
+        cache = make_cache(w, kvp, store)
+        kvp.kvp_assemble(store, reqs, cache)
+        kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, ws, out2)
+        return out.float().cpu(), out2.float().cpu()
+
+    at, col = (2 * n_q) // 3, d // 2 + 3
+    clean = calls(lambda vn: None)
+    for value in (float("-inf"), float("nan")):
+        def change(vn):
+            vn[at, 0, col] = value
+        hit = torch.zeros(clean[0].shape, dtype=torch.bool)
+        hit[at:, :g, col] = True
+        for got, want in zip(calls(change), clean):
+            assert torch.equal(got[~hit], want[~hit])
+            assert bool(((got[hit] == value) if value == value else torch.isnan(got[hit])).all())
 
 
 @pytest.mark.parametrize("d,g,ctx,n_q,paged", [
