@@ -103,8 +103,9 @@ static_assert(sizeof(AttnTile) == 32, "AttnTile is 32 bytes");
 
 // The work items of a launch for ONE request whose packed rows fit one row block are a regular
 // pattern -- kv head h, split sp, all splits the same length but the last -- in a known launch
-// order (split by split, the heads of a split next to each other).  A
-// workgroup of such a launch rebuilds its AttnItem from its index with scalar arithmetic and
+// order: split by split, the heads of a split next to each other (a multiple of eight KV heads, and
+// launches without splits), or head by head with the heads' shorter last splits, if they are shorter,
+// behind all the full ones.  A workgroup of such a launch rebuilds its AttnItem from its index with scalar arithmetic and
 // starts its query and tile loads one memory round trip earlier than one that first has to fetch
 // its item.  The host fills this only after it has rebuilt every planned item with the same
 // function and found it equal, field by field.  (A table of items in the kernel arguments was
@@ -115,13 +116,23 @@ struct AttnInline {
     int32_t split_len;           // kv rows (in-place path: tiles) per split
     int32_t vis;                 // end of the kv range the rows may see
     int32_t ns;                  // splits per head
+    int32_t n_front;             // 0: split by split; else the splits of a head that come head by head, in front
     int32_t n_rows;              // packed rows (n_q x heads per kv head)
 };
 
 __host__ __device__ inline AttnItem attn_inline_item(const AttnInline &t, int i, int n_kv, int part_stride)
 {
     AttnItem it{};
-    const int sp = i / n_kv, h = i - sp * n_kv;
+    int sp, h;
+    if (i < n_kv * t.n_front) {
+        h = i / t.n_front;
+        sp = i - h * t.n_front;
+    } else {
+        const int j = i - n_kv * t.n_front;
+        sp = j / n_kv;
+        h = j - sp * n_kv;
+        sp += t.n_front;
+    }
     it.group = h;
     it.split = sp;
     it.kv_begin = sp * t.split_len;

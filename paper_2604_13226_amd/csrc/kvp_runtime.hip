@@ -1363,16 +1363,22 @@ void fill_inline_items(const kvp_store *s, int n_req, const ReqMeta *reqs, const
     t.vis = 0;
     for (const AttnItem &it : items) t.vis = std::max(t.vis, it.kv_end);
     if ((int64_t)n_kv * t.ns != (int64_t)items.size()) return;
-    for (size_t i = 0; i < items.size(); ++i) {
-        const AttnItem &want = items[i];
-        const AttnItem got = attn_inline_item(t, (int)i, n_kv, part_stride);
-        if (got.group != want.group || got.split != want.split || got.kv_begin != want.kv_begin || got.kv_end != want.kv_end ||
-            got.req != want.req || got.kv_head != want.kv_head || got.m0 != want.m0 || got.n_rows != want.n_rows ||
-            got.ctx_len != want.ctx_len || got.q_off != want.q_off || got.part_slot != want.part_slot || got.n_q != want.n_q ||
-            got.pos0 != want.pos0 || got.half_block != want.half_block)
+    for (int n_front : {0, t.ns, t.ns - 1}) {
+        t.n_front = n_front;
+        bool same = true;
+        for (size_t i = 0; i < items.size() && same; ++i) {
+            const AttnItem &want = items[i];
+            const AttnItem got = attn_inline_item(t, (int)i, n_kv, part_stride);
+            same = got.group == want.group && got.split == want.split && got.kv_begin == want.kv_begin && got.kv_end == want.kv_end &&
+                   got.req == want.req && got.kv_head == want.kv_head && got.m0 == want.m0 && got.n_rows == want.n_rows &&
+                   got.ctx_len == want.ctx_len && got.q_off == want.q_off && got.part_slot == want.part_slot && got.n_q == want.n_q &&
+                   got.pos0 == want.pos0 && got.half_block == want.half_block;
+        }
+        if (same) {
+            t.n = (int32_t)items.size();
             return;
+        }
     }
-    t.n = (int32_t)items.size();
 }
 
 uint64_t q_rot_bytes(const kvp_store *s, int64_t tot_q)

@@ -382,6 +382,31 @@ def test_regular_one_request_plans_are_rebuilt_from_the_block_index():
     assert int(kvp.kvp_debug_last_plan(f32, 2)[0]) == 0                     # the generic kernel reads its items from memory
 
 
+@pytest.mark.parametrize("n_q_heads,n_kv_heads", [(28, 4), (16, 4), (16, 2), (7, 1), (24, 3), (32, 8), (32, 16)])
+def test_regular_one_request_plans_of_any_head_count(n_q_heads, n_kv_heads):
+    """The launch order depends on the number of KV heads (split by split for multiples of eight, else
+    head by head with the shorter last splits behind the others): both are rebuilt from the block
+    index, over a cache and in place."""
+    s = dry_store(n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, max_positions=1 << 17)
+    kvp.kvp_store_put(s, 0, None, None, n_tokens=512)
+    kvp.kvp_store_put(s, 1, None, None, n_tokens=300)
+    n_split = 0
+    for ctx, n_q in [(8192, 1), (8192, 16), (3000, 4), (0, 3), (511, 16), (100000, 7), (6144 - 16, 16)]:
+        cache = kvp.Cache.dry(1, t_cap=ctx + n_q)
+        cache.ctx_len[0] = ctx
+        kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.array([0, n_q], np.int32), None, None)
+        kind, bm, groups, items, slots, need = _attn_plan(s)
+        n_split += len(items) > n_kv_heads
+        assert int(kvp.kvp_debug_last_plan(s, 2)[0]) == len(items), (ctx, n_q)
+    for packets in [[0] * 16, [0] * 5, [0]]:
+        for n_q in (1, 16):
+            kvp.kvp_prefill_packets(s, [(packets, 0)], 0, None, None, None, np.array([0, n_q], np.int32), None, None, None)
+            p = kvp.kvp_debug_last_plan(s, 1)
+            n_split += int(p[3]) > n_kv_heads
+            assert int(kvp.kvp_debug_last_plan(s, 2)[0]) == int(p[3]), (packets, n_q)
+    assert n_split >= 8                                                      # most of them have splits to order
+
+
 def test_packets_plan_tiles_and_items():
     s = dry_store(n_q_heads=32, n_kv_heads=8)
     lens = {0: 70, 1: 1, 2: 64, 3: 129}

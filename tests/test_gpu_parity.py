@@ -1299,11 +1299,18 @@ def _with_lens(w, n):
     return w
 
 
+def _with_n_q(w, n):
+    w.requests[0].n_q = n
+    return w
+
+
 @pytest.mark.parametrize("mk", [
     lambda: W.llama_k5(n_layers=1, n_packets=8),
     lambda: W.llama_8k(n_layers=1, n_packets=16),
     lambda: W.llama_8k(n_layers=1, n_packets=16, n_q=1),
     lambda: _with_lens(W.llama_8k(n_layers=1, n_packets=16), 526),      # 8416 + 32 rows = 22 x 384: the last kv range is a full one
+    lambda: _with_n_q(W.qwen_k20(n_layers=1, n_packets=20), 16),        # four KV heads: another launch order
+    lambda: _with_n_q(W.qwen_k20(n_layers=1, n_packets=20), 1),
 ])
 def test_items_rebuilt_from_the_block_index_give_the_same_bits_as_items_read_from_memory(gpu_device, mk):
     """The workgroups of a regular one-request launch rebuild their work items from their index;
