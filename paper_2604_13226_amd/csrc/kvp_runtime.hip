@@ -1472,40 +1472,61 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     if (!s->dry) HIP_TRY(s, hipSetDevice(g.device));
     const bool in_capture = capturing(s, hip_stream);
     if (in_capture && tot_q == 0) return KVP_OK;  // nothing to launch, and no plan to touch
-    kvp_store::PrefillCached *found;
-    if (fixed) {
-        found = fixed;
+    auto look_up = [&]() -> kvp_store::PrefillCached * {
+        if (!fixed) return find_plan(s, s->pf_set, sig, hip_stream, sig_hash, hit);
         sig_hash = 0;
         hit = fixed->valid && fixed->owner == s->serial && fixed->stream == hip_stream && fixed->sig == sig;
-    } else {
-        found = find_plan(s, s->pf_set, sig, hip_stream, sig_hash, hit);
-    }
-    kvp_store::PrefillCached &pf = *found;
+        return fixed;
+    };
     // fp32 stores and head dims 64 and 256: the matrix kernels' fp32 partial rows come in blocks of 32 and
     // 128 rows, the generic kernel's in blocks of 8, so a workspace may hold the one and not the other.
     // Such a call takes the generic kernel, as it does wherever the matrix kernels cannot go.  The narrow
     // kernel cuts finer than the 128-row kernel, and steps back to that one.
     const int best_kind = call_kind(s, cache, n_req, rows.data(), q_offsets);
-    const bool may_fall_back = best_kind != ATTN_GENERIC && !part_f16_of(best_kind, g.head_dim);
-    if (hit && may_fall_back && !in_capture && !pf.captured && (pf.kind == best_kind ? workspace_bytes < pf.need : workspace_bytes >= pf.best_need)) hit = false;
+    // Both plans of a geometry may be kept (the signature's last word tells them apart): the workspace of
+    // each call decides, whichever of them a graph holds.
+    const bool may_fall_back = best_kind != ATTN_GENERIC && !part_f16_of(best_kind, g.head_dim) && !s->dry;
+    sig.push_back(0);
+    kvp_store::PrefillCached *found = look_up();
+    uint64_t best_need = 0;  // workspace of best_kind's plan, once known
+    if (may_fall_back && (!hit || workspace_bytes < found->need)) {
+        kvp_store::PrefillCached *const best = found;
+        const bool too_small = hit;
+        if (too_small) best_need = best->need;
+        sig.back() = 1;
+        found = look_up();
+        if (!too_small && !(hit && workspace_bytes < found->best_need)) {  // no plan of either, or room for best_kind's
+            sig.back() = 0;
+            found = look_up();
+        }
+    }
     if (in_capture && !hit)
         return fail(s, KVP_E_INVAL, "kvp_query_prefill under stream capture needs the plan of an earlier call with the same "
                                     "geometry on the same stream (call it once before capturing)");
+    PrefillPlan p;
+    auto plan_need = [&]() -> uint64_t {  // (the matrix kernels rotate the query in registers)
+        return (p.kind == ATTN_GENERIC ? q_rot_bytes(s, tot_q) : 0) +
+               (uint64_t)p.n_slots * (uint64_t)part_slot_bytes(p.bm, g.head_dim, part_f16_of(p.kind, g.head_dim));
+    };
+    if (!hit) {
+        if (sig.back() == 0) {
+            plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+            best_need = plan_need();
+            if (may_fall_back && workspace_bytes < best_need) {
+                sig.back() = 1;
+                found = look_up();
+            }
+        }
+        if (sig.back() == 1) {
+            p = PrefillPlan();
+            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+        }
+    }
+    kvp_store::PrefillCached &pf = *found;
     if (in_capture && !pf.captured && captured_plans(s->pf_set) >= MAX_CAPTURED_PLANS)
         return fail(s, KVP_E_CAPACITY, "%d plans of this store are already held for HIP graphs (kvp_release_captured_plans)", MAX_CAPTURED_PLANS);
 
     if (!hit) {
-        PrefillPlan p;
-        auto plan_need = [&]() -> uint64_t {  // (the matrix kernels rotate the query in registers)
-            return (p.kind == ATTN_GENERIC ? q_rot_bytes(s, tot_q) : 0) +
-                   (uint64_t)p.n_slots * (uint64_t)part_slot_bytes(p.bm, g.head_dim, part_f16_of(p.kind, g.head_dim));
-        };
-        plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, p);
-        const uint64_t best_need = plan_need();
-        if (may_fall_back && !s->dry && workspace_bytes < best_need) {
-            p = PrefillPlan();
-            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, p);
-        }
         const uint64_t need = plan_need();
         const uint64_t bytes = p.reqs.size() * sizeof(ReqMeta) + p.row_req.size() * 4 + p.groups.size() * sizeof(AttnGroup) +
                                p.items.size() * sizeof(AttnItem) + (uint64_t)n_req * bt_stride * 4 + 6 * 64;

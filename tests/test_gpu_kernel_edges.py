@@ -228,6 +228,48 @@ def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkey
         kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, kvp.alloc_workspace(256), out)
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64), ("bf16", 256)])
+@pytest.mark.parametrize("captured", ["small", "full"])
+def test_a_captured_plan_leaves_calls_with_another_workspace_alone(gpu_device, monkeypatch, dtype, d, captured):
+    """Whether a call steps back to the generic kernel follows from its own workspace, also while a graph
+    holds the plan of the other kernel for the same geometry."""
+    import paper_2604_13226_amd as kvp
+    monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", "4000")               # ranges of 64 rows with either kernel
+    w = _request(dtype, d, 2, 900, 3)
+    store = build_store(w, kvp)
+    cache = make_cache(w, kvp, store)
+    kvp.kvp_assemble(store, [(rq.packet_ids, 0) for rq in w.requests], cache)
+    q_off = np.array([0, 3], np.int32)
+    q, kn, vn = w.query(0, 0, "cuda:0")
+    ws = {"full": kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, 3, 903)),
+          "small": kvp.alloc_workspace(30 * 8 * (d + 2) * 4 + (1 << 14))}   # 15 ranges, 2 heads: the generic kernel's 30 slots, and the query
+    out = torch.empty_like(q)
+
+    def call(size):
+        kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, ws[size], out)
+
+    def result(run):
+        out.fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        return out.clone()
+
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        want = {size: result(lambda: call(size)) for size in ("full", "small")}
+        assert not torch.equal(want["full"], want["small"])            # two kernels, two orders of the sums
+        call(captured)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call(captured)
+        for _ in range(3):
+            assert torch.equal(result(graph.replay), want[captured])
+            for size in ("full", "small", "full"):
+                assert torch.equal(result(lambda: call(size)), want[size])
+    del graph
+    kvp.kvp_release_captured_plans(store)
+
+
 @pytest.mark.parametrize("g,ctx,n_q,paged,target,n_req", [
     (1, 0, 1, False, None, 1), (4, 1, 1, True, None, 2), (4, 31, 1, False, None, 1), (7, 32, 4, True, None, 3), (4, 255, 8, False, None, 1),
     (8, 257, 4, True, "4000", 1), (1, 1000, 32, False, "4000", 2), (2, 16, 16, True, None, 1), (4, 5000, 1, False, None, 1),
