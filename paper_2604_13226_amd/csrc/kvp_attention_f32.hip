@@ -54,7 +54,7 @@ __global__ __launch_bounds__(64 * F32_WAVES, 1) void attention_f32_kernel(AttnAr
     constexpr int NP = EB / VW;             // pieces per V row and lane
     static_assert(D == 64 || D == 128 || D == 256, "shape");
     extern __shared__ __attribute__((aligned(16))) float f32_lds[];
-    const AttnItem it = a.inl.n ? attn_inline_item(a.inl, blockIdx.x, a.n_kv, a.part_stride) : a.items[blockIdx.x];
+    const AttnItem it = a.items[blockIdx.x];
     if (it.n_rows <= 0) return;  // padding item of the launch order
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
