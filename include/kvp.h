@@ -309,7 +309,9 @@ const char *kvp_last_error(const kvp_store_t *store);
  * the last kvp_assemble (which == 0) or kvp_query_prefill / kvp_prefill_packets (which == 1) and
  * returns the number of words the full description has.  Layout: see kvp_plan.h in the sources.
  * which == 2: one word, the number of work items of that prefill plan that the workgroups
- * rebuild from their index (regular launches for one request), 0 if they read them from memory. */
+ * rebuild from their index (regular launches for one request), 0 if they read them from memory.
+ * which == 3: one word, the attention kernel of the last such call (from a kept plan or a new one): 0
+ * generic, 1 bf16 matrix kernel, 2 fp32 matrix kernel, 3 bf16 narrow kernel (at most 32 packed rows). */
 int64_t kvp_debug_last_plan(const kvp_store_t *store, int32_t which, int64_t *out,
                             int64_t cap);
 

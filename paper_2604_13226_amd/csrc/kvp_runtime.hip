@@ -220,13 +220,16 @@ struct kvp_store {
     bool dbg_layered = false;
     // the last prefill plan, kept as built (kvp_debug_last_plan expands it on request)
     struct DebugPlan {
-        int64_t head[6] = {0, 0, 0, 0, 0, 0};  // kind, bm, groups, items, slots, workspace bytes needed
+        // layout (1: bf16 stores of 128 columns on a matrix kernel, 2: in place, 0: others), bm, groups, items,
+        // slots, workspace bytes needed
+        int64_t head[6] = {0, 0, 0, 0, 0, 0};
         std::vector<AttnGroup> groups;
         std::vector<AttnItem> items;
         std::vector<AttnTile> tiles;
         bool has_tiles = false;
         int64_t inl_n = 0;  // items that ride in the kernel arguments (0: none)
     } dbg_plan;
+    int dbg_kernel = 0;  // ATTN_* of the last call's plan, kept or new
     bool dry = false;
     int n_cu = 256;
     int force_generic = 0;
@@ -1602,7 +1605,10 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         pf.stream = hip_stream;
         pf.inl.n = inl.n;
         if (inl.n) pf.inl = inl;
-        if (s->dry || tot_q == 0) return KVP_OK;
+        if (s->dry || tot_q == 0) {
+            s->dbg_kernel = pf.kind;
+            return KVP_OK;
+        }
         rc = upload_plan(s, slot, w.off, hip_stream);
         if (rc) return rc;
         pf.valid = true;
@@ -1612,6 +1618,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         if (workspace_bytes < pf.need)
             return fail(s, KVP_E_CAPACITY, "workspace too small: %llu < %llu", (unsigned long long)workspace_bytes, (unsigned long long)pf.need);
     }
+    s->dbg_kernel = pf.kind;
     if (s->dry || tot_q == 0) return KVP_OK;
 
     hipStream_t st = (hipStream_t)hip_stream;
@@ -1767,6 +1774,7 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
     const bool in_capture = capturing(s, hip_stream);
     if (in_capture && tot_q == 0) return KVP_OK;  // nothing to launch, and no plan to touch
     kvp_store::PrefillCached &pk = *find_plan(s, s->pk_set, sig, hip_stream, sig_hash, hit);
+    s->dbg_kernel = ATTN_MFMA;
     if (in_capture && !hit)
         return fail(s, KVP_E_INVAL, "kvp_prefill_packets under stream capture needs the plan of an earlier call with the same "
                                     "requests on the same stream (call it once before capturing)");
@@ -2054,6 +2062,8 @@ int64_t kvp_debug_last_plan(const kvp_store_t *s, int32_t which, int64_t *out, i
     }
     if (which == 2) {  // how many of the last prefill plan's items ride in the kernel arguments
         tiles.push_back(s->dbg_plan.inl_n);
+    } else if (which == 3) {
+        tiles.push_back(s->dbg_kernel);
     } else if (which != 0) {
         // the last prefill plan: head, then groups (6 numbers each), items (4 each) and, for the
         // in-place path, the tile count and the tiles (6 each)

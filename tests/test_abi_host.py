@@ -379,7 +379,7 @@ def test_regular_one_request_plans_are_rebuilt_from_the_block_index():
     cache = kvp.Cache.dry(1, t_cap=600)
     cache.ctx_len[0] = 500
     kvp.kvp_query_prefill(f32, cache, 0, None, None, None, np.array([0, 5], np.int32), None, None)
-    assert int(kvp.kvp_debug_last_plan(f32, 2)[0]) == 0                     # the generic kernel reads its items from memory
+    assert int(kvp.kvp_debug_last_plan(f32, 2)[0]) == 0                     # fp32 stores: the items are read from memory
 
 
 @pytest.mark.parametrize("n_q_heads,n_kv_heads", [(28, 4), (16, 4), (16, 2), (7, 1), (24, 3), (32, 8), (32, 16)])
@@ -405,6 +405,36 @@ def test_regular_one_request_plans_of_any_head_count(n_q_heads, n_kv_heads):
             n_split += int(p[3]) > n_kv_heads
             assert int(kvp.kvp_debug_last_plan(s, 2)[0]) == int(p[3]), (packets, n_q)
     assert n_split >= 8                                                      # most of them have splits to order
+
+
+GENERIC, MFMA, F32, NARROW = 0, 1, 2, 3   # kvp_debug_last_plan(s, 3)
+
+
+@pytest.mark.parametrize("dtype,head_dim,block_size,ctx,n_q,kernel", [
+    ("f32", 64, 0, [100], [5], F32), ("f32", 128, 0, [100], [5], F32), ("f32", 256, 16, [100], [5], F32),
+    ("f32", 96, 0, [100], [5], GENERIC), ("f32", 128, 8, [100], [5], GENERIC),
+    ("bf16", 64, 0, [100], [5], MFMA), ("bf16", 256, 16, [100], [1], MFMA), ("bf16", 32, 0, [100], [5], GENERIC),
+    ("bf16", 64, 8, [100], [5], GENERIC), ("bf16", 192, 0, [100], [5], GENERIC),
+    ("bf16", 128, 0, [100], [8], NARROW), ("bf16", 128, 16, [8192], [8], NARROW), ("bf16", 128, 0, [8192], [9], MFMA),
+    ("bf16", 128, 8, [100], [8], GENERIC), ("bf16", 128, 0, [100, 50], [8, 9], MFMA), ("bf16", 128, 0, [100, 50], [8, 0], NARROW),
+    ("bf16", 128, 0, [16 * 64 * 128 - 1], [1], MFMA), ("bf16", 128, 0, [16 * 64 * 128 - 65], [1], NARROW),   # 16 tiles per CU, one less
+])
+def test_the_kernel_a_call_takes(dtype, head_dim, block_size, ctx, n_q, kernel):
+    """The rule of the dispatch, either side of each of its lines: 8 / 2 heads, so 8 query rows are 32
+    packed rows."""
+    s = dry_store(dtype=dtype, head_dim=head_dim, max_positions=1 << 18)
+    n_req, rows = len(ctx), max(c + q for c, q in zip(ctx, n_q))
+    if block_size:
+        per = -(-rows // block_size)
+        table = np.arange(n_req * per, dtype=np.int32).reshape(n_req, per)
+        cache = kvp.Cache.dry(n_req, layout=kvp.KVP_PAGED, n_blocks=n_req * per, block_table=table, block_size=block_size)
+    else:
+        cache = kvp.Cache.dry(n_req, t_cap=rows)
+    cache.ctx_len[:n_req] = ctx
+    q_off = np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32)
+    for _ in range(2):                                                       # a new plan, and the kept one
+        kvp.kvp_query_prefill(s, cache, 0, None, None, None, q_off, None, None)
+        assert int(kvp.kvp_debug_last_plan(s, 3)[0]) == kernel
 
 
 def test_packets_plan_tiles_and_items():

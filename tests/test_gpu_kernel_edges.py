@@ -10,6 +10,17 @@ from tests.test_gpu_parity import compare
 
 pytestmark = pytest.mark.gpu
 
+GENERIC, MFMA, F32, NARROW = 0, 1, 2, 3   # kvp_debug_last_plan(store, 3)
+_run_workload, LAST = run_workload, {}
+
+
+def run_workload(w):
+    """The harness's, and keeps which kernel its last call took."""
+    import paper_2604_13226_amd as kvp
+    got = _run_workload(w)
+    LAST["kernel"] = int(kvp.kvp_debug_last_plan(got["store"], 3)[0])
+    return got
+
 
 def _request(dtype, d, g, ctx, n_q, n_kv=2, paged=False, seed=5, n_req=1):
     w = W.random_small(seed, dtype=dtype, d=d, n_q_heads=n_kv * g, n_kv_heads=n_kv, n_layers=1, n_packets=2, k=0, n_q=n_q, n_req=n_req)
@@ -30,6 +41,7 @@ def test_fp32_matrix_kernel(gpu_device, monkeypatch, d, g, ctx, n_q, paged, targ
         monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)  # ranges of 64 rows: waves without a tile, many partial rows
     w = _request("f32", d, g, ctx, n_q, paged=paged)
     compare(w, run_workload(w), oracle_workload(w))
+    assert LAST["kernel"] == F32
 
 
 @pytest.mark.parametrize("d,g,ctx,n_q,paged,target", [
@@ -42,6 +54,7 @@ def test_bf16_head_dims_64_and_256(gpu_device, monkeypatch, d, g, ctx, n_q, page
         monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
     w = _request("bf16", d, g, ctx, n_q, paged=paged, n_req=2)
     compare(w, run_workload(w), oracle_workload(w))
+    assert LAST["kernel"] == MFMA
 
 
 @pytest.mark.parametrize("dtype,d,g,ctx,n_q,paged,target", [
@@ -74,6 +87,8 @@ def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypa
 
     at, col = (2 * n_q) // 3, d // 2 + 3
     clean = call(lambda vn: None)
+    kernel = F32 if dtype == "f32" else NARROW if d == 128 and n_q * g <= 32 else MFMA
+    assert int(kvp.kvp_debug_last_plan(store, 3)[0]) == kernel
     for value in (float("inf"), float("nan")):
         def change(vn):
             vn[at, 0, col] = value
@@ -214,6 +229,7 @@ def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkey
     q_off = np.array([0, 3], np.int32)
     full = kvp.kvp_prefill_workspace_bytes(store, 1, 3, 903)
     outs = []
+    kernels = []
     for size in (full, 30 * 8 * (d + 2) * 4 + (1 << 14), full):    # 15 ranges, 2 heads: 30 slots of 8 rows, and the query
         cache = make_cache(w, kvp, store)
         kvp.kvp_assemble(store, [(rq.packet_ids, 0) for rq in w.requests], cache)
@@ -221,6 +237,9 @@ def test_a_workspace_that_holds_only_the_generic_kernels_rows(gpu_device, monkey
         out = torch.full_like(q, float("nan"))
         kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, q_off, kvp.alloc_workspace(size), out)
         outs.append(out.float().cpu())
+        kernels.append(int(kvp.kvp_debug_last_plan(store, 3)[0]))
+    best = F32 if dtype == "f32" else MFMA
+    assert kernels == [best, GENERIC, best]
     assert torch.equal(outs[0], outs[2])
     # one computation in two orders: the tolerance of the parity tests
     assert float((outs[0] - outs[1]).abs().max()) <= (1e-5 if dtype == "f32" else 2e-2)
@@ -282,3 +301,4 @@ def test_bf16_requests_of_few_packed_rows(gpu_device, monkeypatch, g, ctx, n_q, 
         monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", target)
     w = _request("bf16", 128, g, ctx, n_q, paged=paged, n_req=n_req)
     compare(w, run_workload(w), oracle_workload(w))
+    assert LAST["kernel"] == NARROW
