@@ -27,6 +27,8 @@
 // Measured (2.9K rows of context, 32 query rows, 32 / 8 heads of 128 columns): 27 us per layer, of which
 // the three tiles of a wave are 12; one wave per row with fp32 vector arithmetic and a lane
 // reduction per score took 1062.  Error against float64 there: 2.0e-7 of the result, 7.0e-7 before.
+// 256 columns spill 34 to 36 registers (140 to 148 bytes of scratch per lane) and take 52 us per layer over
+// the same rows with 16 / 4 heads, 873 before.
 #include "kvp_device.h"
 
 #include <type_traits>

@@ -238,7 +238,7 @@ struct kvp_store {
     int asm_nontemporal = -1;  // -1: non-temporal gather decided per call
     int asm_split_kv = 1;  // the gather's workgroups move either the K or the V rows of a tile (KVP_ASM_SPLIT_KV=0: both)
     int dbg_tile_rows = 32;  // tile rows of the last gather plan
-    int nt_loads = -1;  // test knob (KVP_ATTN_NT_LOADS=0/1): streaming hint on the attention kernel's tile loads
+    int nt_loads = -1;  // test knob (KVP_ATTN_NT_LOADS=0/1): streaming hint on the 128-row kernel's tile loads (128 columns)
     int mixed_blocks = 1;  // test knob (KVP_ATTN_MIXED=0): no half blocks in launches of 256-row blocks
     int plan_copy_engine = 0;  // test knob: plans go up with hipMemcpyAsync instead of the upload kernel
     int inline_items = 1;  // test knob (KVP_ATTN_INLINE_ITEMS=0): work items are always read from memory
@@ -1024,10 +1024,15 @@ void assign_part_slots(std::vector<AttnGroup> &groups, std::vector<AttnItem> &it
 // Cohorts go out longest first (kv rows x query rows of their largest member): workgroups
 // start in index order as compute units fall free, so the long items of a ragged batch start
 // early and the short ones fill the end of the launch.  With a multiple of eight KV heads, cohorts of
-// equal work go out split by split: head h then stays on XCD h % 8, where the combine's workgroups of that
-// head run too and find its partial rows in the L2 (per layer: 2.9K rows 20.0 -> 19.1 us, one token at 8K
-// 13.9 -> 13.5, in place 21.6 -> 21.2, pruned 26.2 -> 25.5).  Four heads have two XCDs each, whatever the
-// order, and measured 2 % slower split by split.
+// equal work go out split by split: head h then stays on XCD h % 8.  The combine's workgroup of group g runs
+// on XCD g % 8, so with one row block per head it runs where the head's partial rows were written (per
+// layer: 2.9K rows 20.0 -> 19.1 us, one token at 8K 13.9 -> 13.5, in place 21.6 -> 21.2, pruned 26.2 ->
+// 25.5).  With several row blocks per head, the 32-row blocks of the fp32 kernel included, a group's
+// number is not its head's, and most groups are merged on another XCD (100 query rows at 8K: 24 of 192 items
+// are on their group's).  Four heads measured 2 % slower split by split, their combine left as it is: of
+// 176 items of two row blocks each 22 are on the XCD of their group's merge.  (That the gain comes from the
+// L2 is an inference: FETCH_SIZE of the combine reads the same either way, under counters that run the
+// kernels one by one.)
 bool xcd_order(std::vector<AttnItem> &items, int n_kv)  // returns whether any two items share their K/V rows
 {
     constexpr int XCDS = 8;
@@ -1184,11 +1189,11 @@ bool streams_many_tiles(const kvp_store *s, int64_t tiles, int bm)
 
 // Whether a call's tile loads carry the streaming hint, provided that no two work items read the same
 // rows: long launches, and calls whose rows over all layers of the store (a forward pass reads every
-// layer's once) would not stay in the 256 MB last-level cache anyway.  There the rows only push the
-// partial results out of the L2s (per layer, without and with the hint: 8K context over 32 layers 29.4
+// layer's once) would not stay in the 256 MB last-level cache anyway.  There the rows would only push
+// other lines out of the caches (per layer, without and with the hint: 8K context over 32 layers 29.4
 // and 28.0 us, in place 21.2 and 19.4, 2.9K rows 19.0 and 18.4; over 8 layers of 8K, 270 MB, 30.1 and
 // 28.6).  Rows that do stay are better kept (2.9K rows over 8 layers, 95 MB: 16.9 and 17.2; one layer of
-// four in-place requests of 8K, 135 MB: 39.3 and 42).
+// four in-place requests of 8K, 135 MB: 39.3 and 42).  The narrow kernel has no variant without the hint.
 bool streams_rows(const kvp_store *s, int64_t rows, int64_t tiles)
 {
     const kvp_config_t &g = s->cfg;
