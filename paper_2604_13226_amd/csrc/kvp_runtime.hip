@@ -1413,24 +1413,27 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
         const ReqMeta &rq = p.reqs[r];
         if (rq.n_q == 0) continue;
         const int total = rq.ctx_len + rq.n_q;
-        auto range_len = [&](int rows) {
-            int len = (rows + want - 1) / want;
-            if (n_req > 1 && !sh.even && s->target_items == 0) len = (int)std::max<int64_t>(batch.tiles * 64, (rows + batch.max_ranges - 1) / batch.max_ranges);
+        auto range_len = [&](int rows, int most) {  // most: ranges at most
+            int n = std::min(want, most), len = (rows + n - 1) / n;
+            if (n_req > 1 && !sh.even && s->target_items == 0) {
+                n = std::min(batch.max_ranges, most);
+                len = (int)std::max<int64_t>(batch.tiles * 64, (rows + n - 1) / n);
+            }
             len = std::max(len, min_split);
             len = (len + p.bn - 1) / p.bn * p.bn;
             return std::min(len, max_split);
         };
-        int split_len = range_len(total);
+        int split_len = range_len(total, MAX_SPLITS);
         // The range with the query rows begins its first tile 2.05 us behind the others (it rotates K_new, stores
         // it and waits for the stores), about two tiles: where that would make it the launch's last to end, the query rows,
         // from a multiple of sixteen rows on (a paged block's boundary), become a short range of their own.
         // (Per layer, with and without: 3.4K rows 16.6 and 17.4 us, 8K 26.2 and 26.4, pruned to 5.7K 22.9 and
-        // 23.2, 12K 35.4 and 36.8.)
+        // 23.2, 12K 35.4 and 36.8.)  It is one of the MAX_SPLITS that the merge takes.
         int tail_begin = 0;  // 0: the last range is what is left, like the others
         const int last_len = total - (total - 1) / split_len * split_len;
         if (sh.own_tail && total > split_len && last_len + 128 > split_len && rq.n_q + 16 <= split_len) {
             tail_begin = rq.ctx_len / 16 * 16;
-            if (tail_begin > 0) split_len = range_len(tail_begin);
+            if (tail_begin > 0) split_len = range_len(tail_begin, MAX_SPLITS - 1);
         }
         if (r == 0) p.split_len0 = split_len;
         const int M = rq.n_q * gq;
@@ -1678,6 +1681,8 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
 
     if (!hit) {
         const uint64_t need = plan_need();
+        if (p.part_stride > MAX_SPLITS)  // (paged contexts past two million rows: see max_split)
+            return fail(s, KVP_E_CAPACITY, "a request needs %d kv ranges, the merge takes %d", p.part_stride, MAX_SPLITS);
         const uint64_t bytes = p.reqs.size() * sizeof(ReqMeta) + p.row_req.size() * 4 + p.groups.size() * sizeof(AttnGroup) +
                                p.items.size() * sizeof(AttnItem) + (uint64_t)n_req * bt_stride * 4 + 6 * 64;
         // every check comes before the entry is touched: a call that fails has changed nothing

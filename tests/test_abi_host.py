@@ -706,3 +706,23 @@ def test_a_ragged_batch_has_ranges_of_one_length(head_dim, dtype, ctx, n_q):
             lengths.setdefault(int(g_), {})[int(sp)] = int(e - b)
     full = {n for r in lengths.values() for sp, n in r.items() if sp + 2 < len(r)}   # (but for a request's last two)
     assert len(full) == 1 and max(n for r in lengths.values() for n in r.values()) <= max(full)
+
+
+@pytest.mark.parametrize("n_q_heads,n_kv_heads,n_req", [(8, 1, 1), (16, 2, 1), (12, 2, 1), (24, 3, 1), (8, 1, 2), (8, 1, 3)])
+def test_no_row_has_more_ranges_than_the_merge_takes(n_q_heads, n_kv_heads, n_req):
+    """Few row blocks are cut as finely as the merge allows, 64 ranges: the query rows' own range is one of them.
+    Contexts just below a multiple of 64 full ranges, where it came on top, and any others."""
+    s = dry_store(n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, max_positions=1 << 18)
+    most = 0
+    for ctx in [12152, 12160, 12270, 12272, 16368] + list(range(8000, 131000, 487)) + list(range(4096 * 5 - 130, 131000, 4096)):
+        for n_q in (10, 16):
+            cache = kvp.Cache.dry(n_req, t_cap=ctx + n_q)
+            cache.ctx_len[:n_req] = [ctx] + [100] * (n_req - 1)
+            kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.arange(n_req + 1, dtype=np.int32) * n_q, None, None)
+            kind, bm, groups, items, slots, need = _attn_plan(s)
+            ranges = sorted((int(b), int(e)) for g_, sp, b, e in items if g_ == 0)
+            assert len(ranges) == groups[0][5] <= 64, (ctx, n_q)
+            assert ranges[0][0] == 0 and ranges[-1][1] == ctx + n_q and all(e0 == b1 for (_, e0), (b1, _) in zip(ranges, ranges[1:]))
+            assert kvp.kvp_prefill_workspace_bytes(s, n_req, n_req * n_q, ctx + n_q) >= need
+            most = max(most, len(ranges))
+    assert most == 64

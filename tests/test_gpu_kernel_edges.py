@@ -330,6 +330,17 @@ def test_query_rows_as_a_range_of_their_own(gpu_device, ctx, n_q, paged):
     assert LAST["kernel"] == MFMA
 
 
+@pytest.mark.parametrize("g,n_kv,ctx,n_q,ranges", [(8, 1, 16100, 16, 64), (8, 1, 16368, 16, 53), (6, 2, 12152, 10, 49)])
+def test_query_rows_as_the_last_of_64_ranges(gpu_device, g, n_kv, ctx, n_q, ranges):
+    """As many ranges as the merge takes, the query rows' own among them; contexts where that one came on top."""
+    import paper_2604_13226_amd as kvp
+    w = _request("bf16", 128, g, ctx, n_q, n_kv=n_kv)
+    got = run_workload(w)
+    p = kvp.kvp_debug_last_plan(got["store"], 1)
+    assert LAST["kernel"] == MFMA and int(p[6 + 5]) == ranges
+    compare(w, got, oracle_workload(w))
+
+
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("what", ["key", "small", "smallest"])
 def test_fp32_numbers_that_bf16_parts_do_not_hold(gpu_device, d, what):
