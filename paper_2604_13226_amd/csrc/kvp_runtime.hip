@@ -2001,9 +2001,12 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
             // query and drains the tile prefetch (16 packets of 8 tiles at 8K: items of 6 tiles 24.3 us
             // per layer, of 4 tiles 23.0).  Items of several packets keep their boundaries whatever
             // their length, and rounding those to whole packets only unbalances them (measured: 8
-            // requests of 32 packets, 32 query rows, +4 %).
+            // requests of 32 packets, 32 query rows, +4 %).  But no more of them than the merge takes, and no more partial
+            // rows than kvp_prefill_workspace_bytes has room for (512 of 256 packed rows): a packet of 15 tiles would turn
+            // items of 14 into items of 5.
             if (const int P = pkt_tiles[r]; P > 0 && n_req == 1 && per_item < P) {
-                for (int dv = per_item; dv >= 4; --dv)
+                const int64_t most = std::min<int64_t>(MAX_SPLITS, (int64_t)2 * s->n_cu * (2 * MFMA_BM) / (bm * blocks.n));
+                for (int dv = per_item; dv >= 4 && (n_t + dv - 1) / dv <= most; --dv)
                     if (P % dv == 0) { per_item = dv; break; }
             }
             if (r == 0) per_item0 = per_item;
@@ -2060,6 +2063,8 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
         if (n_req == 1 && metas[0].n_q > 0) {
             fill_inline_items(s, n_req, metas.data(), groups, items, bm, part_stride, per_item0, gq, inl);
         }
+        if (part_stride > MAX_SPLITS)
+            return fail(s, KVP_E_CAPACITY, "a request needs %d kv ranges, the merge takes %d", part_stride, MAX_SPLITS);
         const uint64_t need = (uint64_t)n_slots * (uint64_t)part_slot_bytes(bm, g.head_dim, 1);
         const uint64_t bytes = metas.size() * sizeof(ReqMeta) + groups.size() * sizeof(AttnGroup) +
                                items.size() * sizeof(AttnItem) + tiles.size() * sizeof(AttnTile) + 6 * 64;

@@ -726,3 +726,27 @@ def test_no_row_has_more_ranges_than_the_merge_takes(n_q_heads, n_kv_heads, n_re
             assert kvp.kvp_prefill_workspace_bytes(s, n_req, n_req * n_q, ctx + n_q) >= need
             most = max(most, len(ranges))
     assert most == 64
+
+
+@pytest.mark.parametrize("n_q_heads,n_kv_heads", [(32, 8), (28, 4), (16, 2), (8, 1), (64, 16), (32, 32)])
+def test_in_place_items_that_divide_a_packet_are_not_too_many(n_q_heads, n_kv_heads):
+    """Items are shortened to a divisor of the packets' tiles, but to no more of them than the merge takes and a workspace of
+    the stated size holds."""
+    divided = 0
+    for per in list(range(4, 24)) + [25, 35, 49, 77, 121]:
+        s = dry_store(n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, max_positions=1 << 18, arena_bytes=1 << 40)
+        for k in range(44):
+            kvp.kvp_store_put(s, k, None, None, n_tokens=64 * per)
+        for n in range(1, 45):
+            for n_q in (32, 200):
+                if 64 * per * n > 150000:
+                    continue
+                kvp.kvp_prefill_packets(s, [(list(range(n)), 0)], 0, None, None, None, np.array([0, n_q], np.int32), None, None, None)
+                p = kvp.kvp_debug_last_plan(s, 1)
+                ng, ni = int(p[2]), int(p[3])
+                groups, items = p[6:6 + 6 * ng].reshape(ng, 6), p[6 + 6 * ng:6 + 6 * ng + 4 * ni].reshape(ni, 4)
+                assert groups[:, 5].max() <= 64, (per, n, n_q)
+                assert kvp.kvp_prefill_workspace_bytes(s, 1, n_q, 64 * per * n + n_q) >= p[5], (per, n, n_q)
+                length = int((items[:, 3] - items[:, 2]).max())
+                divided += length < per and per % length == 0
+    assert divided > 100
