@@ -1408,7 +1408,16 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
         if (s->target_items > 0 || !mfma) target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s);
         want = (int)std::min<int64_t>(MAX_SPLITS, (target + blocks.n - 1) / blocks.n);
     }
-    const BatchRanges batch = batch_ranges(s, blocks, want, mfma && g.head_dim == 128 && (p.bm == 2 * MFMA_BM || p.split_in_wg), target);
+    BatchRanges batch = batch_ranges(s, blocks, want, mfma && g.head_dim == 128 && (p.bm == 2 * MFMA_BM || p.split_in_wg), target);
+    // At 256 columns a partial slot of the bf16 kernel is 129 KB: no more ranges than the static scratch has slots for, or than
+    // three quarters of the CU count gives.  (Without it four requests of 2K to 4K rows of 16 / 8 heads wanted 36 MB, and
+    // kvp_query_prefill_static stepped back to the generic kernel, which takes a hundred times as long.)
+    if (mfma && g.head_dim == 256 && s->target_items == 0) {
+        const int64_t room = (int64_t)kvp_static_workspace_bytes() / (part_slot_bytes(p.bm, g.head_dim, 0) * blocks.n);
+        const int most = (int)std::max<int64_t>(room, (target_items(s) + blocks.n - 1) / blocks.n);
+        want = std::min(want, most);
+        batch.max_ranges = std::min(batch.max_ranges, most);
+    }
     for (int r = 0; r < n_req; ++r) {
         const ReqMeta &rq = p.reqs[r];
         if (rq.n_q == 0) continue;

@@ -113,3 +113,21 @@ def test_sizes_beyond_the_scratch_are_rejected(gpu_device):
     torch.cuda.synchronize()
     assert not bool((out == 5.0).all())
     kvp.kvp_store_destroy(store)
+
+
+def test_a_batch_of_256_columns_takes_the_matrix_kernel(gpu_device):
+    """The ragged batch's ranges are as many as the scratch has room for."""
+    import paper_2604_13226_amd as kvp
+    dev = "cuda:0"
+    w = W.random_small(41, dtype="bf16", d=256, n_q_heads=16, n_kv_heads=8, n_layers=1, n_packets=4, k=0, n_q=32, n_req=4)
+    w.packet_lens[:] = [2000, 3000, 2500, 4000]
+    for i, rq in enumerate(w.requests):
+        rq.packet_ids = [i]
+    store = build_store(w, kvp, dev)
+    o_ref, o_new, _, _, lost = _run_both(w, kvp, store, dev)
+    assert int(kvp.kvp_debug_last_plan(store, 3)[0]) == 1 and lost == 0
+    assert torch.equal(o_new.view(torch.uint8), o_ref.view(torch.uint8))
+    ref = oracle_workload(w, layers=[0], requests=[0])
+    got = o_new[:w.requests[0].n_q].float().cpu().numpy().astype(np.float64)
+    assert float(np.max(np.abs(got - ref["out"][0][0]))) <= TOL["bf16"]
+    kvp.kvp_store_destroy(store)
