@@ -274,10 +274,9 @@ int kvp_prefill_packets(kvp_store_t *store, const kvp_request_t *reqs, int32_t n
  * plan; a call that needs more of either returns KVP_E_CAPACITY and launches nothing (the
  * metric's 8K-context request needs 5.7 MiB, eight 16.9K-context requests of 128 query rows
  * together 16.5 MiB; the split counts the planner chooses by itself keep a call's partial rows
- * within the 31 MiB at head_dim 64 and 128, so only calls cut finer through a tuning knob exceed them;
- * at 256 in bf16 a partial row block is 129 KB, and a batch of 62, 83 to 95 or 124 to 191 row blocks of
- * 128 packed rows may need more and takes the generic kernel; other head dims keep their rotated
- * query there too).  Arguments,
+ * within the 31 MiB -- at head_dim 256 in bf16, where kvp_query_prefill may want up to 65 MiB for a
+ * batch, by cutting it into fewer ranges -- so only calls cut finer through a tuning knob and long
+ * rotated queries of the generic kernel exceed them).  Arguments,
  * results and other errors as kvp_query_prefill, without `workspace`.
  * All calls on one GPU share that GPU's array, whichever store or stream they come from, and the
  * array keeps the last call's contents: calls are correct one after the other in stream order

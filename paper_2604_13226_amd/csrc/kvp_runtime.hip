@@ -1367,7 +1367,7 @@ int call_kind(const kvp_store *s, const kvp_cache_t *c, int n_req, const int32_t
 int part_f16_of(int kind, int d) { return kind == ATTN_MFMA && d == 128 ? 1 : 0; }
 
 void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
-                  PrefillPlan &p)
+                  uint64_t room, PrefillPlan &p)
 {
     const kvp_config_t &g = s->cfg;
     const int gq = g.n_q_heads / g.n_kv_heads;
@@ -1408,41 +1408,35 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
         if (s->target_items > 0 || !mfma) target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s);
         want = (int)std::min<int64_t>(MAX_SPLITS, (target + blocks.n - 1) / blocks.n);
     }
-    BatchRanges batch = batch_ranges(s, blocks, want, mfma && g.head_dim == 128 && (p.bm == 2 * MFMA_BM || p.split_in_wg), target);
-    // At 256 columns a partial slot of the bf16 kernel is 129 KB: no more ranges than the static scratch has slots for, or than
-    // three quarters of the CU count gives.  (Without it four requests of 2K to 4K rows of 16 / 8 heads wanted 36 MB, and
-    // kvp_query_prefill_static stepped back to the generic kernel, which takes a hundred times as long.)
-    if (mfma && g.head_dim == 256 && s->target_items == 0) {
-        const int64_t room = (int64_t)kvp_static_workspace_bytes() / (part_slot_bytes(p.bm, g.head_dim, 0) * blocks.n);
-        const int most = (int)std::max<int64_t>(room, (target_items(s) + blocks.n - 1) / blocks.n);
-        want = std::min(want, most);
-        batch.max_ranges = std::min(batch.max_ranges, most);
-    }
+    const BatchRanges batch = batch_ranges(s, blocks, want, mfma && g.head_dim == 128 && (p.bm == 2 * MFMA_BM || p.split_in_wg), target);
+    int most = MAX_SPLITS;  // ranges of a row block, at most: what the merge takes, and what `room` has slots for
+    if (s->target_items == 0)
+        most = (int)std::min<uint64_t>(most, std::max<uint64_t>(1, room / (uint64_t)(part_slot_bytes(p.bm, g.head_dim, part_f16_of(kind, g.head_dim)) * blocks.n)));
     for (int r = 0; r < n_req; ++r) {
         const ReqMeta &rq = p.reqs[r];
         if (rq.n_q == 0) continue;
         const int total = rq.ctx_len + rq.n_q;
-        auto range_len = [&](int rows, int most) {  // most: ranges at most
-            int n = std::min(want, most), len = (rows + n - 1) / n;
+        auto range_len = [&](int rows, int limit) {  // limit: ranges at most
+            int n = std::min(want, limit), len = (rows + n - 1) / n;
             if (n_req > 1 && !sh.even && s->target_items == 0) {
-                n = std::min(batch.max_ranges, most);
+                n = std::min(batch.max_ranges, limit);
                 len = (int)std::max<int64_t>(batch.tiles * 64, (rows + n - 1) / n);
             }
             len = std::max(len, min_split);
             len = (len + p.bn - 1) / p.bn * p.bn;
             return std::min(len, max_split);
         };
-        int split_len = range_len(total, MAX_SPLITS);
+        int split_len = range_len(total, most);
         // The range with the query rows begins its first tile 2.05 us behind the others (it rotates K_new, stores
         // it and waits for the stores), about two tiles: where that would make it the launch's last to end, the query rows,
         // from a multiple of sixteen rows on (a paged block's boundary), become a short range of their own.
         // (Per layer, with and without: 3.4K rows 16.6 and 17.4 us, 8K 26.2 and 26.4, pruned to 5.7K 22.9 and
-        // 23.2, 12K 35.4 and 36.8.)  It is one of the MAX_SPLITS that the merge takes.
+        // 23.2, 12K 35.4 and 36.8.)  It is one of the `most` ranges.
         int tail_begin = 0;  // 0: the last range is what is left, like the others
         const int last_len = total - (total - 1) / split_len * split_len;
         if (sh.own_tail && total > split_len && last_len + 128 > split_len && rq.n_q + 16 <= split_len) {
             tail_begin = rq.ctx_len / 16 * 16;
-            if (tail_begin > 0) split_len = range_len(tail_begin, MAX_SPLITS - 1);
+            if (tail_begin > 0) split_len = range_len(tail_begin, most - 1);
         }
         if (r == 0) p.split_len0 = split_len;
         const int M = rq.n_q * gq;
@@ -1672,8 +1666,16 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     };
     if (!hit) {
         if (sig.back() == 0) {
-            plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+            plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, UINT64_MAX, p);
             best_need = plan_need();
+            // The static scratch cannot grow: there a launch that wants more is cut into what fits.  (256 columns of bf16,
+            // where a partial slot is 129 KB: four requests of 8K to 0.5K rows of 32 / 8 heads want 65 MB and take 44 us in a
+            // workspace, 72 in the scratch's 31; the generic kernel takes a hundred times as long.)
+            if (fixed && workspace_bytes < best_need && p.kind != ATTN_GENERIC) {
+                p = PrefillPlan();
+                plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, workspace_bytes, p);
+                best_need = plan_need();
+            }
             if (may_fall_back && workspace_bytes < best_need) {
                 sig.back() = 1;
                 found = look_up();
@@ -1681,7 +1683,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         }
         if (sig.back() == 1) {
             p = PrefillPlan();
-            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, p);
+            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, UINT64_MAX, p);
         }
     }
     kvp_store::PrefillCached &pf = *found;

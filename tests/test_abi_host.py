@@ -754,9 +754,9 @@ def test_in_place_items_that_divide_a_packet_are_not_too_many(n_q_heads, n_kv_he
 
 @pytest.mark.parametrize("dtype,head_dim", [("bf16", 64), ("bf16", 128), ("bf16", 256), ("f32", 64), ("f32", 128), ("f32", 256)])
 @pytest.mark.parametrize("n_q_heads,n_kv_heads", [(32, 8), (16, 8), (28, 4), (8, 1)])
-def test_the_partial_rows_of_a_batch_fit_the_static_scratch(dtype, head_dim, n_q_heads, n_kv_heads):
-    """... as far as they did when every request was cut for three quarters of the compute units: only 256 columns have rows
-    that long, and only with more row blocks than that leaves room for two ranges each."""
+def test_the_partial_rows_of_a_batch_fit(dtype, head_dim, n_q_heads, n_kv_heads):
+    """... a workspace of the stated size, and the static scratch but for 256 columns of bf16 (for which
+    kvp_query_prefill_static cuts fewer ranges)."""
     s = dry_store(n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, head_dim=head_dim, dtype=dtype, max_positions=1 << 17)
     rng = np.random.default_rng(11)
     batches = [([2000, 3000, 2500, 4000], [32] * 4), ([1500, 3000, 2200, 900], [64, 32, 48, 16]), ([8000, 1000, 500, 1000], [16] * 4),
@@ -764,14 +764,16 @@ def test_the_partial_rows_of_a_batch_fit_the_static_scratch(dtype, head_dim, n_q
     for _ in range(60):
         n = int(rng.integers(1, 12))
         batches.append((rng.integers(50, 20000, size=n).tolist(), rng.integers(1, int(rng.integers(2, 200)), size=n).tolist()))
+    beyond = 0
     for ctx, n_q in batches:
         n = len(ctx)
         cache = kvp.Cache.dry(n, t_cap=max(ctx) + 256)
         cache.ctx_len[:n] = ctx
-        kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32), None, None)
+        q_off = np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32)
+        kvp.kvp_query_prefill(s, cache, 0, None, None, None, q_off, None, None)
         kind, bm, groups, items, slots, need = _attn_plan(s)
-        blocks = sum(-(-q * (n_q_heads // n_kv_heads) // bm) for q in n_q) * n_kv_heads
-        ranges = -(-192 // blocks)                                               # three quarters of 256 compute units
-        if not (head_dim == 256 and dtype == "bf16" and ranges * blocks * bm * 258 * 4 > 31 << 20):
-            assert need <= kvp.load().kvp_static_workspace_bytes(), (ctx, n_q)
         assert groups[:, 5].max() <= 64 and need <= kvp.kvp_prefill_workspace_bytes(s, n, sum(n_q), max(ctx) + 256)
+        most = kvp.load().kvp_static_workspace_bytes()
+        assert need <= most or (head_dim, dtype) == (256, "bf16")
+        beyond += need > most
+    assert (beyond > 0) == ((head_dim, dtype) == (256, "bf16"))
