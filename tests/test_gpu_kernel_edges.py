@@ -372,6 +372,45 @@ def test_fp32_numbers_that_bf16_parts_do_not_hold(gpu_device, d, what):
     assert err <= (2.0 ** -7 if what == "smallest" else 60 * 2.0 ** -24), err
 
 
+def _one_token(d, q, k, v):
+    """fp32 attention of one token of 32 heads over rows of k and v as they are; its own row is zero.  (result, float64)"""
+    import paper_2604_13226_amd as kvp
+    n = len(k)
+    store = kvp.kvp_store_create(1, 32, 1, d, "f32", 1.0e4, n + 64, 1 << 20)
+    cache = kvp.Cache.contiguous(store, 1, n + 1)
+    cache.ctx_len[0] = n
+    cache.k[0, 0, 0, :n], cache.v[0, 0, 0, :n] = k, v
+    q, zero, out = q.float().cuda(), torch.zeros(1, 1, d, device="cuda:0"), torch.empty(1, 32, d, device="cuda:0")
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, 1, n + 1))
+    kvp.kvp_query_prefill(store, cache, 0, q[None].contiguous(), zero, zero, np.array([0, 1], np.int32), ws, out, kvp.KVP_PREROTATED)
+    assert int(kvp.kvp_debug_last_plan(store, 3)[0]) == F32
+    scores = torch.cat([q.double() @ cache.k[0, 0, 0, :n].double().T / d ** 0.5, torch.zeros(32, 1, device="cuda:0")], 1)
+    return out[0].double(), torch.softmax(scores, 1)[:, :n] @ cache.v[0, 0, 0, :n].double()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what", ["scores", "values"])
+def test_fp32_products_keep_their_small_parts(gpu_device, d, what):
+    """Numbers whose bits below the eighth are all ones, all of one sign: what a product of parts leaves out would
+    add up.  Bound: four roundings of 2^-24, of the scaled query, the score or weight, the product and the sum."""
+    a, scale = 1 + 2.0 ** -7 - 2.0 ** -19, 1.4426950408889634 / d ** 0.5       # (the kernel's query: times scale)
+    if what == "scores":                                                       # column 0 of V marks the rows, column 1 one that scores zero
+        q, k, v = torch.full((32, d), 2 * a / scale / 8), torch.full((100, d), a), torch.zeros(100, d)
+        k[0] = 0
+        v[1:, 0] = 1
+        v[0, 1] = 1
+        got, want = _one_token(d, q, k, v)
+        score = (want[:, 0] / want[:, 1]).log() - float(np.log(99))
+        err = ((got[:, 0] / got[:, 1]).log() - float(np.log(99)) - score).abs() / score
+    else:                                                                      # every weight a / 2, under the largest score of its tile
+        q, k, v = torch.zeros(32, d), torch.zeros(100, d), torch.full((100, d), a)
+        q[:, 0] = 8 / scale
+        k[::32, 0], v[::32] = (1 - float(np.log2(a))) / 8, 0
+        got, want = _one_token(d, q, k, v)
+        err = (got / want - 1).abs()
+    assert float(err.max()) <= 4 * 2.0 ** -24, float(err.max())
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64)])
 def test_a_capture_takes_the_kept_plan_of_either_kernel(gpu_device, monkeypatch, dtype, d):
     """A geometry warmed up with a workspace that holds only the generic kernel's rows can be captured with a larger one:
