@@ -411,6 +411,24 @@ def test_fp32_products_keep_their_small_parts(gpu_device, d, what):
     assert float(err.max()) <= 4 * 2.0 ** -24, float(err.max())
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("what", ["column of V", "key", "query"])
+def test_fp32_numbers_out_of_the_parts_range(gpu_device, d, what):
+    """Numbers so small that their parts would fall below bf16's range, in one column of V beside ordinary ones, or in keys or
+    queries whose partners are as large.  Bound: 16 roundings of 2^-24 (the weights of 300 rows; a cut leaves 2e-6 and more)."""
+    gen = torch.Generator().manual_seed(5)
+    q, k, v = (torch.randn(n, d, generator=gen, dtype=torch.float64) for n in (32, 300, 300))
+    if what == "column of V":
+        v[:, 5] *= 2.0 ** -115
+    else:
+        q *= 2.0 ** (118 if what == "key" else -118)
+        k *= 2.0 ** (-118 if what == "key" else 118)
+    got, want = _one_token(d, q.float(), k.float(), v.float())
+    cols = [5] if what == "column of V" else list(range(d))
+    err = float((got - want)[:, cols].norm() / want[:, cols].norm())
+    assert err <= 2.0 ** -20, err
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64)])
 def test_a_capture_takes_the_kept_plan_of_either_kernel(gpu_device, monkeypatch, dtype, d):
     """A geometry warmed up with a workspace that holds only the generic kernel's rows can be captured with a larger one:
