@@ -429,6 +429,19 @@ def test_fp32_numbers_out_of_the_parts_range(gpu_device, d, what):
     assert err <= 2.0 ** -20, err
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_fp32_sums_over_many_rows(gpu_device, monkeypatch, d):
+    """One range of 20000 rows, V of one sign: what an addition to a large sum cuts would add up.  Bound: 16 roundings of 2^-24
+    (a wave's sums of 2500 to 5000 weighted rows in any order, each rounded to nearest, err by about their square root)."""
+    monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", "1")
+    gen = torch.Generator().manual_seed(6)
+    q, k = torch.randn(32, d, generator=gen), torch.randn(20000, d, generator=gen)
+    v = 1 + (torch.rand(20000, d, generator=gen) - 0.5) * 2.0 ** -7
+    got, want = _one_token(d, q, k, v)
+    err = float((got / want - 1).abs().square().mean().sqrt())
+    assert err <= 2.0 ** -20, err
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 64)])
 def test_a_capture_takes_the_kept_plan_of_either_kernel(gpu_device, monkeypatch, dtype, d):
     """A geometry warmed up with a workspace that holds only the generic kernel's rows can be captured with a larger one:
