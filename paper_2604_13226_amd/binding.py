@@ -351,9 +351,10 @@ def _requests(requests):
     arr = (kvp_request_t * max(n_req, 1))()
     keep = []
     for i, (ids, base_pos) in enumerate(requests):
+        ids = np.ascontiguousarray(ids, np.int64)  # (one id alone: an array of one)
         n = len(ids)
         if n:  # (an array's .ctypes.data costs four times as much as this copy)
-            a = (ctypes.c_char * (8 * n)).from_buffer_copy(np.ascontiguousarray(ids, np.int64).tobytes())
+            a = (ctypes.c_char * (8 * n)).from_buffer_copy(ids.tobytes())
             keep.append(a)
             arr[i].packet_ids = ctypes.addressof(a)
         arr[i].k = n

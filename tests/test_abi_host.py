@@ -777,3 +777,15 @@ def test_the_partial_rows_of_a_batch_fit(dtype, head_dim, n_q_heads, n_kv_heads)
         assert need <= most or (head_dim, dtype) == (256, "bf16")
         beyond += need > most
     assert (beyond > 0) == ((head_dim, dtype) == (256, "bf16"))
+
+
+@pytest.mark.parametrize("ids,n", [(7, 1), (np.int64(7), 1), (np.array(7), 1), ([7], 1), ((7, 8, 7), 3), (np.array([8, 7], np.int32), 2),
+                                   (np.arange(7, 11)[::2][:1], 1), ([], 0), (np.zeros(0, np.int64), 0)])
+def test_packet_ids_in_any_form(ids, n):
+    s = dry_store()
+    for pid in (7, 8):
+        kvp.kvp_store_put(s, pid, None, None, n_tokens=10)
+    cache = kvp.Cache.dry(1, t_cap=64)
+    kvp.kvp_assemble(s, [(ids, 3)], cache)
+    assert cache.ctx_len[0] == 3 + 10 * n
+    kvp.kvp_prefill_packets(s, [(ids, 0)], 0, None, None, None, np.array([0, 2], np.int32), None, None, None)
