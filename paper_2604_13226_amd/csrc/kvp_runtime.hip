@@ -1267,13 +1267,18 @@ MfmaShape mfma_shape(const kvp_store *s, int n_req, const int32_t *q_off, const 
         const double work = tile * (rb.tiles - rb.half_tiles) + 1.08 * rb.half_tiles, mean = work / rb.n;
         const bool alike = tile * rb.longest <= 1.05 * mean, even = alike || !wide;
         const int64_t most = bm == 256 ? s->n_cu * 15 / 8 : 3 * s->n_cu;  // (30 MB of partial rows)
+        // (a call plans for every new geometry: the requests are walked once per length that a range can have)
+        std::vector<int32_t> row_bl(even ? 0 : n_req);
+        for (int r = 0; r < n_req && !even; ++r) row_bl[r] = (int32_t)(((int64_t)(q_off[r + 1] - q_off[r]) * gq + bm - 1) / bm * s->cfg.n_kv_heads);
+        int32_t walked = 0, walked_items = 0;
         for (int64_t w = 1; w <= MAX_SPLITS && (w == 1 || (rb.n * w <= most && rb.longest >= 4 * w)); ++w) {
             const int64_t range = (rb.longest + w - 1) / w;  // tiles, the same for all requests of a ragged batch
-            double items = (double)rb.n * w;
-            if (!even) {
-                items = 0;
-                for (int r = 0; r < n_req; ++r) items += (double)(((int64_t)(q_off[r + 1] - q_off[r]) * gq + bm - 1) / bm * s->cfg.n_kv_heads) * ((req_tiles[r] + range - 1) / range);
+            if (!even && walked != range) {
+                walked = (int32_t)range;
+                walked_items = 0;
+                for (int r = 0; r < n_req; ++r) walked_items += row_bl[r] * ((req_tiles[r] + walked - 1) / walked);
             }
+            const double items = even ? (double)rb.n * w : walked_items;
             const double last = (even ? tile * rb.longest / w : tile * range) + 8;
             double us;
             if (items <= n_cu) us = last;
