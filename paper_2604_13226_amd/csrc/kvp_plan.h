@@ -213,8 +213,8 @@ enum { ATTN_GENERIC = 0, ATTN_MFMA = 1, ATTN_F32 = 2, ATTN_NARROW = 3 };
 constexpr int ATTN_NARROW_BM = 32;  // packed rows of a work item of the narrow kernel
 constexpr int ATTN_F32_BM = 32;  // packed rows of a work item of the fp32 kernel
 
-// Matrix-core kernels, paged layout: the fp32 kernel keeps an item's block ids in LDS, so one item may span at most
-// this many blocks, and blocks must hold at least MFMA_MIN_BLOCK_SIZE rows.
+// Matrix-core kernels, paged layout: an item spans at most this many blocks (the fp32 kernel keeps their ids in LDS; the
+// bf16 kernels read ids where they need them), and blocks must hold at least MFMA_MIN_BLOCK_SIZE rows.
 constexpr int MFMA_MAX_ITEM_BLOCKS = 2048;
 constexpr int MFMA_MIN_BLOCK_SIZE = 16;
 

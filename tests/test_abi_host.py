@@ -284,8 +284,8 @@ def test_prefill_plan_covers_every_row_and_kv_exactly_once(cfg):
 
 
 def test_paged_items_stay_within_the_block_id_limit(monkeypatch):
-    """Paged layout: an item keeps its block ids in LDS, at most 2047 of them, so a long context
-    is cut further than the work-item target asks for."""
+    """Paged layout: an item spans at most 2047 blocks (what the fp32 kernel's LDS has room for), so a long
+    context is cut further than the work-item target asks for."""
     monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", "1")
     s = dry_store(n_q_heads=8, n_kv_heads=2, max_positions=1 << 17)
     ctx, n_q = [70000, 40000, 100], [8, 40, 3]
