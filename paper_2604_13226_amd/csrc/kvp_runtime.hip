@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <unordered_set>
 #include <string>
 #include <thread>
@@ -1332,6 +1333,10 @@ BatchRanges batch_ranges(const kvp_store *s, const RowBlocks &b, int want, bool 
     return BatchRanges{(b.tiles + target - 1) / target, (int)std::max<int64_t>(want, std::min<int64_t>(MAX_SPLITS, 2 * s->n_cu / b.n))};
 }
 
+// How the requests of a batch are cut: into ranges of one length (batch_ranges), as many for each, or of
+// the least length up to twice that which leaves an item per CU.
+enum BatchCut { CUT_ONE_LENGTH, CUT_EQUALLY, CUT_TO_FIT };
+
 // Groups of packed rows and their split-KV items.  Every group of a request gets the same
 // split length (a multiple of bn rows), chosen so the launch has about target_items work
 // items; a group's kv range stops at the last row any of its query rows may see.
@@ -1372,7 +1377,7 @@ int call_kind(const kvp_store *s, const kvp_cache_t *c, int n_req, const int32_t
 int part_f16_of(int kind, int d) { return kind == ATTN_MFMA && d == 128 ? 1 : 0; }
 
 void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
-                  uint64_t room, PrefillPlan &p)
+                  uint64_t room, BatchCut cut, PrefillPlan &p)
 {
     const kvp_config_t &g = s->cfg;
     const int gq = g.n_q_heads / g.n_kv_heads;
@@ -1416,7 +1421,23 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
         if (s->target_items > 0 || !mfma) target = kind == ATTN_F32 && s->target_items == 0 ? s->n_cu : target_items(s);
         want = (int)std::min<int64_t>(MAX_SPLITS, (target + blocks.n - 1) / blocks.n);
     }
-    const BatchRanges batch = batch_ranges(s, blocks, want, mfma && g.head_dim == 128 && (p.bm == 2 * MFMA_BM || p.split_in_wg), target);
+    BatchRanges batch = batch_ranges(s, blocks, want, mfma && g.head_dim == 128 && (p.bm == 2 * MFMA_BM || p.split_in_wg), target);
+    if (cut == CUT_TO_FIT) {
+        for (int64_t t = batch.tiles; t <= 2 * batch.tiles; ++t) {
+            int64_t items = 0;
+            for (int r = 0; r < n_req; ++r) {
+                const int64_t rows = ctx_len[r] + p.reqs[r].n_q;
+                const int64_t len = (std::max<int64_t>({t * 64, (rows + batch.max_ranges - 1) / batch.max_ranges, min_split}) + p.bn - 1) / p.bn * p.bn;
+                items += ((int64_t)p.reqs[r].n_q * gq + p.bm - 1) / p.bm * g.n_kv_heads * ((rows + len - 1) / len);
+            }
+            if (items <= s->n_cu) {
+                batch.tiles = t;
+                break;
+            }
+        }
+    } else if (cut == CUT_EQUALLY) {
+        want = (int)std::min<int64_t>(MAX_SPLITS, ((kind == ATTN_F32 ? s->n_cu : target_items(s)) + blocks.n - 1) / blocks.n);
+    }
     int most = MAX_SPLITS;  // ranges of a row block, at most: what the merge takes, and what `room` has slots for
     if (s->target_items == 0)
         most = (int)std::min<uint64_t>(most, std::max<uint64_t>(1, room / (uint64_t)(part_slot_bytes(p.bm, g.head_dim, part_f16_of(kind, g.head_dim)) * blocks.n)));
@@ -1426,7 +1447,7 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
         const int total = rq.ctx_len + rq.n_q;
         auto range_len = [&](int rows, int limit) {  // limit: ranges at most
             int n = std::min(want, limit), len = (rows + n - 1) / n;
-            if (n_req > 1 && !sh.even && s->target_items == 0) {
+            if (n_req > 1 && !sh.even && cut != CUT_EQUALLY && s->target_items == 0) {
                 n = std::min(batch.max_ranges, limit);
                 len = (int)std::max<int64_t>(batch.tiles * 64, (rows + n - 1) / n);
             }
@@ -1496,6 +1517,62 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
     int64_t rows = 0;
     for (int r = 0; r < n_req; ++r) rows += p.reqs[r].n_q > 0 ? p.reqs[r].ctx_len + p.reqs[r].n_q : 0;
     p.shared_rows = xcd_order(p.items, g.n_kv_heads) || !streams_rows(s, rows, blocks.tiles);
+}
+
+// When the last item of a launch ends, and when it would if the work were spread evenly, in kv rows: an item takes
+// as long as 512 rows beyond its own, starts in launch order on its XCD as soon as a workgroup's place
+// is free there, and every XCD has `places` of them.
+struct LaunchTime { int64_t end = 0, even = 0; };
+LaunchTime launch_time(const std::vector<AttnItem> &items, int n_kv, int places)
+{
+    LaunchTime t;
+    std::vector<int64_t> busy;
+    int64_t longest = 0;
+    for (int x = 0; x < (n_kv % 8 == 0 ? 1 : 8); ++x) {  // (with a multiple of eight heads the XCDs' items are alike)
+        busy.assign(places, 0);
+        int64_t sum = 0;
+        for (size_t i = x; i < items.size(); i += 8) {
+            if (items[i].group < 0) continue;
+            const int64_t rows = 512 + (items[i].kv_end - items[i].kv_begin + 31) / 32 * 32;
+            std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+            busy.back() += rows;
+            t.end = std::max(t.end, busy.back());
+            std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+            sum += rows;
+            longest = std::max(longest, rows);
+        }
+        t.even += sum / places;
+    }
+    if (n_kv % 8 != 0) t.even /= 8;
+    t.even = std::max(t.even, longest);
+    return t;
+}
+
+// A batch of the kernels that mfma_shape does not cover.  Ranges of one length are the rule; where they leave an XCD
+// a second round of workgroups or a longer queue than others, another cut may end sooner.  (Per layer with as many ranges for each
+// request, ranges of one length, and the cut taken here: fp32, 32 / 8 heads, four requests of 0.7K to 3K rows with 16 to 32
+// query rows 35.9, 39.0, 30.4 us at 64 columns, 56.9, 67.2, 53.4 at 128, 163.7, 183.0, 157.7 at 256; bf16 of 256 columns,
+// 16 / 2 heads, three of 2.5K to 5.6K with 81 to 203 81.3, 121.2, 80.7, 32 / 8 heads, nine of 3K to 16K with 8 to 98 460, 592,
+// 462, twelve of 0.3K to 6K with 2 to 38 155, 138, 118.  Of 140 random batches, with the rule, none got slower.)
+void plan_batch(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
+                uint64_t room, PrefillPlan &p)
+{
+    const kvp_config_t &g = s->cfg;
+    plan_prefill(s, cache, kind, n_req, ctx_len, pos0, q_off, room, CUT_ONE_LENGTH, p);
+    if (n_req < 2 || s->target_items > 0 || !(kind == ATTN_F32 || (kind == ATTN_MFMA && g.head_dim != 128))) return;
+    const int places = s->n_cu / 8 * (kind == ATTN_MFMA && g.head_dim == 64 ? 2 : 1);  // (LDS and registers)
+    const LaunchTime first = launch_time(p.items, g.n_kv_heads, places);
+    if (first.end * 10 <= first.even * 11) return;
+    int64_t least = first.end;
+    for (BatchCut cut : {CUT_EQUALLY, CUT_TO_FIT}) {
+        PrefillPlan other;
+        plan_prefill(s, cache, kind, n_req, ctx_len, pos0, q_off, room, cut, other);
+        const int64_t end = launch_time(other.items, g.n_kv_heads, places).end;
+        if (end < least) {
+            least = end;
+            p = std::move(other);
+        }
+    }
 }
 
 // The items of a one-request MFMA launch as a formula in the kernel arguments (AttnInline), if
@@ -1674,14 +1751,14 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     };
     if (!hit) {
         if (sig.back() == 0) {
-            plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, UINT64_MAX, p);
+            plan_batch(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, UINT64_MAX, p);
             best_need = plan_need();
             // The static scratch cannot grow: there a launch that wants more is cut into what fits.  (256 columns of bf16,
             // where a partial slot is 129 KB: four requests of 8K to 0.5K rows of 32 / 8 heads want 65 MB and take 44 us in a
             // workspace, 72 in the scratch's 31; the generic kernel takes a hundred times as long.)
             if (fixed && workspace_bytes < best_need && p.kind != ATTN_GENERIC) {
                 p = PrefillPlan();
-                plan_prefill(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, workspace_bytes, p);
+                plan_batch(s, cache, best_kind, n_req, rows.data(), cache->ctx_len, q_offsets, workspace_bytes, p);
                 best_need = plan_need();
             }
             if (may_fall_back && workspace_bytes < best_need) {
@@ -1691,7 +1768,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
         }
         if (sig.back() == 1) {
             p = PrefillPlan();
-            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, UINT64_MAX, p);
+            plan_prefill(s, cache, best_kind == ATTN_NARROW ? ATTN_MFMA : ATTN_GENERIC, n_req, rows.data(), cache->ctx_len, q_offsets, UINT64_MAX, CUT_ONE_LENGTH, p);
         }
     }
     kvp_store::PrefillCached &pf = *found;

@@ -789,3 +789,38 @@ def test_packet_ids_in_any_form(ids, n):
     kvp.kvp_assemble(s, [(ids, 3)], cache)
     assert cache.ctx_len[0] == 3 + 10 * n
     kvp.kvp_prefill_packets(s, [(ids, 0)], 0, None, None, None, np.array([0, 2], np.int32), None, None, None)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128, 256])
+@pytest.mark.parametrize("heads,ctx,n_q,items_at_most,range_at_most", [
+    ((32, 8), [1200, 2500, 700, 3000], [16, 30, 20, 32], 256, 1024), ((28, 4), [1800, 1500, 1900, 2100], [30, 20, 25, 31], 256, 1152),
+    ((32, 8), [300] * 3 + [9000], [64] * 4, 320, 4608), ((32, 8), [3000] * 9, [16] * 8 + [17], 304, 1920)])
+def test_an_fp32_batch_has_an_item_per_compute_unit(head_dim, heads, ctx, n_q, items_at_most, range_at_most):
+    """... where ranges up to twice as long do it and are expected to end sooner; not in the last two."""
+    s = dry_store(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim, dtype="f32", max_positions=1 << 15)
+    cache = kvp.Cache.dry(len(ctx), t_cap=max(ctx) + 64)
+    cache.ctx_len[:len(ctx)] = ctx
+    kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32), None, None)
+    kind, bm, groups, items, slots, need = _attn_plan(s)
+    real = items[items[:, 0] >= 0]
+    assert len(real) <= items_at_most and int((real[:, 3] - real[:, 2]).max()) <= range_at_most
+
+
+@pytest.mark.parametrize("heads,ctx,n_q,longest", [((16, 2), [4061, 5602, 2461], [203, 119, 81], 1472),
+                                                   ((32, 8), [12979, 15889, 5757, 8481, 11629, 14471, 15648, 2903, 6139], [81, 98, 33, 8, 27, 90, 43, 92, 20], 8000)])
+def test_a_batch_whose_equal_ranges_would_queue_is_cut_otherwise(heads, ctx, n_q, longest):
+    """bf16 of 256 columns: with ranges of one length some XCDs would get a second round of workgroups."""
+    s = dry_store(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=256, max_positions=1 << 15)
+    cache = kvp.Cache.dry(len(ctx), t_cap=max(ctx) + 256)
+    cache.ctx_len[:len(ctx)] = ctx
+    kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32), None, None)
+    kind, bm, groups, items, slots, need = _attn_plan(s)
+    real = items[items[:, 0] >= 0]
+    assert groups[:, 5].min() == groups[:, 5].max() and int((real[:, 3] - real[:, 2]).max()) <= longest
+    per_group = {}
+    for g_, sp, b, e in real:
+        per_group.setdefault(int(g_), []).append((int(b), int(e)))
+    for gi, (r, h, m0, n_rows, part0, n_splits) in enumerate(groups):
+        rng = sorted(per_group[gi])
+        assert len(rng) == n_splits and rng[0][0] == 0 and all(e0 == b1 for (_, e0), (b1, _) in zip(rng, rng[1:]))
+        assert rng[-1][1] == ctx[r] + (m0 + n_rows - 1) // (heads[0] // heads[1]) + 1
