@@ -1394,7 +1394,15 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
     for (int r = 0; r < n_req; ++r) req_tiles[r] = (ctx_len[r] + q_off[r + 1] - q_off[r] + 63) / 64;
     MfmaShape sh;
     if (mfma && g.head_dim == 128) {
-        sh = mfma_shape(s, n_req, q_off, req_tiles.data());
+        if (cut == CUT_EQUALLY) {  // blocks of 256 rows if a request has that many, ranges for three quarters of the CUs
+            for (int r = 0; r < n_req; ++r)
+                if ((int64_t)(q_off[r + 1] - q_off[r]) * gq >= 2 * MFMA_BM) sh.bm = 2 * MFMA_BM;
+            const RowBlocks b = row_blocks(s, n_req, q_off, req_tiles.data(), sh.bm);
+            sh.split_in_wg = streams_many_tiles(s, b.tiles, sh.bm);
+            if (b.n > 0) sh.want = (int)std::min<int64_t>(MAX_SPLITS, ((sh.split_in_wg ? s->n_cu : target_items(s)) + b.n - 1) / b.n);
+        } else {
+            sh = mfma_shape(s, n_req, q_off, req_tiles.data());
+        }
         p.bm = sh.bm;
         p.split_in_wg = sh.split_in_wg;
     }
@@ -1435,7 +1443,7 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
                 break;
             }
         }
-    } else if (cut == CUT_EQUALLY) {
+    } else if (cut == CUT_EQUALLY && !(mfma && g.head_dim == 128)) {
         want = (int)std::min<int64_t>(MAX_SPLITS, ((kind == ATTN_F32 ? s->n_cu : target_items(s)) + blocks.n - 1) / blocks.n);
     }
     int most = MAX_SPLITS;  // ranges of a row block, at most: what the merge takes, and what `room` has slots for
@@ -1519,55 +1527,72 @@ void plan_prefill(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_
     p.shared_rows = xcd_order(p.items, g.n_kv_heads) || !streams_rows(s, rows, blocks.tiles);
 }
 
-// When the last item of a launch ends, and when it would if the work were spread evenly, in kv rows: an item takes
-// as long as 512 rows beyond its own, starts in launch order on its XCD as soon as a workgroup's place
-// is free there, and every XCD has `places` of them.
-struct LaunchTime { int64_t end = 0, even = 0; };
-LaunchTime launch_time(const std::vector<AttnItem> &items, int n_kv, int places)
+// When the last item of a launch ends, and when it would if the work were spread evenly.  Items start in launch order, each
+// on its XCD as soon as one of the `places` there is free.  Microseconds for the bf16 kernel at 128 columns
+// (see mfma_shape; its 4-wave shape takes 6 for an item and 1.33 for a tile, 0.6 of that beside another on its CU), else
+// tiles of 64 rows, an item being eight more.
+struct LaunchTime {
+    double end = 0, even = 0;
+    bool few_over = false;  // an XCD has more items than places, but by an eighth at most
+};
+LaunchTime launch_time(const kvp_store *s, const PrefillPlan &p)
 {
+    const kvp_config_t &g = s->cfg;
+    const bool us = p.kind == ATTN_MFMA && g.head_dim == 128;
+    const int places = s->n_cu / 8 * (p.kind == ATTN_MFMA && g.head_dim == 64 ? 2 : 1);  // (LDS and registers)
+    const bool four_waves = us && p.bm == MFMA_BM && !p.split_in_wg;
+    const double per_item = four_waves ? 6 : 8;
+    const double tile = !us ? 1 : p.bm != MFMA_BM ? 2.0 : p.split_in_wg ? 1.08 : 1.33;
+    int most = 0;
     LaunchTime t;
-    std::vector<int64_t> busy;
-    int64_t longest = 0;
-    for (int x = 0; x < (n_kv % 8 == 0 ? 1 : 8); ++x) {  // (with a multiple of eight heads the XCDs' items are alike)
+    std::vector<double> busy;
+    double longest = 0, sum = 0;
+    const int xcds = g.n_kv_heads % 8 == 0 ? 1 : 8;  // (with a multiple of eight heads all have alike items)
+    for (int x = 0; x < xcds; ++x) {
         busy.assign(places, 0);
-        int64_t sum = 0;
-        for (size_t i = x; i < items.size(); i += 8) {
-            if (items[i].group < 0) continue;
-            const int64_t rows = 512 + (items[i].kv_end - items[i].kv_begin + 31) / 32 * 32;
-            std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
-            busy.back() += rows;
+        int n = 0;
+        for (size_t i = x; i < p.items.size(); i += 8) {
+            const AttnItem &it = p.items[i];
+            if (it.group < 0) continue;
+            ++n;
+            const double took = per_item + (it.half_block ? 1.08 : tile) * ((it.kv_end - it.kv_begin + 63) / 64);
+            std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+            busy.back() += four_waves && busy.back() > 0 ? 0.6 * took : took;
             t.end = std::max(t.end, busy.back());
-            std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
-            sum += rows;
-            longest = std::max(longest, rows);
+            std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+            sum += took;
+            longest = std::max(longest, took);
         }
-        t.even += sum / places;
+        most = std::max(most, n);
     }
-    if (n_kv % 8 != 0) t.even /= 8;
-    t.even = std::max(t.even, longest);
+    t.few_over = most > places && most <= places * 9 / 8;
+    t.even = std::max(longest, sum / (xcds * places));
+    if (us && p.any_split) t.end += 4 + p.n_slots * (0.4e-6 * 256) * p.bm;
     return t;
 }
 
-// A batch of the kernels that mfma_shape does not cover.  Ranges of one length are the rule; where they leave an XCD
-// a second round of workgroups or a longer queue than others, another cut may end sooner.  (Per layer with as many ranges for each
-// request, ranges of one length, and the cut taken here: fp32, 32 / 8 heads, four requests of 0.7K to 3K rows with 16 to 32
-// query rows 35.9, 39.0, 30.4 us at 64 columns, 56.9, 67.2, 53.4 at 128, 163.7, 183.0, 157.7 at 256; bf16 of 256 columns,
-// 16 / 2 heads, three of 2.5K to 5.6K with 81 to 203 81.3, 121.2, 80.7, 32 / 8 heads, nine of 3K to 16K with 8 to 98 460, 592,
-// 462, twelve of 0.3K to 6K with 2 to 38 155, 138, 118.  Of 140 random batches, with the rule, none got slower.)
+// A batch.  Ranges of one length are the rule; where they leave an XCD a second round of workgroups or a longer queue than
+// others, another cut may end sooner.  (Per layer with as many ranges for each request, ranges of one length, and the cut taken
+// here: fp32, 32 / 8 heads, four requests of 0.7K to 3K rows with 16 to 32 query rows 35.9, 39.0, 30.4 us at 64
+// columns, 56.9, 67.2, 53.4 at 128, 163.7, 183.0, 157.7 at 256; bf16 of 256 columns, 16 / 2 heads, three of 2.5K to 5.6K with
+// 81 to 203 81.3, 121.2, 80.7, 32 / 8 heads, nine of 3K to 16K with 8 to 98 460, 592, 462; bf16 of 128 columns, 16 / 2 heads,
+// three of 18.5K with 162 92.5, 153.6, 93.1, 28 / 4 heads, two of 1.4K and 1.9K with 152 and 216 31.4, 37.8, 31.5, 32 / 8 heads,
+// 32 of 0.2K to 6K 189, 215, 185.  Of 440 random batches 22 are cut otherwise, 4 to 65 % faster.)
 void plan_batch(const kvp_store *s, const kvp_cache_t *cache, int kind, int n_req, const int32_t *ctx_len, const int32_t *pos0, const int32_t *q_off,
                 uint64_t room, PrefillPlan &p)
 {
-    const kvp_config_t &g = s->cfg;
     plan_prefill(s, cache, kind, n_req, ctx_len, pos0, q_off, room, CUT_ONE_LENGTH, p);
-    if (n_req < 2 || s->target_items > 0 || !(kind == ATTN_F32 || (kind == ATTN_MFMA && g.head_dim != 128))) return;
-    const int places = s->n_cu / 8 * (kind == ATTN_MFMA && g.head_dim == 64 ? 2 : 1);  // (LDS and registers)
-    const LaunchTime first = launch_time(p.items, g.n_kv_heads, places);
-    if (first.end * 10 <= first.even * 11) return;
-    int64_t least = first.end;
+    if (n_req < 2 || s->target_items > 0 || s->force_bm || s->force_split_in_wg >= 0 || !(kind == ATTN_F32 || kind == ATTN_MFMA)) return;
+    const LaunchTime first = launch_time(s, p);
+    if (first.end <= 1.2 * first.even) return;
+    // (two of the 4-wave shape's workgroups share a CU well; a few that do so in an otherwise even launch are its last)
+    if (kind == ATTN_MFMA && s->cfg.head_dim == 128 && p.bm == MFMA_BM && !p.split_in_wg && !first.few_over) return;
+    double least = 0.95 * first.end;
     for (BatchCut cut : {CUT_EQUALLY, CUT_TO_FIT}) {
+        if (cut == CUT_TO_FIT && kind == ATTN_MFMA && s->cfg.head_dim == 128) continue;  // (mfma_shape has weighed that)
         PrefillPlan other;
         plan_prefill(s, cache, kind, n_req, ctx_len, pos0, q_off, room, cut, other);
-        const int64_t end = launch_time(other.items, g.n_kv_heads, places).end;
+        const double end = launch_time(s, other).end;
         if (end < least) {
             least = end;
             p = std::move(other);

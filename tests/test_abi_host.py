@@ -806,11 +806,13 @@ def test_an_fp32_batch_has_an_item_per_compute_unit(head_dim, heads, ctx, n_q, i
     assert len(real) <= items_at_most and int((real[:, 3] - real[:, 2]).max()) <= range_at_most
 
 
-@pytest.mark.parametrize("heads,ctx,n_q,longest", [((16, 2), [4061, 5602, 2461], [203, 119, 81], 1472),
-                                                   ((32, 8), [12979, 15889, 5757, 8481, 11629, 14471, 15648, 2903, 6139], [81, 98, 33, 8, 27, 90, 43, 92, 20], 8000)])
-def test_a_batch_whose_equal_ranges_would_queue_is_cut_otherwise(heads, ctx, n_q, longest):
-    """bf16 of 256 columns: with ranges of one length some XCDs would get a second round of workgroups."""
-    s = dry_store(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=256, max_positions=1 << 15)
+@pytest.mark.parametrize("head_dim,heads,ctx,n_q,longest", [
+    (256, (16, 2), [4061, 5602, 2461], [203, 119, 81], 1472),
+    (256, (32, 8), [12979, 15889, 5757, 8481, 11629, 14471, 15648, 2903, 6139], [81, 98, 33, 8, 27, 90, 43, 92, 20], 8000),
+    (128, (16, 2), [18499] * 3, [162] * 3, 3136), (128, (28, 4), [1430, 1942], [152, 216], 448)])
+def test_a_batch_whose_equal_ranges_would_queue_is_cut_otherwise(head_dim, heads, ctx, n_q, longest):
+    """bf16: with ranges of one length some XCDs would get a second round of workgroups."""
+    s = dry_store(n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=head_dim, max_positions=1 << 15)
     cache = kvp.Cache.dry(len(ctx), t_cap=max(ctx) + 256)
     cache.ctx_len[:len(ctx)] = ctx
     kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.concatenate([[0], np.cumsum(n_q)]).astype(np.int32), None, None)
