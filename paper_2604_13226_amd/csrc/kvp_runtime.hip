@@ -236,7 +236,7 @@ struct kvp_store {
     bool dry = false;
     int n_cu = 256;
     int force_generic = 0;
-    int target_items = 0;  // 0: three quarters of the CU count (measured optimum at 8K context)
+    int target_items = 0;  // test knob (KVP_ATTN_TARGET_ITEMS): work items of an attention launch; 0: chosen per call
     int asm_tile_rows = 0;  // 0: chosen per call (tile_rows_for)
     int asm_nontemporal = -1;  // -1: non-temporal gather decided per call
     int asm_split_kv = 1;  // the gather's workgroups move either the K or the V rows of a tile (KVP_ASM_SPLIT_KV=0: both)
