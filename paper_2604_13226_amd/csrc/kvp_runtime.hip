@@ -1660,8 +1660,9 @@ uint64_t kvp_prefill_workspace_bytes(const kvp_store_t *s, int32_t n_req, int32_
     const int kind = attn_kind(s, nullptr);
     const bool mfma = kind == ATTN_MFMA;
     const int bm = base_bm(kind);  // smaller or larger row blocks need no more
-    // groups <= Hkv * (rows / bm + one ragged block per request); every group has at most
-    // ceil(target / groups) <= target / groups + 1 splits (and never more than MAX_SPLITS)
+    // groups <= Hkv * (rows / bm + one ragged block per request); every group has as many slots as the most ranges of any, at
+    // most 2 n_cu / groups or the target / groups, rounded up, and one of the query rows (mfma_shape's larger launches: 3 n_cu
+    // slots of 128 rows or 15/8 n_cu of 256)
     const uint64_t groups = (uint64_t)g.n_kv_heads * ((uint64_t)max_tot_q * gq / bm + (uint64_t)n_req);
     // (a paged cache may force extra splits: at most max_ctx / 32704 more per group)
     const uint64_t extra = (uint64_t)max_ctx / ((MFMA_MAX_ITEM_BLOCKS - 1) * MFMA_MIN_BLOCK_SIZE / 64 * 64);
