@@ -853,7 +853,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         }
     } else if (it.part_slot >= 0) {
         // A slot holds a.bm rows of D fp16 values (the launch's largest row block; BM <= a.bm), then
-        // m and l of each row in fp32.  A row of the split's unnormalised O goes out as fp16 scaled
+        // (m, l) of each row in fp32.  A row of the split's unnormalised O goes out as fp16 scaled
         // by a power of two 2^-e that brings its largest magnitude below 1; m + e and l 2^-e go with
         // it, which is the same partial result relative to another reference, so the merge's
         // algebra does not change.  Eleven significant bits relative to the row's maximum, where the
@@ -881,31 +881,18 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             return make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, halfx2)),
                               __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, halfx2)));
         };
-        // The rows go through LDS so that they leave as whole 256-byte rows (four per store
-        // instruction) instead of 16-byte pieces: each wave parks its 32 x D halves in a region of its
-        // own in the (now idle) tile stages, 8-byte chunk c of row n at chunk c ^ n (n mod the chunks of
-        // a row), and reads them back row by row.  (KS = 2: half rows, behind the first 70 KiB that the merge has used.)
-        if (KS == 1) wg_barrier();  // every wave is done with the tiles
-        constexpr int CHO = CH / KS, OB = 16 * CHO;  // 16-byte chunks and bytes of a row that this wave writes
-        char *reg = lds + (KS == 2 ? 70 * 1024 : 0) + wave * (32 * OB);
+        // Written as the accumulators lie (part_f16_at): a store instruction fills a whole KiB, and nothing passes
+        // through LDS.  (KS = 2: half of the columns each.)
+        if (row_ok) {
 #pragma unroll
-        for (int eb = 0; eb < EBO; ++eb)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) *(uint2 *)(reg + n * OB + 8 * ((8 * eb + 2 * q4 + h) ^ (n & (2 * CHO - 1)))) = pack4(eb, q4);
-        // (a wave reads only what it wrote itself: no barrier, the compiler orders the two)
-        const int c = lane % CHO;
-#pragma unroll
-        for (int j = 0; j < CHO / 2; ++j) {
-            const int r = 64 / CHO * j + lane / CHO;
-            // logical 8-byte chunks 2c and 2c + 1 of row r sit in the 16-byte unit c ^ (r >> 1), swapped when r is odd
-            uint4 f = *(const uint4 *)(reg + r * OB + 16 * (c ^ ((r >> 1) & (CHO - 1))));
-            if (r & 1) f = make_uint4(f.z, f.w, f.x, f.y);
-            if (32 * wave_r + r < it.n_rows) *(uint4 *)(pp + (int64_t)(32 * wave_r + r) * (D * 2) + 2 * col0 + 16 * c) = f;
+            for (int j = 0; j < 2 * EBO; ++j) {
+                const uint2 lo = pack4(j >> 1, 2 * (j & 1)), hi = pack4(j >> 1, 2 * (j & 1) + 1);
+                *(uint4 *)(pp + part_f16_at(32 * wave_r + n, 2 * (j + 2 * EBO * (KS == 2 ? grp : 0)) + h)) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
         }
         if (row_ok && h == 0 && grp == 0) {
-            float *ml = (float *)(pp + part_rows_bytes(a.bm, D, 1));
-            ml[rr] = m_ref == -INFINITY ? -INFINITY : m_ref + (float)e;
-            ml[a.bm + rr] = l_i * sc;
+            float2 *ml = (float2 *)(pp + part_rows_bytes(a.bm, D, 1));
+            ml[rr] = make_float2(m_ref == -INFINITY ? -INFINITY : m_ref + (float)e, l_i * sc);
         }
     }
     KVP_STAMP(31);
@@ -940,7 +927,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             bf16_t *op = (bf16_t *)a.out + ((int64_t)(it.q_off + tr) * a.n_q_heads + it.kv_head * g + (it.m0 + r) % g) * D + e;
             if (it.part_slot < 0) *op = f32_to_bf16(ld_elem(op) + x);
             else if (SPLIT_P) *((float *)pp + (int64_t)r * D + e) += x;
-            else *((_Float16 *)pp + (int64_t)r * D + e) += (_Float16)x;
+            else *(_Float16 *)(pp + part_f16_at(r, e / 16 * 2 + (e >> 2 & 1)) + 2 * (e & 3) + (e & 8)) += (_Float16)x;
         }
     }
 }

@@ -170,8 +170,7 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(AttnArgs a)
 //   m = max m_i;  l = sum l_i 2^(m_i - m);  O = sum O~_i 2^(m_i - m) / l.
 // A split that saw no visible row has m_i = -inf, l_i = 0 and contributes nothing.
 // ---------------------------------------------------------------------------------
-// One wave per packed row.  A partial row is CPR pieces of 16 bytes -- fp32, or fp16 scaled per row by a power
-// of two that m and l carry along (the MFMA kernel at 128 columns) -- and the 64 lanes hold the pieces of
+// fp32 rows: one wave per packed row.  A partial row is CPR pieces of 16 bytes, and the 64 lanes hold the pieces of
 // G = 64 / CPR splits at a time.  The first NB pieces of every lane are requested before anything is known about
 // the group.  Nothing of the merge passes through LDS: the maximum and the sum over the splits'
 // (m, l) are lane permutes, a split's weight reaches its lanes by a broadcast within sixteen lanes (or a read into a
@@ -242,16 +241,16 @@ template <typename P> __device__ __forceinline__ void add_piece(float (&acc)[16 
 #pragma unroll
     for (int j = 0; j < (int)(16 / sizeof(P)); ++j) acc[j] = __builtin_fmaf((float)e[j], w, acc[j]);
 }
-template <typename P, int CPR, int... I>
-__device__ __forceinline__ void add_pieces(float (&acc)[16 / sizeof(P)], const uint4 *v, float w, int sg, std::integer_sequence<int, I...>)
+template <int CPR, int... I>
+__device__ __forceinline__ void add_pieces(float (&acc)[4], const uint4 *v, float w, int sg, std::integer_sequence<int, I...>)
 {
-    (add_piece<P>(acc, v[I], split_weight<CPR, I>(w, sg)), ...);
+    (add_piece<float>(acc, v[I], split_weight<CPR, I>(w, sg)), ...);
 }
 
-template <typename T, typename P, int D, int NB>
+template <typename T, int D, int NB>
 __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
 {
-    constexpr int CPR = D * (int)sizeof(P) / 16, G = 64 / CPR, NC = 16 / (int)sizeof(P), NCO = NC / G;
+    constexpr int CPR = D / 4, G = 64 / CPR, NC = 4, NCO = NC / G;
     static_assert(CPR <= 64 && NB <= CPR && NCO >= 1, "shape");
     const int lane = threadIdx.x & 63, sg = lane / CPR, c = lane % CPR;
     const int rr = (int)blockIdx.y * COMBINE_ROWS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -267,7 +266,7 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
         mi = ml[0];
         li = ml[a.bm];
     }
-    const char *row = base + (int64_t)rc * (D * (int)sizeof(P)) + 16 * c;
+    const char *row = base + (int64_t)rc * (D * 4) + 16 * c;
     uint4 v[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -284,7 +283,7 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
     float acc[NC];
 #pragma unroll
     for (int j = 0; j < NC; ++j) acc[j] = 0.f;
-    add_pieces<P, CPR>(acc, v, w, sg, std::make_integer_sequence<int, NB>{});
+    add_pieces<CPR>(acc, v, w, sg, std::make_integer_sequence<int, NB>{});
     constexpr int BATCH = 8;  // later pieces go out BATCH per lane at a time, all before the first is used
     for (int s0 = G * NB; s0 < ns; s0 += G * BATCH) {
         uint4 u[BATCH];
@@ -297,11 +296,11 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
         for (int i = 0; i < BATCH; ++i) {
             const int sp = s0 + G * i + sg;
             const float ws = __shfl(w, sg * CPR + (s0 / G + i < CPR ? s0 / G + i : CPR - 1), 64);
-            add_piece<P>(acc, u[i], sp < ns ? ws : 0.f);
+            add_piece<float>(acc, u[i], sp < ns ? ws : 0.f);
         }
     }
     int col = NC * c;
-    if (G >= 2) {
+    if constexpr (G >= 2) {
         col += (lane >> 5) * (NC / 2);
 #pragma unroll
         for (int j = 0; j < NC / 2; ++j) {
@@ -309,7 +308,7 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
             acc[j] += acc[j + NC / 2];
         }
     }
-    if (G == 4) {
+    if constexpr (G == 4) {
         col += ((lane >> 4) & 1) * (NC / 4);
 #pragma unroll
         for (int j = 0; j < NC / 4; ++j) {
@@ -324,6 +323,76 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
     for (int j = 0; j < NCO; ++j) st_elem(o + j, acc[j] * inv);
     T *op = (T *)a.out + ((int64_t)(gp.q_off + t) * a.n_q_heads + hq) * D + col;
     __builtin_memcpy(__builtin_assume_aligned(op, sizeof o), o, sizeof o);
+}
+
+// The MFMA kernel's fp16 rows of 128 columns, scaled per row by a power of two that m and l carry along.  They lie as its
+// accumulators do (part_f16_at), pieces of neighbouring rows next to each other: a workgroup merges four rows, a quad of
+// lanes reads a piece of each, and wave w takes every fourth split from w on.  Each lane reads the (m, l) of its splits itself,
+// so that nothing but the four waves' sums passes between lanes, once, through LDS.  (A wave per row, as above, takes 64
+// places of this layout with every load: 8K context, 27 splits, 26.6 us per layer of a step, so 26.1; with whole rows 26.4.)
+template <int NB>
+__global__ __launch_bounds__(256) void combine_f16_kernel(CombineArgs a)
+{
+    constexpr int D = 128, RS = D + 4;  // (row stride in LDS: the four rows of a quad in banks of their own)
+    __shared__ float xo[4][4][RS];
+    __shared__ float2 xml[4][4];
+    const int lane = threadIdx.x & 63, row = lane & 3, c = lane >> 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r0 = (int)blockIdx.y * 4, stride = a.part_stride;  // (a slot has a multiple of four rows)
+    const char *base = a.partials + (int64_t)blockIdx.x * stride * a.slot_bytes;
+    const char *piece = base + part_f16_at(r0 + row, c), *ml = base + a.rows_bytes + (r0 + row) * 8;
+    float2 s[NB];
+    uint4 v[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int sp = 4 * i + wave;
+        const int64_t at = (int64_t)(sp < stride ? sp : stride - 1) * a.slot_bytes;
+        s[i] = *(const float2 *)(ml + at);
+        v[i] = *(const uint4 *)(piece + at);
+    }
+    const AttnGroup gp = a.groups[blockIdx.x];
+    const int ns = gp.n_splits;
+    if (ns <= 1 || r0 >= gp.n_rows) return;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        if (4 * i + wave >= ns) s[i] = make_float2(-INFINITY, 0.f);
+        mx = fmaxf(mx, s[i].x);
+    }
+    float l = 0.f, acc[8] = {};
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const float w = s[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[i].x - mx);
+        l += s[i].y * w;
+        add_piece<_Float16>(acc, v[i], w);
+    }
+    float *x = &xo[wave][row][16 * (c >> 1) + 4 * (c & 1)];
+    *(float4 *)x = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    *(float4 *)(x + 8) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    if (c == 0) xml[wave][row] = make_float2(mx, l);
+    __syncthreads();
+    const int rr = r0 + wave;  // each wave writes one of the rows
+    if (rr >= gp.n_rows) return;
+    float2 t[4], o[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        t[w] = xml[w][wave];
+        o[w] = *(const float2 *)&xo[w][wave][2 * lane];
+    }
+    const float mm = fmaxf(fmaxf(t[0].x, t[1].x), fmaxf(t[2].x, t[3].x));
+    float lo = 0.f, hi = 0.f, sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float f = t[w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(t[w].x - mm);
+        sum += t[w].y * f;
+        lo = __builtin_fmaf(o[w].x, f, lo);
+        hi = __builtin_fmaf(o[w].y, f, hi);
+    }
+    const float inv = 1.f / sum;
+    const int m = gp.m0 + rr;
+    const int tok = m / a.g, hq = gp.kv_head * a.g + m % a.g;
+    *(uint32_t *)((bf16_t *)a.out + ((int64_t)(gp.q_off + tok) * a.n_q_heads + hq) * D + 2 * lane) =
+        (uint32_t)f32_to_bf16(lo * inv) | ((uint32_t)f32_to_bf16(hi * inv) << 16);
 }
 
 // Other head dims (the generic attention kernel's): a wave per row, a column per lane, split by split.
@@ -362,35 +431,53 @@ __global__ __launch_bounds__(256) void combine_any_kernel(AttnArgs a)
     }
 }
 
-// Pieces requested up front: for the launch's largest split count, rounded up.  (A second round trip costs 2 us; the
-// variant for 24 splits is 0.2 us slower than that for 16 where 12 are needed.  256 columns of fp32: no more
-// than 24, the pieces fill the registers.)
-template <typename T, typename P, int D> static void launch_combine_wave(const AttnArgs &a, dim3 grid, hipStream_t st)
+static CombineArgs combine_args(const AttnArgs &a, int f16)
 {
-    constexpr int G = 64 * 16 / (D * (int)sizeof(P));
     CombineArgs c;
     c.partials = (const char *)a.partials;
     c.out = a.out;
     c.groups = a.groups;
-    c.slot_bytes = (int32_t)part_slot_bytes(a.bm, D, sizeof(P) == 2);
-    c.rows_bytes = (int32_t)part_rows_bytes(a.bm, D, sizeof(P) == 2);
+    c.slot_bytes = (int32_t)part_slot_bytes(a.bm, a.d, f16);
+    c.rows_bytes = (int32_t)part_rows_bytes(a.bm, a.d, f16);
     c.part_stride = a.part_stride;
     c.bm = a.bm;
     c.n_q_heads = a.n_q_heads;
     c.g = a.g;
-    if (a.part_stride <= 4) launch(combine_wave_kernel<T, P, D, 4 / G>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 8) launch(combine_wave_kernel<T, P, D, 8 / G>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 16) launch(combine_wave_kernel<T, P, D, 16 / G>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 24 || D == 256) launch(combine_wave_kernel<T, P, D, 24 / G>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 32) launch(combine_wave_kernel<T, P, D, (D < 256 ? 32 : 24) / G>, grid, dim3(256), 0, st, c);
-    else launch(combine_wave_kernel<T, P, D, (D < 256 ? 40 : 24) / G>, grid, dim3(256), 0, st, c);
+    return c;
+}
+
+// Pieces requested up front: for the launch's largest split count, rounded up.  (A second round trip costs 2 us; the
+// variant for 24 splits is 0.2 us slower than that for 16 where 12 are needed.  256 columns of fp32: no more
+// than 24, the pieces fill the registers.)
+template <typename T, int D> static void launch_combine_wave(const AttnArgs &a, dim3 grid, hipStream_t st)
+{
+    constexpr int G = 64 * 4 / D;
+    const CombineArgs c = combine_args(a, 0);
+    if (a.part_stride <= 4) launch(combine_wave_kernel<T, D, 4 / G>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 8) launch(combine_wave_kernel<T, D, 8 / G>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 16) launch(combine_wave_kernel<T, D, 16 / G>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 24 || D == 256) launch(combine_wave_kernel<T, D, 24 / G>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 32) launch(combine_wave_kernel<T, D, (D < 256 ? 32 : 24) / G>, grid, dim3(256), 0, st, c);
+    else launch(combine_wave_kernel<T, D, (D < 256 ? 40 : 24) / G>, grid, dim3(256), 0, st, c);
+}
+
+static void launch_combine_f16(const AttnArgs &a, dim3 grid, hipStream_t st)
+{
+    const CombineArgs c = combine_args(a, 1);
+    if (a.part_stride <= 4) launch(combine_f16_kernel<1>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 8) launch(combine_f16_kernel<2>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 16) launch(combine_f16_kernel<4>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 24) launch(combine_f16_kernel<6>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 32) launch(combine_f16_kernel<8>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 40) launch(combine_f16_kernel<10>, grid, dim3(256), 0, st, c);
+    else launch(combine_f16_kernel<16>, grid, dim3(256), 0, st, c);
 }
 
 template <typename T> static void launch_combine_fp32_rows(const AttnArgs &a, dim3 grid, hipStream_t st)
 {
-    if (a.d == 64) launch_combine_wave<T, float, 64>(a, grid, st);
-    else if (a.d == 128) launch_combine_wave<T, float, 128>(a, grid, st);
-    else if (a.d == 256) launch_combine_wave<T, float, 256>(a, grid, st);
+    if (a.d == 64) launch_combine_wave<T, 64>(a, grid, st);
+    else if (a.d == 128) launch_combine_wave<T, 128>(a, grid, st);
+    else if (a.d == 256) launch_combine_wave<T, 256>(a, grid, st);
     else hipLaunchKernelGGL((combine_any_kernel<T>), grid, dim3(256), 0, st, a);
 }
 
@@ -403,7 +490,7 @@ int launch_combine(int dtype, const AttnArgs &a, void *stream)
     const dim3 grid((unsigned)a.n_groups, (unsigned)((rows + COMBINE_ROWS - 1) / COMBINE_ROWS));
     if (a.part_f16) {  // the MFMA kernel's partial rows (bf16 stores of 128 columns only)
         if (dtype != 1 || a.d != 128) return (int)hipErrorInvalidValue;
-        launch_combine_wave<bf16_t, _Float16, 128>(a, grid, st);
+        launch_combine_f16(a, grid, st);
     } else if (dtype == 1) {
         launch_combine_fp32_rows<bf16_t>(a, grid, st);
     } else {
