@@ -884,10 +884,18 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         // Written as the accumulators lie (part_f16_at): a store instruction fills a whole KiB, and nothing passes
         // through LDS.  (KS = 2: half of the columns each.)
         if (row_ok) {
-#pragma unroll
-            for (int j = 0; j < 2 * EBO; ++j) {
+            char *const own = pp + part_f16_at(32 * wave_r + n, 4 * EBO * (KS == 2 ? grp : 0) + h);
+            auto piece = [&](int j) -> u32x4_t {
                 const uint2 lo = pack4(j >> 1, 2 * (j & 1)), hi = pack4(j >> 1, 2 * (j & 1) + 1);
-                *(uint4 *)(pp + part_f16_at(32 * wave_r + n, 2 * (j + 2 * EBO * (KS == 2 ? grp : 0)) + h)) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                return u32x4_t{lo.x, lo.y, hi.x, hi.y};
+            };
+            static_assert(KS == 2 || EBO == EB, "2 EBO pieces, 1024 bytes apart");
+            if (a.merged_elsewhere) {
+#pragma unroll
+                for (int j = 0; j < 2 * EBO; ++j) store16_through(own + 1024 * j, piece(j));
+            } else {
+#pragma unroll
+                for (int j = 0; j < 2 * EBO; ++j) *(u32x4_t *)(own + 1024 * j) = piece(j);
             }
         }
         if (row_ok && h == 0 && grp == 0) {

@@ -179,6 +179,8 @@ struct AttnArgs {
     int32_t mixed;        // MFMA kernel, 256-row blocks: some items are half blocks (AttnItem::half_block)
     int32_t nt_loads;     // MFMA kernel, 128 columns: tiles are loaded with the streaming hint (the narrow kernel's always are)
     int32_t part_stride;  // partial slots per group
+    int32_t merged_elsewhere;  // MFMA kernel at 128 columns, 4-wave shape: the merge's workgroups run on other XCDs than the items they
+                               // merge (xcd_order): partial rows are written through the L2
     int32_t max_group_rows;  // largest n_rows among the groups that are split (the combine grid covers no more)
     float scale_log2e;  // log2(e) / sqrt(d)
     AttnInline inl;     // MFMA kernel: the items as a formula (inl.n > 0), when the launch is that regular

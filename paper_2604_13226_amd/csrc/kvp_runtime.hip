@@ -1373,6 +1373,16 @@ int call_kind(const kvp_store *s, const kvp_cache_t *c, int n_req, const int32_t
     return streams_many_tiles(s, tiles, MFMA_BM) ? kind : ATTN_NARROW;
 }
 
+// Whether a launch's partial rows are written through the L2: the merge's workgroups run on other XCDs than the items (see
+// xcd_order), so nothing is gained by keeping the rows there, and in short launches, which have little else to write, the
+// next one waits for all of them to leave at once.  (Per layer, kept and through: 6K rows of 28 / 4 heads 23.1 and 22.7 us,
+// four in-place requests of two row blocks 29.3 and 29.0; where the merge finds them on its own XCD 2.9K rows 16.3 and 16.6,
+// 8K 26.0 and 26.6; eight contexts of 16.9K rows, blocks of 256, 453.8 and 460.2; one token over them 87.4 and 87.8.)
+bool merged_elsewhere(const kvp_store *s, const AttnArgs &a, int n_req)
+{
+    return a.bm == MFMA_BM && !a.split_in_wg && (s->cfg.n_kv_heads % 8 != 0 || a.n_groups > s->cfg.n_kv_heads * n_req);
+}
+
 // Partial rows in scaled fp16: the MFMA kernel at 128 columns (elsewhere they are fp32).
 int part_f16_of(int kind, int d) { return kind == ATTN_MFMA && d == 128 ? 1 : 0; }
 
@@ -1950,6 +1960,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     at.nt_loads = s->nt_loads >= 0 ? s->nt_loads : (pf.shared_rows ? 0 : 1);
     at.part_stride = pf.part_stride;
     at.max_group_rows = pf.max_group_rows;
+    at.merged_elsewhere = merged_elsewhere(s, at, n_req);
     at.g = g.n_q_heads / g.n_kv_heads;
     at.scale_log2e = (float)(1.4426950408889634 / sqrt((double)g.head_dim));
     at.inl.n = pf.inl.n;
@@ -2281,6 +2292,7 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
     at.nt_loads = s->nt_loads >= 0 ? s->nt_loads : (pk.shared_rows ? 0 : 1);
     at.part_stride = pk.part_stride;
     at.max_group_rows = pk.max_group_rows;
+    at.merged_elsewhere = merged_elsewhere(s, at, n_req);
     at.g = g.n_q_heads / g.n_kv_heads;
     at.scale_log2e = (float)(1.4426950408889634 / sqrt((double)g.head_dim));
     at.inl.n = pk.inl.n;
