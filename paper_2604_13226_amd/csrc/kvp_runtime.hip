@@ -1253,6 +1253,33 @@ struct MfmaShape {
     bool own_tail = false;  // the query rows may become a range of their own (plan_prefill)
     bool even = false;      // a large launch, requests about equally long or of one row block each: `want` ranges each
 };
+
+// Ranges of one request with several row blocks to a head, 4-wave shape: as many as leave seven eighths of the CUs an item
+// (`want`), or fewer if an XCD then had more items than CUs.  All row blocks of a head that read a range run on one XCD
+// (xcd_order), and those that share a CU end last.  The number comes from an estimate as in launch_time, for ranges of one
+// length: an item 6 us and 1.5 a tile, 0.6 of it more beside another on its CU, a range with the query rows 1.4 tiles later; the
+// merge 2.4 and 0.25 per MB.  (Per layer, 28 / 4 heads: 2.5K rows with 223 query rows, 39 items on an XCD, 30.6 -> 25.8 us; 3.1K
+// with 197, 33, 31.7 -> 27.0; with the gather, 2.3K with 160, 36, 31.6 -> 24.8, 5.5K with 160, 36, 43.1 -> 35.1.  Left to the
+// estimate everywhere, launches that fit became 0.93 to 1.08 times as fast.)
+int ranges_of_one_request(const kvp_store *s, const RowBlocks &b, int want)
+{
+    const int64_t heads = s->cfg.n_kv_heads, cus = s->n_cu / 8;
+    double least = 0;
+    int best = want;
+    for (int w = want; w >= 1; --w) {
+        const int64_t len = std::max<int64_t>(4, (b.longest + w - 1) / w), n = (b.longest + len - 1) / len;
+        const int64_t on_xcd = b.n / heads * ((heads * n + 7) / 8);
+        if (w == want && on_xcd <= cus) return want;
+        const double tiles = std::max<double>(len, b.longest - (n - 1) * len + 1.4);
+        const double us = (6 + 1.5 * tiles) * (1 + 0.6 * ((on_xcd - 1) / cus)) + (n > 1 ? 2.4 + b.n * n * (0.25e-6 * 256 * MFMA_BM) : 0);
+        if (least == 0 || us < least) {
+            least = us;
+            best = w;
+        }
+    }
+    return best;
+}
+
 MfmaShape mfma_shape(const kvp_store *s, int n_req, const int32_t *q_off, const int32_t *req_tiles)
 {
     MfmaShape sh;
@@ -1313,6 +1340,7 @@ MfmaShape mfma_shape(const kvp_store *s, int n_req, const int32_t *q_off, const 
         sh.own_tail = true;
         for (int r = 0; r < n_req; ++r) sh.own_tail &= (int64_t)(q_off[r + 1] - q_off[r]) * gq <= 128;
         if (sh.own_tail) sh.min_split = 192;
+        else if (n_req == 1) sh.want = ranges_of_one_request(s, b, sh.want);
     }
     return sh;
 }

@@ -407,6 +407,23 @@ def test_regular_one_request_plans_of_any_head_count(n_q_heads, n_kv_heads):
     assert n_split >= 8                                                      # most of them have splits to order
 
 
+@pytest.mark.parametrize("ctx,n_q", [(2300, 160), (5500, 160), (2400, 223), (3080, 197), (1000, 197), (400, 256), (5400, 64)])
+def test_no_xcd_gets_more_items_of_a_request_than_it_has_cus(ctx, n_q):
+    """Several row blocks to a head: workgroup i runs on XCD i mod 8, 32 CUs each; every row block's ranges still
+    cover its rows."""
+    s = dry_store(n_q_heads=28, n_kv_heads=4, max_positions=1 << 17)
+    cache = kvp.Cache.dry(1, t_cap=ctx + n_q)
+    cache.ctx_len[0] = ctx
+    kvp.kvp_query_prefill(s, cache, 0, None, None, None, np.array([0, n_q], np.int32), None, None)
+    kind, bm, groups, items, slots, need = _attn_plan(s)
+    assert kind == MFMA and bm == 128 and len(groups) == 4 * -(-n_q * 7 // 128)
+    assert max(np.count_nonzero(items[x::8, 0] >= 0) for x in range(8)) <= 32
+    for g in range(len(groups)):
+        ranges = sorted((int(b), int(e)) for grp, _, b, e in items if grp == g)
+        last_row = ctx + (min(n_q * 7, int(groups[g][2]) + 128) - 1) // 7 + 1
+        assert ranges[0][0] == 0 and ranges[-1][1] == last_row and all(x[1] == y[0] for x, y in zip(ranges, ranges[1:]))
+
+
 GENERIC, MFMA, F32, NARROW = 0, 1, 2, 3   # kvp_debug_last_plan(s, 3)
 
 
