@@ -82,10 +82,11 @@ __device__ __forceinline__ u32x4_t load16_nowait(const void *p)
     return v;
 }
 // A store that goes on to memory at once, for what a later launch reads on another XCD.  (A line that stays dirty in the L2
-// leaves it at the end of the launch, all of them together.)
+// leaves it at the end of the launch, all of them together.)  The compiler does not see a store in the asm, so the wait states
+// before a vector instruction may overwrite the data of a 16-byte store stand here.
 __device__ __forceinline__ void store16_through(void *p, const u32x4_t &v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 // a pointer the program knows to be wave-uniform, made so for the compiler too
 __device__ __forceinline__ const char *uniform_ptr(const void *p)
