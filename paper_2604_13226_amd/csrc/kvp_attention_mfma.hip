@@ -837,7 +837,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 }
         }
     }
-    if (SPLIT_P) {
+    if constexpr (D == 64) {
         if (it.part_slot >= 0 && row_ok) {  // fp32 rows, then m and l of each row
             float *pp = (float *)((char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 0));
 #pragma unroll
@@ -850,6 +850,26 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 pp[(int64_t)a.bm * D + rr] = m_ref;
                 pp[(int64_t)a.bm * D + a.bm + rr] = l_i;
             }
+        }
+    } else if constexpr (SPLIT_P) {
+        // 256 columns: as the accumulators lie, then (m, l) of each row.  (Row by row, a layer of a step over 2K rows took 32.3 us,
+        // now 30.5; four paged requests of 3 to 8 passages 58.6 and 56.4.  64 columns: a launch that is not split became 2 % slower.)
+        if (it.part_slot >= 0 && row_ok) {
+            char *pp = (char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 0);
+            char *const own = pp + part_piece_at(4 * D, rr, h);
+            auto piece = [&](int j) -> u32x4_t {
+                const floatx16 &o = oacc[j >> 2];
+                const int r = 4 * (j & 3);
+                return __builtin_bit_cast(u32x4_t, make_float4(o[r], o[r + 1], o[r + 2], o[r + 3]));
+            };
+            if (a.merged_elsewhere) {
+#pragma unroll
+                for (int j = 0; j < 4 * EB; ++j) store16_through(own + 1024 * j, piece(j));
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4 * EB; ++j) *(u32x4_t *)(own + 1024 * j) = piece(j);
+            }
+            if (h == 0) ((float2 *)(pp + part_rows_bytes(a.bm, D, 0)))[rr] = make_float2(m_ref, l_i);
         }
     } else if (it.part_slot >= 0) {
         // A slot holds a.bm rows of D fp16 values (the launch's largest row block; BM <= a.bm), then
@@ -881,10 +901,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             return make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, halfx2)),
                               __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, halfx2)));
         };
-        // Written as the accumulators lie (part_f16_at): a store instruction fills a whole KiB, and nothing passes
+        // Written as the accumulators lie (part_piece_at): a store instruction fills a whole KiB, and nothing passes
         // through LDS.  (KS = 2: half of the columns each.)
         if (row_ok) {
-            char *const own = pp + part_f16_at(32 * wave_r + n, 4 * EBO * (KS == 2 ? grp : 0) + h);
+            char *const own = pp + part_piece_at(2 * D, 32 * wave_r + n, 4 * EBO * (KS == 2 ? grp : 0) + h);
             auto piece = [&](int j) -> u32x4_t {
                 const uint2 lo = pack4(j >> 1, 2 * (j & 1)), hi = pack4(j >> 1, 2 * (j & 1) + 1);
                 return u32x4_t{lo.x, lo.y, hi.x, hi.y};
@@ -934,8 +954,9 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
             if (x == 0.f) continue;
             bf16_t *op = (bf16_t *)a.out + ((int64_t)(it.q_off + tr) * a.n_q_heads + it.kv_head * g + (it.m0 + r) % g) * D + e;
             if (it.part_slot < 0) *op = f32_to_bf16(ld_elem(op) + x);
-            else if (SPLIT_P) *((float *)pp + (int64_t)r * D + e) += x;
-            else *(_Float16 *)(pp + part_f16_at(r, e / 16 * 2 + (e >> 2 & 1)) + 2 * (e & 3) + (e & 8)) += (_Float16)x;
+            else if (D == 64) *((float *)pp + (int64_t)r * D + e) += x;
+            else if (SPLIT_P) *(float *)(pp + part_piece_at(4 * D, r, e >> 2) + 4 * (e & 3)) += x;
+            else *(_Float16 *)(pp + part_piece_at(2 * D, r, e / 16 * 2 + (e >> 2 & 1)) + 2 * (e & 3) + (e & 8)) += (_Float16)x;
         }
     }
 }

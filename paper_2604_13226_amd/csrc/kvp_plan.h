@@ -170,16 +170,17 @@ struct AttnArgs {
     const ReqMeta *reqs;
     const AttnGroup *groups;
     const AttnItem *items;
-    float *partials;  // [slot]: bm O~ rows of d elements, then m[bm], then l[bm] (fp32).  The rows are fp32, or (part_f16)
-                      // fp16 scaled per row by a power of two that m and l carry along, where part_f16_at says, then (m, l)[bm]
-    int32_t part_f16;
+    float *partials;  // [slot]: bm O~ rows of d elements (fp32), then m[bm], then l[bm].  The MFMA kernel's at 128 and 256 columns (part_pieces) lie
+                      // where part_piece_at says, then (m, l)[bm]; at 128 columns (part_f16) they are fp16, scaled per row
+                      // by a power of two that m and l carry along
+    int32_t part_f16, part_pieces;
     void *out;        // [tot_q][Hq][d]
     int32_t n_items, n_groups, layer, n_q_heads, n_kv, d, bm, g;
     int32_t split_in_wg;  // MFMA kernel, 128-row blocks: two wave groups take alternate tiles
     int32_t mixed;        // MFMA kernel, 256-row blocks: some items are half blocks (AttnItem::half_block)
     int32_t nt_loads;     // MFMA kernel, 128 columns: tiles are loaded with the streaming hint (the narrow kernel's always are)
     int32_t part_stride;  // partial slots per group
-    int32_t merged_elsewhere;  // MFMA kernel at 128 columns, 4-wave shape: the merge's workgroups run on other XCDs than the items they
+    int32_t merged_elsewhere;  // MFMA kernel, 4-wave shape: the merge's workgroups run on other XCDs than the items they
                                // merge (xcd_order): partial rows are written through the L2
     int32_t max_group_rows;  // largest n_rows among the groups that are split (the combine grid covers no more)
     float scale_log2e;  // log2(e) / sqrt(d)
@@ -202,11 +203,11 @@ struct AppendArgs {
 __host__ __device__ inline int64_t part_rows_bytes(int bm, int d, int f16) { return (int64_t)bm * d * (f16 ? 2 : 4); }
 __host__ __device__ inline int64_t part_slot_bytes(int bm, int d, int f16) { return part_rows_bytes(bm, d, f16) + (int64_t)bm * 8; }
 
-// Where piece c (16 bytes) of an fp16 partial row lies in its slot: columns 16 (c / 2) + 4 (c % 2) + {0..3, 8..11}, the eight
-// that one lane of the MFMA kernel holds in neighbouring accumulators.  Pieces c of 32 rows follow each other.  Behind
+// Where piece c (16 bytes) of the MFMA kernel's partial rows lies in its slot: pieces c of 32 rows follow each other.  fp32: columns
+// 4 c + {0..3}; fp16: 16 (c / 2) + 4 (c % 2) + {0..3, 8..11}, the eight that one lane holds in neighbouring accumulators.  Behind
 // the rows of a slot, (m, l) of each row.  (Row by row, the accumulators had to pass through LDS: an epilogue of 1.5 us, now
 // 1.0.  Per layer of a step: 2.9K rows 16.6 -> 16.3 us, 8K 26.4 -> 26.1, 6K of 28 / 4 heads 23.2 -> 23.0; pruned 22.9 -> 22.7.)
-__host__ __device__ inline int part_f16_at(int row, int c) { return (row >> 5) * 8192 + c * 512 + (row & 31) * 16; }
+__host__ __device__ inline int part_piece_at(int row_bytes, int row, int c) { return (row >> 5) * 32 * row_bytes + c * 512 + (row & 31) * 16; }
 
 // launchers (defined next to their kernels)
 int launch_assemble(int dtype, const AsmArgs &a, int n_layers_launch, void *stream);

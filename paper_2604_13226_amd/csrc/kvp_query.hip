@@ -325,30 +325,32 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
     __builtin_memcpy(__builtin_assume_aligned(op, sizeof o), o, sizeof o);
 }
 
-// The MFMA kernel's fp16 rows of 128 columns, scaled per row by a power of two that m and l carry along.  They lie as its
-// accumulators do (part_f16_at), pieces of neighbouring rows next to each other: a workgroup merges four rows, a quad of
-// lanes reads a piece of each, and wave w takes every fourth split from w on.  Each lane reads the (m, l) of its splits itself,
+// The MFMA kernel's rows: fp16 of 128 columns, scaled per row by a power of two that m and l carry along, or fp32 of 256.
+// They lie as its accumulators do (part_piece_at), pieces of neighbouring rows next to each other: a workgroup merges
+// sixteen pieces of four rows (or, of up to sixteen splits of 256 columns, all 64), a quad of lanes reads a piece of each, and wave w takes every fourth split from w on.  Each lane reads the (m, l) of its splits itself,
 // so that nothing but the four waves' sums passes between lanes, once, through LDS.  (A wave per row, as above, takes 64
 // places of this layout with every load: 8K context, 27 splits, 26.6 us per layer of a step, so 26.1; with whole rows 26.4.)
-template <int NB>
-__global__ __launch_bounds__(256) void combine_f16_kernel(CombineArgs a)
+template <typename P, int D, int NB, int ZC>
+__global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
 {
-    constexpr int D = 128, RS = D + 4;  // (row stride in LDS: the four rows of a quad in banks of their own)
-    __shared__ float xo[4][4][RS];
+    constexpr int NC = 16 / (int)sizeof(P), W = 16 * NC * ZC;  // columns of a piece, and of a workgroup
+    constexpr int RS = W + 4;  // (row stride in LDS: the four rows of a quad in banks of their own)
+    __shared__ __attribute__((aligned(16))) float xo[4][4][RS];
     __shared__ float2 xml[4][4];
     const int lane = threadIdx.x & 63, row = lane & 3, c = lane >> 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = (int)blockIdx.y * 4, stride = a.part_stride;  // (a slot has a multiple of four rows)
     const char *base = a.partials + (int64_t)blockIdx.x * stride * a.slot_bytes;
-    const char *piece = base + part_f16_at(r0 + row, c), *ml = base + a.rows_bytes + (r0 + row) * 8;
+    const char *piece = base + part_piece_at(D * (int)sizeof(P), r0 + row, 16 * ZC * (int)blockIdx.z + c), *ml = base + a.rows_bytes + (r0 + row) * 8;
     float2 s[NB];
-    uint4 v[NB];
+    uint4 v[NB][ZC];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int sp = 4 * i + wave;
         const int64_t at = (int64_t)(sp < stride ? sp : stride - 1) * a.slot_bytes;
         s[i] = *(const float2 *)(ml + at);
-        v[i] = *(const uint4 *)(piece + at);
+#pragma unroll
+        for (int z = 0; z < ZC; ++z) v[i][z] = *(const uint4 *)(piece + at + 8192 * z);
     }
     const AttnGroup gp = a.groups[blockIdx.x];
     const int ns = gp.n_splits;
@@ -359,40 +361,49 @@ __global__ __launch_bounds__(256) void combine_f16_kernel(CombineArgs a)
         if (4 * i + wave >= ns) s[i] = make_float2(-INFINITY, 0.f);
         mx = fmaxf(mx, s[i].x);
     }
-    float l = 0.f, acc[8] = {};
+    float l = 0.f, acc[ZC][NC] = {};
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const float w = s[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[i].x - mx);
         l += s[i].y * w;
-        add_piece<_Float16>(acc, v[i], w);
+#pragma unroll
+        for (int z = 0; z < ZC; ++z) add_piece<P>(acc[z], v[i][z], w);
     }
-    float *x = &xo[wave][row][16 * (c >> 1) + 4 * (c & 1)];
-    *(float4 *)x = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    *(float4 *)(x + 8) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+#pragma unroll
+    for (int z = 0; z < ZC; ++z) {
+        float *x = &xo[wave][row][16 * NC * z + (NC == 8 ? 16 * (c >> 1) + 4 * (c & 1) : 4 * c)];
+        *(float4 *)x = make_float4(acc[z][0], acc[z][1], acc[z][2], acc[z][3]);
+        if constexpr (NC == 8) *(float4 *)(x + 8) = make_float4(acc[z][4], acc[z][5], acc[z][6], acc[z][7]);
+    }
     if (c == 0) xml[wave][row] = make_float2(mx, l);
     __syncthreads();
     const int rr = r0 + wave;  // each wave writes one of the rows
     if (rr >= gp.n_rows) return;
-    float2 t[4], o[4];
+    constexpr int NO = W / 64;  // columns that a lane writes
+    float2 t[4];
+    float o[4][NO];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         t[w] = xml[w][wave];
-        o[w] = *(const float2 *)&xo[w][wave][2 * lane];
+        __builtin_memcpy(o[w], __builtin_assume_aligned(&xo[w][wave][NO * lane], 4 * NO), 4 * NO);
     }
     const float mm = fmaxf(fmaxf(t[0].x, t[1].x), fmaxf(t[2].x, t[3].x));
-    float lo = 0.f, hi = 0.f, sum = 0.f;
+    float out[NO] = {}, sum = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const float f = t[w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(t[w].x - mm);
         sum += t[w].y * f;
-        lo = __builtin_fmaf(o[w].x, f, lo);
-        hi = __builtin_fmaf(o[w].y, f, hi);
+#pragma unroll
+        for (int j = 0; j < NO; ++j) out[j] = __builtin_fmaf(o[w][j], f, out[j]);
     }
     const float inv = 1.f / sum;
     const int m = gp.m0 + rr;
     const int tok = m / a.g, hq = gp.kv_head * a.g + m % a.g;
-    *(uint32_t *)((bf16_t *)a.out + ((int64_t)(gp.q_off + tok) * a.n_q_heads + hq) * D + 2 * lane) =
-        (uint32_t)f32_to_bf16(lo * inv) | ((uint32_t)f32_to_bf16(hi * inv) << 16);
+    bf16_t *op = (bf16_t *)a.out + ((int64_t)(gp.q_off + tok) * a.n_q_heads + hq) * D + W * (int)blockIdx.z + NO * lane;
+    bf16_t u[NO];
+#pragma unroll
+    for (int j = 0; j < NO; ++j) u[j] = f32_to_bf16(out[j] * inv);
+    __builtin_memcpy(__builtin_assume_aligned(op, sizeof u), u, sizeof u);
 }
 
 // Other head dims (the generic attention kernel's): a wave per row, a column per lane, split by split.
@@ -461,16 +472,18 @@ template <typename T, int D> static void launch_combine_wave(const AttnArgs &a, 
     else launch(combine_wave_kernel<T, D, (D < 256 ? 40 : 24) / G>, grid, dim3(256), 0, st, c);
 }
 
-static void launch_combine_f16(const AttnArgs &a, dim3 grid, hipStream_t st)
+template <typename P, int D> static void launch_combine_pieces(const AttnArgs &a, dim3 grid, hipStream_t st)
 {
-    const CombineArgs c = combine_args(a, 1);
-    if (a.part_stride <= 4) launch(combine_f16_kernel<1>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 8) launch(combine_f16_kernel<2>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 16) launch(combine_f16_kernel<4>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 24) launch(combine_f16_kernel<6>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 32) launch(combine_f16_kernel<8>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 40) launch(combine_f16_kernel<10>, grid, dim3(256), 0, st, c);
-    else launch(combine_f16_kernel<16>, grid, dim3(256), 0, st, c);
+    const CombineArgs c = combine_args(a, sizeof(P) == 2);
+    constexpr int Z = D * (int)sizeof(P) / 256;
+    if (a.part_stride > 16) grid.z = Z;  // (the pieces of all columns would fill the registers)
+    if (a.part_stride <= 4) launch(combine_pieces_kernel<P, D, 1, Z>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 8) launch(combine_pieces_kernel<P, D, 2, Z>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 16) launch(combine_pieces_kernel<P, D, 4, Z>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 24) launch(combine_pieces_kernel<P, D, 6, 1>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 32) launch(combine_pieces_kernel<P, D, 8, 1>, grid, dim3(256), 0, st, c);
+    else if (a.part_stride <= 40) launch(combine_pieces_kernel<P, D, 10, 1>, grid, dim3(256), 0, st, c);
+    else launch(combine_pieces_kernel<P, D, 16, 1>, grid, dim3(256), 0, st, c);
 }
 
 template <typename T> static void launch_combine_fp32_rows(const AttnArgs &a, dim3 grid, hipStream_t st)
@@ -488,9 +501,11 @@ int launch_combine(int dtype, const AttnArgs &a, void *stream)
     hipStream_t st = (hipStream_t)stream;
     if (a.part_stride > COMBINE_MAX_SPLITS) return (int)hipErrorInvalidValue;
     const dim3 grid((unsigned)a.n_groups, (unsigned)((rows + COMBINE_ROWS - 1) / COMBINE_ROWS));
-    if (a.part_f16) {  // the MFMA kernel's partial rows (bf16 stores of 128 columns only)
-        if (dtype != 1 || a.d != 128) return (int)hipErrorInvalidValue;
-        launch_combine_f16(a, grid, st);
+    if (a.part_pieces) {  // the MFMA kernel's partial rows (bf16 stores only)
+        if (dtype != 1 || a.part_f16 != (a.d == 128)) return (int)hipErrorInvalidValue;
+        if (a.d == 128) launch_combine_pieces<_Float16, 128>(a, grid, st);
+        else if (a.d == 256) launch_combine_pieces<float, 256>(a, grid, st);
+        else return (int)hipErrorInvalidValue;
     } else if (dtype == 1) {
         launch_combine_fp32_rows<bf16_t>(a, grid, st);
     } else {

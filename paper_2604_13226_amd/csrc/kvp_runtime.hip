@@ -1975,6 +1975,7 @@ int query_prefill_impl(kvp_store *s, kvp_cache_t *cache, int32_t layer, const vo
     at.items = pf.items_dev;
     at.partials = (float *)((char *)workspace + (pf.kind == ATTN_GENERIC ? q_rot_bytes(s, tot_q) : 0));
     at.part_f16 = part_f16_of(pf.kind, g.head_dim);
+    at.part_pieces = pf.kind == ATTN_MFMA && g.head_dim != 64;
     at.out = out;
     at.n_items = pf.n_items;
     at.n_groups = pf.n_groups;
@@ -2306,7 +2307,7 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
     at.groups = pk.groups_dev;
     at.items = pk.items_dev;
     at.partials = (float *)workspace;
-    at.part_f16 = 1;
+    at.part_f16 = at.part_pieces = 1;
     at.out = out;
     at.n_items = pk.n_items;
     at.n_groups = pk.n_groups;

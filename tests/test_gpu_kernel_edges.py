@@ -323,14 +323,15 @@ def test_a_merge_of_many_splits(gpu_device, monkeypatch, dtype, d, n_q, kernel, 
 
 
 @pytest.mark.parametrize("splits", [2, 4, 5, 8])
-@pytest.mark.parametrize("g,n_q,bm", [(1, 33, None), (7, 37, None), (4, 65, "256"), (5, 7, None)])
-def test_a_merge_of_few_splits_of_bf16_rows(gpu_device, monkeypatch, g, n_q, bm, splits):
-    """fp16 partial rows are merged four at a time, each wave every fourth split: few splits, rows that end inside a
-    quad, several row blocks; tolerance of every bf16 case (Q, P and the output rounded to bf16)."""
+@pytest.mark.parametrize("d,g,n_q,bm", [(128, 1, 33, None), (128, 7, 37, None), (128, 4, 65, "256"), (128, 5, 7, None),
+                                        (64, 1, 33, None), (64, 7, 37, None), (256, 5, 7, None), (256, 4, 65, None)])
+def test_a_merge_of_few_splits_of_bf16_rows(gpu_device, monkeypatch, d, g, n_q, bm, splits):
+    """The matrix kernel's partial rows are merged four at a time, each wave every fourth split: few splits, rows that end
+    inside a quad, several row blocks; tolerance of every bf16 case (Q, P and the output rounded to bf16)."""
     monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", str(splits * 2 * -(-g * n_q // int(bm or 128))))
     if bm:
         monkeypatch.setenv("KVP_ATTN_BM", bm)
-    w = _request("bf16", 128, g, splits * 256 - n_q - 7, n_q)
+    w = _request("bf16", d, g, splits * 256 - n_q - 7, n_q)
     got = run_workload(w)
     import paper_2604_13226_amd as kvp
     assert LAST["kernel"] == MFMA and int(kvp.kvp_debug_last_plan(got["store"], 1)[6 + 5]) == splits
