@@ -224,6 +224,17 @@ template <typename F> __device__ __forceinline__ float over_lanes(float x, F f) 
     swap32(x, y);
     return f(x, y);
 }
+__device__ __forceinline__ float max_over_quads(float x)  // over the sixteen lanes that have this one's place in their quad
+{
+    x = fmaxf(x, dpp<0x124>(x));  // turned by four within sixteen
+    x = fmaxf(x, dpp<0x128>(x));  // and by eight
+    float y = opaque(x);
+    swap16(x, y);
+    x = fmaxf(x, y);
+    y = opaque(x);
+    swap32(x, y);
+    return fmaxf(x, y);
+}
 // w of lane CPR * (this lane / CPR) + I
 template <int CPR, int I> __device__ __forceinline__ float split_weight(float w, int sg)
 {
@@ -327,8 +338,11 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
 
 // The MFMA kernel's rows: fp16 of 128 columns, scaled per row by a power of two that m and l carry along, or fp32 of 256.
 // They lie as its accumulators do (part_piece_at), pieces of neighbouring rows next to each other: a workgroup merges
-// sixteen pieces of four rows (or, of up to sixteen splits of 256 columns, all 64), a quad of lanes reads a piece of each, and wave w takes every fourth split from w on.  Each lane reads the (m, l) of its splits itself,
-// so that nothing but the four waves' sums passes between lanes, once, through LDS.  (A wave per row, as above, takes 64
+// sixteen pieces of four rows (or, of up to sixteen splits of 256 columns, all 64), a quad of lanes reads a piece of each,
+// and wave w takes every fourth split from w on.  Each lane reads the (m, l) of its splits itself, and the sixteen lanes of a
+// row read all splits' m between them: weights are relative to the group's maximum in every wave, so that the waves' sums,
+// which pass through LDS once, only need adding.  (Relative to a wave's own they would overflow, or keep an infinity, where
+// the split does not count.)  (A wave per row, as above, takes 64
 // places of this layout with every load: 8K context, 27 splits, 26.6 us per layer of a step, so 26.1; with whole rows 26.4.)
 template <typename P, int D, int NB, int ZC>
 __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
@@ -336,14 +350,21 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     constexpr int NC = 16 / (int)sizeof(P), W = 16 * NC * ZC;  // columns of a piece, and of a workgroup
     constexpr int RS = W + 4;  // (row stride in LDS: the four rows of a quad in banks of their own)
     __shared__ __attribute__((aligned(16))) float xo[4][4][RS];
-    __shared__ float2 xml[4][4];
+    __shared__ float xl[4][4];
+    constexpr int NM = (4 * NB + 15) / 16;
     const int lane = threadIdx.x & 63, row = lane & 3, c = lane >> 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = (int)blockIdx.y * 4, stride = a.part_stride;  // (a slot has a multiple of four rows)
     const char *base = a.partials + (int64_t)blockIdx.x * stride * a.slot_bytes;
     const char *piece = base + part_piece_at(D * (int)sizeof(P), r0 + row, 16 * ZC * (int)blockIdx.z + c), *ml = base + a.rows_bytes + (r0 + row) * 8;
+    float m[NM];
     float2 s[NB];
     uint4 v[NB][ZC];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+        const int sp = 16 * i + c;
+        m[i] = *(const float *)(ml + (int64_t)(sp < stride ? sp : stride - 1) * a.slot_bytes);
+    }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int sp = 4 * i + wave;
@@ -357,13 +378,12 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     if (ns <= 1 || r0 >= gp.n_rows) return;
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        if (4 * i + wave >= ns) s[i] = make_float2(-INFINITY, 0.f);
-        mx = fmaxf(mx, s[i].x);
-    }
+    for (int i = 0; i < NM; ++i) mx = fmaxf(mx, 16 * i + c < ns ? m[i] : -INFINITY);
+    mx = max_over_quads(mx);
     float l = 0.f, acc[ZC][NC] = {};
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
+        if (4 * i + wave >= ns) s[i] = make_float2(-INFINITY, 0.f);
         const float w = s[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[i].x - mx);
         l += s[i].y * w;
 #pragma unroll
@@ -375,30 +395,23 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
         *(float4 *)x = make_float4(acc[z][0], acc[z][1], acc[z][2], acc[z][3]);
         if constexpr (NC == 8) *(float4 *)(x + 8) = make_float4(acc[z][4], acc[z][5], acc[z][6], acc[z][7]);
     }
-    if (c == 0) xml[wave][row] = make_float2(mx, l);
+    if (c == 0) xl[wave][row] = l;
     __syncthreads();
     const int rr = r0 + wave;  // each wave writes one of the rows
     if (rr >= gp.n_rows) return;
     constexpr int NO = W / 64;  // columns that a lane writes
-    float2 t[4];
-    float o[4][NO];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        t[w] = xml[w][wave];
-        __builtin_memcpy(o[w], __builtin_assume_aligned(&xo[w][wave][NO * lane], 4 * NO), 4 * NO);
-    }
-    const float mm = fmaxf(fmaxf(t[0].x, t[1].x), fmaxf(t[2].x, t[3].x));
     float out[NO] = {}, sum = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        const float f = t[w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(t[w].x - mm);
-        sum += t[w].y * f;
+        float o[NO];
+        __builtin_memcpy(o, __builtin_assume_aligned(&xo[w][wave][NO * lane], 4 * NO), 4 * NO);
+        sum += xl[w][wave];
 #pragma unroll
-        for (int j = 0; j < NO; ++j) out[j] = __builtin_fmaf(o[w][j], f, out[j]);
+        for (int j = 0; j < NO; ++j) out[j] += o[j];
     }
     const float inv = 1.f / sum;
-    const int m = gp.m0 + rr;
-    const int tok = m / a.g, hq = gp.kv_head * a.g + m % a.g;
+    const int pr = gp.m0 + rr;
+    const int tok = pr / a.g, hq = gp.kv_head * a.g + pr % a.g;
     bf16_t *op = (bf16_t *)a.out + ((int64_t)(gp.q_off + tok) * a.n_q_heads + hq) * D + W * (int)blockIdx.z + NO * lane;
     bf16_t u[NO];
 #pragma unroll

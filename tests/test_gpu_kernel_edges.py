@@ -338,6 +338,61 @@ def test_a_merge_of_few_splits_of_bf16_rows(gpu_device, monkeypatch, d, g, n_q, 
     compare(w, got, oracle_workload(w))
 
 
+def _merged(monkeypatch, d, splits, score, v, v_new, n_q=9, g=4, n_kv=1):
+    """One request of `splits` ranges of 256 rows, the query rows in the last: all rows of range i score score[i] (log2, a bf16
+    key's rounding aside) and hold v[i] (a number, or one for each column), the query rows score zero and hold
+    v_new.  Returns the output [n_q][n_kv g][d] and the one of float64, from the keys as they are."""
+    import paper_2604_13226_amd as kvp
+    monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", str(splits * n_kv))
+    n = 256 * splits - n_q
+    store = kvp.kvp_store_create(1, n_kv * g, n_kv, d, "bf16", 1.0e4, n + 64, 1 << 20)
+    cache = kvp.Cache.contiguous(store, 1, n + n_q)
+    cache.ctx_len[0] = n
+    k, val = torch.zeros(splits, 256, d), torch.zeros(splits, 256, d)
+    k[:, :, 0] = torch.tensor(score)[:, None] * float(np.log(2)) * d ** 0.5 / 16
+    for i in range(splits):
+        val[i] = torch.as_tensor(v[i], dtype=torch.float32)
+    k, val = (x.view(-1, d)[:n].to(torch.bfloat16).cuda() for x in (k, val))
+    cache.k[0, 0, :, :n], cache.v[0, 0, :, :n] = k, val
+    q = torch.zeros(n_q, n_kv * g, d, dtype=torch.bfloat16, device="cuda:0")
+    q[:, :, 0] = 16
+    kn = torch.zeros(n_q, n_kv, d, dtype=torch.bfloat16, device="cuda:0")
+    vn, out = torch.full_like(kn, v_new), torch.empty_like(q)
+    ws = kvp.alloc_workspace(kvp.kvp_prefill_workspace_bytes(store, 1, n_q, n + n_q))
+    kvp.kvp_query_prefill(store, cache, 0, q, kn, vn, np.array([0, n_q], np.int32), ws, out, kvp.KVP_PREROTATED)
+    plan = kvp.kvp_debug_last_plan(store, 1)
+    assert int(kvp.kvp_debug_last_plan(store, 3)[0]) == MFMA and int(plan[2]) == n_kv and int(plan[6 + 5]) == splits
+    s = torch.cat([k[:, 0].double().cpu() * 16 / d ** 0.5, torch.zeros(n_q, dtype=torch.float64)])
+    w = torch.exp(s - s.max())[None] * (torch.arange(n + n_q)[None] <= n + torch.arange(n_q)[:, None])
+    want = (w / w.sum(1, keepdim=True)) @ torch.cat([val, vn[:, 0]]).double().cpu()
+    return out.double().cpu(), want[:, None].expand(-1, n_kv * g, -1)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("splits,at", [(4, 0), (4, 2), (7, 2), (7, 3), (20, 0), (20, 3), (41, 7), (41, 8)])
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_a_split_of_no_weight_does_not_reach_the_output(gpu_device, monkeypatch, d, splits, at, value):
+    """The query rows weigh 2^300 times what is stored, whose ranges hold an infinity or NaN in one column: whichever
+    of the merge's waves takes it, the output is what the query rows hold."""
+    v = [0.0] * splits
+    v[at] = torch.zeros(d)
+    v[at][d // 2 + 3] = value
+    got, _ = _merged(monkeypatch, d, splits, [-300.0] * (splits - 1) + [-200.0], v, 1.0)
+    assert bool((got == 1).all())
+
+
+@pytest.mark.parametrize("splits", [8, 16, 23])
+@pytest.mark.parametrize("d", [64, 256])
+def test_large_sums_of_splits_of_little_weight_do_not_overflow(gpu_device, monkeypatch, d, splits):
+    """Two ranges whose unnormalised sums come near the end of fp32's range (256 weights of 2^-8 times 3e38), 2^-20 of the
+    query rows' weight: the merge adds them weighed.  Bound: the output's rounding to bf16, and 2^-10 for the scores in fp32."""
+    score, v = [-300.0] * splits, [0.0] * splits
+    for at in (1, 5):
+        score[at], v[at] = -20.0, 3e38
+    got, want = _merged(monkeypatch, d, splits, score, v, 0.0)
+    assert float((got / want - 1).abs().max()) <= 2.0 ** -8 + 2.0 ** -10
+
+
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("ctx,n_q", [(384, 10), (385, 48), (1000, 33), (1009, 20), (1023, 60), (1500, 100), (2047, 9)])
 def test_query_rows_as_a_range_of_their_own(gpu_device, ctx, n_q, paged):
