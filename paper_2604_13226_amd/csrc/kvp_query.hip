@@ -379,12 +379,12 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NM; ++i) mx = fmaxf(mx, 16 * i + c < ns ? m[i] : -INFINITY);
-    mx = max_over_quads(mx);
+    mx = fmaxf(max_over_quads(mx), -3.4028235e38f);  // (finite, so that a split without visible rows has weight zero below)
     float l = 0.f, acc[ZC][NC] = {};
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         if (4 * i + wave >= ns) s[i] = make_float2(-INFINITY, 0.f);
-        const float w = s[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[i].x - mx);
+        const float w = exp2f(s[i].x - mx);  // (the instruction alone gives zero below 2^-126)
         l += s[i].y * w;
 #pragma unroll
         for (int z = 0; z < ZC; ++z) add_piece<P>(acc[z], v[i][z], w);

@@ -393,6 +393,21 @@ def test_large_sums_of_splits_of_little_weight_do_not_overflow(gpu_device, monke
     assert float((got / want - 1).abs().max()) <= 2.0 ** -8 + 2.0 ** -10
 
 
+@pytest.mark.parametrize("splits", [4, 21])
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_splits_whose_weight_is_below_the_normal_range_count(gpu_device, monkeypatch, d, splits):
+    """A range 2^-135 of the query rows' weight holds 3e38; at 128 columns, where a partial row is scaled by its largest
+    number, ranges of one score hold 2^60 and 2^-80.  Bound: the output's rounding to bf16, 2^-10 for the scores in
+    fp32 and the scaled rows in fp16, 2^-13 for a weight of 14 bits."""
+    score, v, v_new = [-300.0] * splits, [0.0] * splits, 1.0
+    score[1], v[1] = -135.0, 3e38
+    if d == 128:
+        score, v, v_new = [0.0] * splits, [2.0 ** -80] * splits, 2.0 ** -80
+        v[1] = 2.0 ** 60
+    got, want = _merged(monkeypatch, d, splits, score, v, v_new)
+    assert float((got / want - 1).abs().max()) <= 2.0 ** -8 + 2.0 ** -10 + 2.0 ** -13
+
+
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("ctx,n_q", [(384, 10), (385, 48), (1000, 33), (1009, 20), (1023, 60), (1500, 100), (2047, 9)])
 def test_query_rows_as_a_range_of_their_own(gpu_device, ctx, n_q, paged):
