@@ -191,6 +191,7 @@ struct CombineArgs {
     void *out;
     const AttnGroup *groups;
     int32_t slot_bytes, rows_bytes, part_stride, bm, n_q_heads, g;
+    int32_t rows_first;  // combine_pieces_kernel: the row blocks run along blockIdx.x, the groups along y
 };
 
 __device__ __forceinline__ float opaque(float x) { asm volatile("" : "+v"(x)); return x; }
@@ -354,8 +355,11 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     constexpr int NM = (4 * NB + 15) / 16;
     const int lane = threadIdx.x & 63, row = lane & 3, c = lane >> 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r0 = (int)blockIdx.y * 4, stride = a.part_stride;  // (a slot has a multiple of four rows)
-    const char *base = a.partials + (int64_t)blockIdx.x * stride * a.slot_bytes;
+    const int stride = a.part_stride;
+    // Eight neighbouring rows lie in the same lines: the two workgroups that read them are on one XCD (every eighth workgroup).
+    const uint32_t x = blockIdx.x, gi = a.rows_first ? blockIdx.y : x;
+    const int r0 = 4 * (int)(a.rows_first ? x / 16 * 16 + x % 8 * 2 + x / 8 % 2 : blockIdx.y);  // (a slot has a multiple of 64 rows)
+    const char *base = a.partials + (int64_t)gi * stride * a.slot_bytes;
     const char *piece = base + part_piece_at(D * (int)sizeof(P), r0 + row, 16 * ZC * (int)blockIdx.z + c), *ml = base + a.rows_bytes + (r0 + row) * 8;
     float m[NM];
     float2 s[NB];
@@ -373,7 +377,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
 #pragma unroll
         for (int z = 0; z < ZC; ++z) v[i][z] = *(const uint4 *)(piece + at + 8192 * z);
     }
-    const AttnGroup gp = a.groups[blockIdx.x];
+    const AttnGroup gp = a.groups[gi];
     const int ns = gp.n_splits;
     if (ns <= 1 || r0 >= gp.n_rows) return;
     float mx = -INFINITY;
@@ -467,6 +471,7 @@ static CombineArgs combine_args(const AttnArgs &a, int f16)
     c.bm = a.bm;
     c.n_q_heads = a.n_q_heads;
     c.g = a.g;
+    c.rows_first = 0;
     return c;
 }
 
@@ -487,8 +492,14 @@ template <typename T, int D> static void launch_combine_wave(const AttnArgs &a, 
 
 template <typename P, int D> static void launch_combine_pieces(const AttnArgs &a, dim3 grid, hipStream_t st)
 {
-    const CombineArgs c = combine_args(a, sizeof(P) == 2);
+    CombineArgs c = combine_args(a, sizeof(P) == 2);
     constexpr int Z = D * (int)sizeof(P) / 256;
+    // As many groups as a multiple of eight: a group's workgroups are on one XCD, that of its items where those keep to one.  Others:
+    // sixteen workgroups take 64 rows of a group, two on each XCD.  (Group by group there too, two XCDs read each line: per layer, 3.4K
+    // rows of 28 / 4 heads with 76 query rows 18.0 us, so 15.6, and by whole rows, a wave each, 16.2; 16 / 2 heads, 145 query
+    // rows over 6K 22.9, 19.9 and 20.5; in place 147 over 2.6K of 28 / 4 heads 26.4, 23.2 and 24.5.)
+    c.rows_first = grid.x % 8 != 0 && grid.x < 65536;
+    if (c.rows_first) grid = dim3((grid.y + 15) / 16 * 16, grid.x);
     if (a.part_stride > 16) grid.z = Z;  // (the pieces of all columns would fill the registers)
     if (a.part_stride <= 4) launch(combine_pieces_kernel<P, D, 1, Z>, grid, dim3(256), 0, st, c);
     else if (a.part_stride <= 8) launch(combine_pieces_kernel<P, D, 2, Z>, grid, dim3(256), 0, st, c);
