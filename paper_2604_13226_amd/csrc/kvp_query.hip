@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
         const int sp = 16 * i + c;
-        m[i] = *(const float *)(ml + (int64_t)(sp < stride ? sp : stride - 1) * a.slot_bytes);
+        m[i] = *(const float *)(ml + __umul24(sp < stride ? sp : stride - 1, a.slot_bytes));
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -382,16 +382,30 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     if (ns <= 1 || r0 >= gp.n_rows) return;
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < NM; ++i) mx = fmaxf(mx, 16 * i + c < ns ? m[i] : -INFINITY);
+    for (int i = 0; i < NM; ++i) {
+        if (16 * i + c >= ns) m[i] = -INFINITY;
+        mx = fmaxf(mx, m[i]);
+    }
     mx = fmaxf(max_over_quads(mx), -3.4028235e38f);  // (finite, so that a split without visible rows has weight zero below)
-    float l = 0.f, acc[ZC][NC] = {};
+    bool low = false;  // weights below 2^-126, for which the instruction alone gives zero
+#pragma unroll
+    for (int i = 0; i < NM; ++i) low |= m[i] - mx < -126.f && m[i] > -INFINITY;
+    float w[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         if (4 * i + wave >= ns) s[i] = make_float2(-INFINITY, 0.f);
-        const float w = exp2f(s[i].x - mx);  // (the instruction alone gives zero below 2^-126)
-        l += s[i].y * w;
+        w[i] = __builtin_amdgcn_exp2f(s[i].x - mx);
+    }
+    if (__any(low)) {
 #pragma unroll
-        for (int z = 0; z < ZC; ++z) add_piece<P>(acc[z], v[i][z], w);
+        for (int i = 0; i < NB; ++i) w[i] = exp2f(opaque(s[i].x) - mx);
+    }
+    float l = 0.f, acc[ZC][NC] = {};
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        l += s[i].y * w[i];
+#pragma unroll
+        for (int z = 0; z < ZC; ++z) add_piece<P>(acc[z], v[i][z], w[i]);
     }
 #pragma unroll
     for (int z = 0; z < ZC; ++z) {
