@@ -856,18 +856,19 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         // now 30.5; four paged requests of 3 to 8 passages 58.6 and 56.4.  64 columns: a launch that is not split became 2 % slower.)
         if (it.part_slot >= 0 && row_ok) {
             char *pp = (char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 0);
-            char *const own = pp + part_piece_at(4 * D, rr, h);
+            const int own = part_piece_at(4 * D, rr, h);
             auto piece = [&](int j) -> u32x4_t {
                 const floatx16 &o = oacc[j >> 2];
                 const int r = 4 * (j & 3);
                 return __builtin_bit_cast(u32x4_t, make_float4(o[r], o[r + 1], o[r + 2], o[r + 3]));
             };
             if (a.merged_elsewhere) {
+                const ThroughStore through(pp, (int)part_rows_bytes(a.bm, D, 0));
 #pragma unroll
-                for (int j = 0; j < 4 * EB; ++j) store16_through(own + 1024 * j, piece(j));
+                for (int j = 0; j < 4 * EB; ++j) through.put16(own + 1024 * j, piece(j));
             } else {
 #pragma unroll
-                for (int j = 0; j < 4 * EB; ++j) *(u32x4_t *)(own + 1024 * j) = piece(j);
+                for (int j = 0; j < 4 * EB; ++j) *(u32x4_t *)(pp + own + 1024 * j) = piece(j);
             }
             if (h == 0) ((float2 *)(pp + part_rows_bytes(a.bm, D, 0)))[rr] = make_float2(m_ref, l_i);
         }
@@ -904,18 +905,19 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         // Written as the accumulators lie (part_piece_at): a store instruction fills a whole KiB, and nothing passes
         // through LDS.  (KS = 2: half of the columns each.)
         if (row_ok) {
-            char *const own = pp + part_piece_at(2 * D, 32 * wave_r + n, 4 * EBO * (KS == 2 ? grp : 0) + h);
+            const int own = part_piece_at(2 * D, 32 * wave_r + n, 4 * EBO * (KS == 2 ? grp : 0) + h);
             auto piece = [&](int j) -> u32x4_t {
                 const uint2 lo = pack4(j >> 1, 2 * (j & 1)), hi = pack4(j >> 1, 2 * (j & 1) + 1);
                 return u32x4_t{lo.x, lo.y, hi.x, hi.y};
             };
             static_assert(KS == 2 || EBO == EB, "2 EBO pieces, 1024 bytes apart");
             if (a.merged_elsewhere) {
+                const ThroughStore through(pp, (int)part_rows_bytes(a.bm, D, 1));
 #pragma unroll
-                for (int j = 0; j < 2 * EBO; ++j) store16_through(own + 1024 * j, piece(j));
+                for (int j = 0; j < 2 * EBO; ++j) through.put16(own + 1024 * j, piece(j));
             } else {
 #pragma unroll
-                for (int j = 0; j < 2 * EBO; ++j) *(u32x4_t *)(own + 1024 * j) = piece(j);
+                for (int j = 0; j < 2 * EBO; ++j) *(u32x4_t *)(pp + own + 1024 * j) = piece(j);
             }
         }
         if (row_ok && h == 0 && grp == 0) {

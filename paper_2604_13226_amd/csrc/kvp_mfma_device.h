@@ -81,13 +81,6 @@ __device__ __forceinline__ u32x4_t load16_nowait(const void *p)
     asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(p) : "memory");
     return v;
 }
-// A store that goes on to memory at once, for what a later launch reads on another XCD.  (A line that stays dirty in the L2
-// leaves it at the end of the launch, all of them together.)  The compiler does not see a store in the asm, so the wait states
-// before a vector instruction may overwrite the data of a 16-byte store stand here.
-__device__ __forceinline__ void store16_through(void *p, const u32x4_t &v)
-{
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
-}
 // a pointer the program knows to be wave-uniform, made so for the compiler too
 __device__ __forceinline__ const char *uniform_ptr(const void *p)
 {
@@ -96,6 +89,14 @@ __device__ __forceinline__ const char *uniform_ptr(const void *p)
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return (const char *)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
+// Stores that go on to memory at once (sc1), for what a later launch reads on another XCD.  (A line that stays dirty in the L2
+// leaves it at the end of the launch, all of them together.)  `bytes` from `base` on, both wave-uniform, can be written.
+struct ThroughStore {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ ThroughStore(void *base, int bytes)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(base), 0, bytes, 0x00027000)) {}
+    __device__ __forceinline__ void put16(int at, const u32x4_t &v) const { __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, at, 0, 16); }
+};
 // same with a full per-lane address
 __device__ __forceinline__ void load_to_lds_16(const void *gptr, uint32_t lds_addr)
 {
