@@ -862,7 +862,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 const int r = 4 * (j & 3);
                 return __builtin_bit_cast(u32x4_t, make_float4(o[r], o[r + 1], o[r + 2], o[r + 3]));
             };
-            if (a.merged_elsewhere) {
+            if (NW == 4 && a.merged_elsewhere) {
                 const ThroughStore through(pp, (int)part_rows_bytes(a.bm, D, 0));
 #pragma unroll
                 for (int j = 0; j < 4 * EB; ++j) through.put16(own + 1024 * j, piece(j));
@@ -911,7 +911,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
                 return u32x4_t{lo.x, lo.y, hi.x, hi.y};
             };
             static_assert(KS == 2 || EBO == EB, "2 EBO pieces, 1024 bytes apart");
-            if (a.merged_elsewhere) {
+            if (NW == 4 && a.merged_elsewhere) {
                 const ThroughStore through(pp, (int)part_rows_bytes(a.bm, D, 1));
 #pragma unroll
                 for (int j = 0; j < 2 * EBO; ++j) through.put16(own + 1024 * j, piece(j));
