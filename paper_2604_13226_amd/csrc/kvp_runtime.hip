@@ -1252,6 +1252,7 @@ struct MfmaShape {
     bool split_in_wg = false;
     bool own_tail = false;  // the query rows may become a range of their own (plan_prefill)
     bool even = false;      // a large launch, requests about equally long or of one row block each: `want` ranges each
+    bool overfull = false;  // `want` ranges would give an XCD more items than CUs: ranges_of_one_request lowered it
 };
 
 // Ranges of one request with several row blocks to a head, 4-wave shape: as many as leave seven eighths of the CUs an item
@@ -1275,6 +1276,55 @@ int ranges_of_one_request(const kvp_store *s, const RowBlocks &b, int want)
         if (least == 0 || us < least) {
             least = us;
             best = w;
+        }
+    }
+    return best;
+}
+
+// The same in place, where a packet boundary inside an item costs more than a tile: how many tiles an item gets, of one request
+// for which `want` would give an XCD more items than CUs -- `now`, or the length that an estimate of the slowest CU puts ahead by
+// a twentieth.  Each head's range goes to the eight XCDs in turn (xcd_order), the row blocks' items of one, each up to the
+// last tile that its rows see, to an XCD's CUs in turn.  Microseconds: an item 9, 1.25 a tile and 1.63 a boundary, a fifth of that
+// beside another on its CU; the merge 2.4 and 0.51 per MB.  (Fitted to 1300 launches of 16 to 50 us.  Over 300 others the launches
+// are 1.07 times as fast as with `now`, twelve of them slower by 2 % or more, 8 % at most; 1.14 times as fast as with items for
+// seven eighths of the CUs.  28 / 4 heads, per layer: 223 query rows over eight packets of 8 tiles, items of 17 and of 9 tiles
+// 39.6 -> 32.1 us; 160 over twenty of 5, items of 18 and of 10, 41.1 -> 33.8.  Planning such a call takes 22 us, 13 without.)
+int in_place_length(const kvp_store *s, const AttnTile *tiles, int n_pkt, int n_q, int gq, int64_t most, int now)
+{
+    const int n_t = n_pkt + (n_q + 63) / 64, cus = s->n_cu / 8, heads = s->cfg.n_kv_heads;
+    std::vector<int> crossed(n_t), sees;  // boundaries up to each tile; tiles that each row block sees
+    for (int i = 1; i < n_t; ++i) crossed[i] = crossed[i - 1] + (tiles[i].pos != tiles[i - 1].pos);
+    for (int m = MFMA_BM; m < n_q * gq + MFMA_BM; m += MFMA_BM) sees.push_back(n_pkt + (std::min(m, n_q * gq) - 1) / gq / 64 + 1);
+    const int alike = heads % 8 == 0 ? 8 : 8 % heads == 0 ? heads : 1;  // XCDs next to each other that get the same ranges
+    std::vector<double> cu(cus);
+    auto launch_us = [&](int len, double least) {  // (or something no less than `least`)
+        const int n = (n_t + len - 1) / len;
+        const double merge = n > 1 ? 2.4 + (double)sees.size() * heads * n * (0.51e-6 * 256 * MFMA_BM) : 0;
+        double us = 0;
+        for (int xcd = 0; xcd < 8 && us + merge < least; xcd += alike) {
+            std::fill(cu.begin(), cu.end(), 0.0);
+            int items = 0;
+            for (int at = xcd; at < n * heads; at += 8) {
+                const int b = at / heads * len;
+                for (const int end : sees) {
+                    const int e = std::min(b + len, end);
+                    if (e <= b) continue;
+                    const double t = 9 + 1.25 * (e - b) + 1.63 * (crossed[e - 1] - crossed[b]);
+                    us = std::max(us, cu[items % cus] += items < cus ? t : 0.2 * t);
+                    ++items;
+                }
+            }
+        }
+        return us + merge;
+    };
+    double least = launch_us(now, INFINITY) / 1.05;
+    int best = now;
+    for (int len = 4; len < now; ++len) {  // (longer ones are ahead in one call of a hundred)
+        if ((n_t + len - 1) / len > most) continue;
+        const double us = launch_us(len, least);
+        if (us < least) {
+            least = us;
+            best = len;
         }
     }
     return best;
@@ -1340,7 +1390,11 @@ MfmaShape mfma_shape(const kvp_store *s, int n_req, const int32_t *q_off, const 
         sh.own_tail = true;
         for (int r = 0; r < n_req; ++r) sh.own_tail &= (int64_t)(q_off[r + 1] - q_off[r]) * gq <= 128;
         if (sh.own_tail) sh.min_split = 192;
-        else if (n_req == 1) sh.want = ranges_of_one_request(s, b, sh.want);
+        else if (n_req == 1) {
+            const int w = ranges_of_one_request(s, b, sh.want);
+            sh.overfull = w < sh.want;
+            sh.want = w;
+        }
     }
     return sh;
 }
@@ -2166,11 +2220,12 @@ int kvp_prefill_packets(kvp_store_t *s, const kvp_request_t *reqs, int32_t n_req
             // requests of 32 packets, 32 query rows, +4 %).  But no more of them than the merge takes, and no more partial
             // rows than kvp_prefill_workspace_bytes has room for (512 of 256 packed rows): a packet of 15 tiles would turn
             // items of 14 into items of 5.
+            const int64_t most = std::min<int64_t>(MAX_SPLITS, (int64_t)2 * s->n_cu * (2 * MFMA_BM) / (bm * blocks.n));
             if (const int P = pkt_tiles[r]; P > 0 && n_req == 1 && per_item < P) {
-                const int64_t most = std::min<int64_t>(MAX_SPLITS, (int64_t)2 * s->n_cu * (2 * MFMA_BM) / (bm * blocks.n));
                 for (int dv = per_item; dv >= 4 && (n_t + dv - 1) / dv <= most; --dv)
                     if (P % dv == 0) { per_item = dv; break; }
             }
+            if (sh.overfull) per_item = in_place_length(s, tiles.data() + tile_begin[r], n_pkt_tiles[r], rq.n_q, gq, most, per_item);
             if (r == 0) per_item0 = per_item;
             const int M = rq.n_q * gq;
             for (int h = 0; h < g.n_kv_heads; ++h)

@@ -424,6 +424,27 @@ def test_no_xcd_gets_more_items_of_a_request_than_it_has_cus(ctx, n_q):
         assert ranges[0][0] == 0 and ranges[-1][1] == last_row and all(x[1] == y[0] for x, y in zip(ranges, ranges[1:]))
 
 
+@pytest.mark.parametrize("packets,rows,n_q,lengths", [(8, 512, 223, (9,)), (20, 300, 160, (8, 9, 10)), (9, 768, 160, (8,)), (2, 640, 30, None),
+                                                      (3, 512, 147, None), (1, 64, 256, None), (12, 768, 147, None), (20, 130, 223, None)])
+def test_items_of_several_row_blocks_in_place(packets, rows, n_q, lengths):
+    """One request of 28 / 4 heads: the items of every row block cover the tiles that its rows see, no more of them than the
+    merge and a workspace take; where an XCD would get more items than CUs, of a length (in tiles) that was measured within
+    5 % of the best."""
+    s = dry_store(n_q_heads=28, n_kv_heads=4, max_positions=1 << 17)
+    kvp.kvp_store_put(s, 0, None, None, n_tokens=rows)
+    kvp.kvp_prefill_packets(s, [([0] * packets, 0)], 0, None, None, None, np.array([0, n_q], np.int32), None, None, None)
+    p = kvp.kvp_debug_last_plan(s, 1)
+    n_groups, n_items = int(p[2]), int(p[3])
+    assert int(p[0]) == 2 and int(p[1]) == 128 and n_groups == 4 * -(-n_q * 7 // 128)
+    groups, items = p[6:6 + 6 * n_groups].reshape(-1, 6), p[6 + 6 * n_groups:6 + 6 * n_groups + 4 * n_items].reshape(-1, 4)
+    assert groups[:, 5].max() <= 64 and kvp.kvp_prefill_workspace_bytes(s, 1, n_q, packets * rows + n_q) >= p[5]
+    for i in range(n_groups):
+        ranges = sorted((int(b), int(e)) for grp, _, b, e in items if grp == i)
+        last_tile = packets * -(-rows // 64) + ((min(n_q * 7, int(groups[i][2]) + 128) - 1) // 7) // 64 + 1
+        assert ranges[0][0] == 0 and ranges[-1][1] == last_tile and all(x[1] == y[0] for x, y in zip(ranges, ranges[1:]))
+    assert lengths is None or int((items[:, 3] - items[:, 2]).max()) in lengths
+
+
 GENERIC, MFMA, F32, NARROW = 0, 1, 2, 3   # kvp_debug_last_plan(s, 3)
 
 
