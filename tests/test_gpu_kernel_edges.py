@@ -60,6 +60,7 @@ def test_bf16_head_dims_64_and_256(gpu_device, monkeypatch, d, g, ctx, n_q, page
 @pytest.mark.parametrize("dtype,d,g,ctx,n_q,paged,target", [
     ("f32", 64, 2, 40, 20, False, None), ("f32", 128, 4, 100, 33, True, "4000"), ("f32", 256, 1, 30, 70, False, None),
     ("bf16", 64, 4, 70, 40, True, None), ("bf16", 64, 7, 0, 65, False, "4000"), ("bf16", 256, 2, 100, 30, False, None),
+    ("bf16", 256, 2, 100, 30, False, "4000"), ("bf16", 256, 7, 300, 20, True, "4000"),
     # bf16, 128 columns, at most 32 packed rows: one tile of query rows, two of them, a later tile of a wave, split
     ("bf16", 128, 4, 40, 8, True, None), ("bf16", 128, 1, 17, 32, False, None), ("bf16", 128, 1, 300, 20, True, "1"),
     ("bf16", 128, 2, 700, 16, False, "4000"),
@@ -88,7 +89,9 @@ def test_an_infinity_in_v_reaches_only_the_rows_that_see_it(gpu_device, monkeypa
     at, col = (2 * n_q) // 3, d // 2 + 3
     clean = call(lambda vn: None)
     kernel = F32 if dtype == "f32" else NARROW if d == 128 and n_q * g <= 32 else MFMA
+    plan = kvp.kvp_debug_last_plan(store, 1)
     assert int(kvp.kvp_debug_last_plan(store, 3)[0]) == kernel
+    assert target != "4000" or int(plan[6 + 5]) > 1 or ctx + n_q <= 65     # the rows were cut
     for value in (float("inf"), float("nan")):
         def change(vn):
             vn[at, 0, col] = value
@@ -406,6 +409,21 @@ def test_splits_whose_weight_is_below_the_normal_range_count(gpu_device, monkeyp
         v[1] = 2.0 ** 60
     got, want = _merged(monkeypatch, d, splits, score, v, v_new)
     assert float((got / want - 1).abs().max()) <= 2.0 ** -8 + 2.0 ** -10 + 2.0 ** -13
+
+
+@pytest.mark.parametrize("d,splits", [(128, 2), (128, 5), (128, 17), (256, 2), (256, 5), (256, 17), (256, 33), (256, 41)])
+@pytest.mark.parametrize("g,n_q", [(4, 17), (1, 37)])
+def test_a_merge_of_eight_heads(gpu_device, monkeypatch, d, splits, g, n_q):
+    """As many groups as XCDs: items and merge of a head on one, partial rows left in its L2 (other tests have one or two heads,
+    whose rows are written through it and whose merge runs row by row)."""
+    import paper_2604_13226_amd as kvp
+    monkeypatch.setenv("KVP_ATTN_TARGET_ITEMS", str(8 * splits))
+    at_least = 256 if d == 128 else 64
+    w = _request("bf16", d, g, splits * at_least - n_q - 7, n_q, n_kv=8)
+    got = run_workload(w)
+    p = kvp.kvp_debug_last_plan(got["store"], 1)
+    assert LAST["kernel"] == MFMA and int(p[2]) == 8 and int(p[6 + 5]) == splits
+    compare(w, got, oracle_workload(w))
 
 
 @pytest.mark.parametrize("paged", [False, True])
