@@ -1264,7 +1264,7 @@ struct MfmaShape {
 // estimate everywhere, launches that fit became 0.93 to 1.08 times as fast.)
 int ranges_of_one_request(const kvp_store *s, const RowBlocks &b, int want)
 {
-    const int64_t heads = s->cfg.n_kv_heads, cus = s->n_cu / 8;
+    const int64_t heads = s->cfg.n_kv_heads, cus = std::max(1, s->n_cu / 8);
     double least = 0;
     int best = want;
     for (int w = want; w >= 1; --w) {
@@ -1283,15 +1283,16 @@ int ranges_of_one_request(const kvp_store *s, const RowBlocks &b, int want)
 
 // The same in place, where a packet boundary inside an item costs more than a tile: how many tiles an item gets, of one request
 // for which `want` would give an XCD more items than CUs -- `now`, or the length that an estimate of the slowest CU puts ahead by
-// a twentieth.  Each head's range goes to the eight XCDs in turn (xcd_order), the row blocks' items of one, each up to the
+// a twelfth.  Each head's range goes to the eight XCDs in turn (xcd_order), the row blocks' items of one, each up to the
 // last tile that its rows see, to an XCD's CUs in turn.  Microseconds: an item 9, 1.25 a tile and 1.63 a boundary, a fifth of that
 // beside another on its CU; the merge 2.4 and 0.51 per MB.  (Fitted to 1300 launches of 16 to 50 us.  Over 300 others the launches
-// are 1.07 times as fast as with `now`, twelve of them slower by 2 % or more, 8 % at most; 1.14 times as fast as with items for
-// seven eighths of the CUs.  28 / 4 heads, per layer: 223 query rows over eight packets of 8 tiles, items of 17 and of 9 tiles
-// 39.6 -> 32.1 us; 160 over twenty of 5, items of 18 and of 10, 41.1 -> 33.8.  Planning such a call takes 22 us, 13 without.)
+// are 1.07 times as fast as with `now`, four of them 2 to 4 % slower, and 1.14 times as fast as with items for seven eighths of the
+// CUs; of 150 with packets of mixed lengths 1.09, seventeen of them 2 to 11 % slower.  28 / 4 heads, per layer: 223 query rows
+// over eight packets of 8 tiles, items of 17 and of 9 tiles 39.6 -> 32.1 us; 160 over twenty of 5, items of 18 and of 10,
+// 41.1 -> 33.8.  Planning such a call takes 22 us, 13 without.)
 int in_place_length(const kvp_store *s, const AttnTile *tiles, int n_pkt, int n_q, int gq, int64_t most, int now)
 {
-    const int n_t = n_pkt + (n_q + 63) / 64, cus = s->n_cu / 8, heads = s->cfg.n_kv_heads;
+    const int n_t = n_pkt + (n_q + 63) / 64, cus = std::max(1, s->n_cu / 8), heads = s->cfg.n_kv_heads;
     std::vector<int> crossed(n_t), sees;  // boundaries up to each tile; tiles that each row block sees
     for (int i = 1; i < n_t; ++i) crossed[i] = crossed[i - 1] + (tiles[i].pos != tiles[i - 1].pos);
     for (int m = MFMA_BM; m < n_q * gq + MFMA_BM; m += MFMA_BM) sees.push_back(n_pkt + (std::min(m, n_q * gq) - 1) / gq / 64 + 1);
@@ -1317,7 +1318,7 @@ int in_place_length(const kvp_store *s, const AttnTile *tiles, int n_pkt, int n_
         }
         return us + merge;
     };
-    double least = launch_us(now, INFINITY) / 1.05;
+    double least = launch_us(now, INFINITY) / 1.08;
     int best = now;
     for (int len = 4; len < now; ++len) {  // (longer ones are ahead in one call of a hundred)
         if ((n_t + len - 1) / len > most) continue;
