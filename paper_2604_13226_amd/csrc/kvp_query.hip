@@ -339,17 +339,15 @@ __global__ __launch_bounds__(256) void combine_wave_kernel(CombineArgs a)
 
 // The MFMA kernel's rows: fp16 of 128 columns, scaled per row by a power of two that m and l carry along, or fp32 of 256.
 // They lie as its accumulators do (part_piece_at), pieces of neighbouring rows next to each other: a workgroup merges
-// sixteen pieces of four rows (a quarter of 256 columns: all 64 in one, up to sixteen splits, were 1.6 % slower per layer in the
-// mean of 50 calls and 4 % where the rows are few; 16 / 4 heads, 3K rows, 8 query rows 22.1 us, so 21.4), a quad of lanes reads
-// a piece of each, and wave w takes every fourth split from w on.  Each lane reads the (m, l) of its splits itself, and the sixteen lanes of a
-// row read all splits' m between them: weights are relative to the group's maximum in every wave, so that the waves' sums,
-// which pass through LDS once, only need adding.  (Relative to a wave's own they would overflow, or keep an infinity, where
-// the split does not count.)  (A wave per row, as above, takes 64
-// places of this layout with every load: 8K context, 27 splits, 26.6 us per layer of a step, so 26.1; with whole rows 26.4.)
-template <typename P, int D, int NB>
+// 16 ZC pieces of four rows, a quad of lanes reads a piece of each, and wave w takes every fourth split from w on.  Each lane
+// reads the (m, l) of its splits itself, and the sixteen lanes of a row read all splits' m between them: weights are relative to
+// the group's maximum in every wave, so that the waves' sums, which pass through LDS once, only need adding.  (Relative to a
+// wave's own they would overflow, or keep an infinity, where the split does not count.)  (A wave per row, as above, takes 64
+// places of this layout with every load: 8K context, 27 splits, 26.6 us per layer of a step, so 26.1; with whole rows 26.3.)
+template <typename P, int D, int NB, int ZC>
 __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
 {
-    constexpr int NC = 16 / (int)sizeof(P), W = 16 * NC;  // columns of a piece, and of a workgroup
+    constexpr int NC = 16 / (int)sizeof(P), W = 16 * NC * ZC;  // columns of a piece, and of a workgroup
     constexpr int RS = W + 4;  // (row stride in LDS: the four rows of a quad in banks of their own)
     __shared__ __attribute__((aligned(16))) float xo[4][4][RS];
     __shared__ float xl[4][4];
@@ -361,10 +359,10 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     const uint32_t x = blockIdx.x, gi = a.rows_first ? blockIdx.y : x;
     const int r0 = 4 * (int)(a.rows_first ? x / 16 * 16 + x % 8 * 2 + x / 8 % 2 : blockIdx.y);  // (a slot has a multiple of 64 rows)
     const char *base = a.partials + (int64_t)gi * stride * a.slot_bytes;
-    const char *piece = base + part_piece_at(D * (int)sizeof(P), r0 + row, 16 * (int)blockIdx.z + c), *ml = base + a.rows_bytes + (r0 + row) * 8;
+    const char *piece = base + part_piece_at(D * (int)sizeof(P), r0 + row, 16 * ZC * (int)blockIdx.z + c), *ml = base + a.rows_bytes + (r0 + row) * 8;
     float m[NM];
     float2 s[NB];
-    uint4 v[NB];
+    uint4 v[NB][ZC];
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
         const int sp = 16 * i + c;
@@ -375,7 +373,8 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
         const int sp = 4 * i + wave;
         const int64_t at = (int64_t)(sp < stride ? sp : stride - 1) * a.slot_bytes;
         s[i] = *(const float2 *)(ml + at);
-        v[i] = *(const uint4 *)(piece + at);
+#pragma unroll
+        for (int z = 0; z < ZC; ++z) v[i][z] = *(const uint4 *)(piece + at + 8192 * z);
     }
     const AttnGroup gp = a.groups[gi];
     const int ns = gp.n_splits;
@@ -400,15 +399,19 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
 #pragma unroll
         for (int i = 0; i < NB; ++i) wt[i] = exp2f(opaque(s[i].x) - mx);
     }
-    float l = 0.f, acc[NC] = {};
+    float l = 0.f, acc[ZC][NC] = {};
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         l += s[i].y * wt[i];
-        add_piece<P>(acc, v[i], wt[i]);
+#pragma unroll
+        for (int z = 0; z < ZC; ++z) add_piece<P>(acc[z], v[i][z], wt[i]);
     }
-    float *xp = &xo[wave][row][NC == 8 ? 16 * (c >> 1) + 4 * (c & 1) : 4 * c];
-    *(float4 *)xp = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    if constexpr (NC == 8) *(float4 *)(xp + 8) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+#pragma unroll
+    for (int z = 0; z < ZC; ++z) {
+        float *x = &xo[wave][row][16 * NC * z + (NC == 8 ? 16 * (c >> 1) + 4 * (c & 1) : 4 * c)];
+        *(float4 *)x = make_float4(acc[z][0], acc[z][1], acc[z][2], acc[z][3]);
+        if constexpr (NC == 8) *(float4 *)(x + 8) = make_float4(acc[z][4], acc[z][5], acc[z][6], acc[z][7]);
+    }
     if (c == 0) xl[wave][row] = l;
     __syncthreads();
     const int rr = r0 + wave;  // each wave writes one of the rows
@@ -500,23 +503,37 @@ template <typename T, int D> static void launch_combine_wave(const AttnArgs &a, 
     else launch(combine_wave_kernel<T, D, (D < 256 ? 40 : 24) / G>, grid, dim3(256), 0, st, c);
 }
 
+template <typename P, int D, int ZC> static void launch_combine_zc(const CombineArgs &c, dim3 grid, hipStream_t st)
+{
+    if (c.part_stride <= 4) launch(combine_pieces_kernel<P, D, 1, ZC>, grid, dim3(256), 0, st, c);
+    else if (c.part_stride <= 8) launch(combine_pieces_kernel<P, D, 2, ZC>, grid, dim3(256), 0, st, c);
+    else if (c.part_stride <= 16) launch(combine_pieces_kernel<P, D, 4, ZC>, grid, dim3(256), 0, st, c);
+    else if constexpr (ZC == 1) {
+        if (c.part_stride <= 24) launch(combine_pieces_kernel<P, D, 6, ZC>, grid, dim3(256), 0, st, c);
+        else if (c.part_stride <= 32) launch(combine_pieces_kernel<P, D, 8, ZC>, grid, dim3(256), 0, st, c);
+        else if (c.part_stride <= 40) launch(combine_pieces_kernel<P, D, 10, ZC>, grid, dim3(256), 0, st, c);
+        else launch(combine_pieces_kernel<P, D, 16, ZC>, grid, dim3(256), 0, st, c);
+    }
+}
+
 template <typename P, int D> static void launch_combine_pieces(const AttnArgs &a, dim3 grid, hipStream_t st)
 {
     CombineArgs c = combine_args(a, sizeof(P) == 2);
+    // 256 columns: all 64 pieces of the rows in one workgroup for up to sixteen splits (of more they would fill the registers), from
+    // three workgroups to a CU on; fewer are dealt out in quarters.  (Per layer, in one and in quarters: 16 / 4 heads, 3K rows, 8
+    // query rows 22.1 and 21.1 us; six requests of 32 / 8 heads, 13 query rows, 624 workgroups 27.9 and 27.6; eight with 12, 768, 50.6 and
+    // 51.5; eight with 39, 4096, 87.2 and 93.7.)
+    constexpr int Z = D * (int)sizeof(P) / 256;
+    const bool quarters = Z > 1 && (a.part_stride > 16 || (int64_t)grid.x * grid.y < 768);
     // As many groups as a multiple of eight: a group's workgroups are on one XCD, that of its items where those keep to one.  Others:
     // sixteen workgroups take 64 rows of a group, two on each XCD.  (Group by group there too, two XCDs read each line: per layer, 3.4K
     // rows of 28 / 4 heads with 76 query rows 18.0 us, so 15.6, and by whole rows, a wave each, 16.2; 16 / 2 heads, 145 query
     // rows over 6K 22.9, 19.9 and 20.5; in place, 160 over 3K of 28 / 4 heads 26.4, 23.2 and 24.5.)
     c.rows_first = grid.x % 8 != 0 && grid.x < 65536;
     if (c.rows_first) grid = dim3((grid.y + 15) / 16 * 16, grid.x);
-    grid.z = D * (int)sizeof(P) / 256;
-    if (a.part_stride <= 4) launch(combine_pieces_kernel<P, D, 1>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 8) launch(combine_pieces_kernel<P, D, 2>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 16) launch(combine_pieces_kernel<P, D, 4>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 24) launch(combine_pieces_kernel<P, D, 6>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 32) launch(combine_pieces_kernel<P, D, 8>, grid, dim3(256), 0, st, c);
-    else if (a.part_stride <= 40) launch(combine_pieces_kernel<P, D, 10>, grid, dim3(256), 0, st, c);
-    else launch(combine_pieces_kernel<P, D, 16>, grid, dim3(256), 0, st, c);
+    if (quarters) grid.z = Z;
+    if (quarters) launch_combine_zc<P, D, 1>(c, grid, st);
+    else launch_combine_zc<P, D, Z>(c, grid, st);
 }
 
 template <typename T> static void launch_combine_fp32_rows(const AttnArgs &a, dim3 grid, hipStream_t st)
