@@ -225,16 +225,22 @@ template <typename F> __device__ __forceinline__ float over_lanes(float x, F f) 
     swap32(x, y);
     return f(x, y);
 }
-__device__ __forceinline__ float max_over_quads(float x)  // over the sixteen lanes that have this one's place in their quad
+// the maximum over the lanes that have this one's place in their quad: of four quads, eight, or all sixteen
+template <int QUADS> __device__ __forceinline__ float max_over_quads(float x)
 {
     x = fmaxf(x, dpp<0x124>(x));  // turned by four within sixteen
     x = fmaxf(x, dpp<0x128>(x));  // and by eight
-    float y = opaque(x);
-    swap16(x, y);
-    x = fmaxf(x, y);
-    y = opaque(x);
-    swap32(x, y);
-    return fmaxf(x, y);
+    if constexpr (QUADS > 4) {
+        float y = opaque(x);
+        swap16(x, y);
+        x = fmaxf(x, y);
+    }
+    if constexpr (QUADS > 8) {
+        float y = opaque(x);
+        swap32(x, y);
+        x = fmaxf(x, y);
+    }
+    return x;
 }
 // w of lane CPR * (this lane / CPR) + I
 template <int CPR, int I> __device__ __forceinline__ float split_weight(float w, int sg)
@@ -351,7 +357,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     constexpr int RS = W + 4;  // (row stride in LDS: the four rows of a quad in banks of their own)
     __shared__ __attribute__((aligned(16))) float xo[4][4][RS];
     __shared__ float xl[4][4];
-    constexpr int NM = (4 * NB + 15) / 16;
+    constexpr int NM = (4 * NB + 15) / 16, QUADS = NB < 4 ? 4 * NB : 16;  // (up to eight splits, fewer quads hold all m)
     const int lane = threadIdx.x & 63, row = lane & 3, c = lane >> 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int stride = a.part_stride;
@@ -365,7 +371,7 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     uint4 v[NB][ZC];
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
-        const int sp = 16 * i + c;
+        const int sp = 16 * i + c % QUADS;
         m[i] = *(const float *)(ml + __umul24(sp < stride ? sp : stride - 1, a.slot_bytes));
     }
 #pragma unroll
@@ -382,10 +388,10 @@ __global__ __launch_bounds__(256) void combine_pieces_kernel(CombineArgs a)
     float mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
-        if (16 * i + c >= ns) m[i] = -INFINITY;
+        if (16 * i + c % QUADS >= ns) m[i] = -INFINITY;
         mx = fmaxf(mx, m[i]);
     }
-    mx = fmaxf(max_over_quads(mx), -3.4028235e38f);  // (finite, so that a split without visible rows has weight zero below)
+    mx = fmaxf(max_over_quads<QUADS>(mx), -3.4028235e38f);  // (finite, so that a split without visible rows has weight zero below)
     bool low = false;  // weights below 2^-126, for which the instruction alone gives zero
 #pragma unroll
     for (int i = 0; i < NM; ++i) low |= m[i] - mx < -126.f && m[i] > -INFINITY;
