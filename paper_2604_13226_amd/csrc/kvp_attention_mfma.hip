@@ -853,7 +853,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs &a)
         }
     } else if constexpr (SPLIT_P) {
         // 256 columns: as the accumulators lie, then (m, l) of each row.  (Row by row, a layer of a step over 2K rows took 32.3 us,
-        // now 30.5; four paged requests of 3 to 8 passages 58.6 and 56.4.  64 columns: a launch that is not split became 2 % slower.)
+        // now 30.7; four paged requests of 3 to 8 passages 58.8 and 57.9.  64 columns: a launch that is not split became 2 % slower.)
         if (it.part_slot >= 0 && row_ok) {
             char *pp = (char *)a.partials + (int64_t)it.part_slot * part_slot_bytes(a.bm, D, 0);
             const int own = part_piece_at(4 * D, rr, h);

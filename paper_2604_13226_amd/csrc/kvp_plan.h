@@ -205,8 +205,9 @@ __host__ __device__ inline int64_t part_slot_bytes(int bm, int d, int f16) { ret
 
 // Where piece c (16 bytes) of the MFMA kernel's partial rows lies in its slot: pieces c of 32 rows follow each other.  fp32: columns
 // 4 c + {0..3}; fp16: 16 (c / 2) + 4 (c % 2) + {0..3, 8..11}, the eight that one lane holds in neighbouring accumulators.  Behind
-// the rows of a slot, (m, l) of each row.  (Row by row, the accumulators had to pass through LDS: an epilogue of 1.5 us, now
-// 1.0.  Per layer of a step: 2.9K rows 16.6 -> 16.3 us, 8K 26.4 -> 26.1, 6K of 28 / 4 heads 23.2 -> 23.0; pruned 22.9 -> 22.7.)
+// the rows of a slot, (m, l) of each row.  (Row by row, fp16 ones passed through LDS: an epilogue of 1.5 us, now
+// 0.75, or 1.6 with rows that go on through the L2.  Per layer of a step: 2.9K rows 16.6 -> 16.4 us, 8K 26.3 -> 26.15, 6K of 28 / 4
+// heads, through the L2, 23.2 -> 22.8; pruned 22.95 -> 22.8.)
 __host__ __device__ inline int part_piece_at(int row_bytes, int row, int c) { return (row >> 5) * 32 * row_bytes + c * 512 + (row & 31) * 16; }
 
 // launchers (defined next to their kernels)

@@ -170,7 +170,8 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(AttnArgs a)
 //   m = max m_i;  l = sum l_i 2^(m_i - m);  O = sum O~_i 2^(m_i - m) / l.
 // A split that saw no visible row has m_i = -inf, l_i = 0 and contributes nothing.
 // ---------------------------------------------------------------------------------
-// fp32 rows: one wave per packed row.  A partial row is CPR pieces of 16 bytes, and the 64 lanes hold the pieces of
+// fp32 rows that lie one behind the other (the fp32, the narrow and the generic kernel's, the MFMA kernel's at 64 columns):
+// one wave per packed row.  A partial row is CPR pieces of 16 bytes, and the 64 lanes hold the pieces of
 // G = 64 / CPR splits at a time.  The first NB pieces of every lane are requested before anything is known about
 // the group.  Nothing of the merge passes through LDS: the maximum and the sum over the splits'
 // (m, l) are lane permutes, a split's weight reaches its lanes by a broadcast within sixteen lanes (or a read into a
@@ -179,10 +180,9 @@ __global__ __launch_bounds__(256) void attention_generic_kernel(AttnArgs a)
 //
 // Bound: latency -- a launch (1.6 us in a chain of empty kernels), the arguments, one trip for the
 // partial rows, the merge.  A layer of a step, with shuffles through LDS for all of that, 8-byte loads, two-byte
-// stores and the whole AttnArgs to fetch, and now: 8K context 28.2 -> 27.1 us (22 splits), 3.4K rows 18.45 ->
-// 17.4 (14), one token at 8K 13.3 -> 12.5 (24), in place 19.4 -> 17.7 (33).  Up to eight splits had a kernel
-// with a thread per piece and the (m, l) in LDS: fp32, 2.3K rows 35.2 -> 34.0 us; 64 columns, four
-// paged requests 27.6 -> 26.9; one token over eight contexts of 16.9K rows 87.9 -> 86.8.
+// stores and the whole AttnArgs to fetch, and now: one token at 8K 13.3 -> 12.5 us (24 splits).  Up to eight
+// splits had a kernel with a thread per piece and the (m, l) in LDS: fp32, 2.3K rows 35.2 -> 34.0 us; 64 columns, four
+// paged requests 27.6 -> 26.9.
 constexpr int COMBINE_ROWS = 4;         // rows (waves) per workgroup
 constexpr int COMBINE_MAX_SPLITS = 64;  // the planner's bound on splits per group
 

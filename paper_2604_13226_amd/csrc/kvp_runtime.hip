@@ -1257,10 +1257,11 @@ struct MfmaShape {
 
 // Ranges of one request with several row blocks to a head, 4-wave shape: as many as leave seven eighths of the CUs an item
 // (`want`), or fewer if an XCD then had more items than CUs.  All row blocks of a head that read a range run on one XCD
-// (xcd_order), and those that share a CU end last.  The number comes from an estimate as in launch_time, for ranges of one
-// length: an item 6 us and 1.5 a tile, 0.6 of it more beside another on its CU, a range with the query rows 1.4 tiles later; the
-// merge 2.4 and 0.25 per MB.  (Per layer, 28 / 4 heads: 2.5K rows with 223 query rows, 39 items on an XCD, 30.6 -> 25.8 us; 3.1K
-// with 197, 33, 31.7 -> 27.0; with the gather, 2.3K with 160, 36, 31.6 -> 24.8, 5.5K with 160, 36, 43.1 -> 35.1.  Left to the
+// (xcd_order), and those that share a CU end last.  The number comes from an estimate for ranges of one length, with numbers of
+// its own, fitted to such launches: an item 6 us and 1.5 a tile, 0.6 of it more beside another on its CU, a range with the query
+// rows 1.4 tiles later; the merge 2.4 and 0.25 per MB.  (Attention per layer, 28 / 4 heads: 2.4K rows with 223 query rows, 39 items
+// on an XCD, 27.8 -> 24.4 us; 2.3K with 160, 36, 23.4 -> 19.3; 5.5K with 160, 36, 34.9 -> 30.8; 3.1K with 197, 33, 30.2 and 30.5.
+// Over 70 calls of any head counts that it cuts otherwise 1.09 times as fast in the mean, three of them slower.  Left to the
 // estimate everywhere, launches that fit became 0.93 to 1.08 times as fast.)
 int ranges_of_one_request(const kvp_store *s, const RowBlocks &b, int want)
 {
